@@ -167,6 +167,12 @@ dd_status dd_create(const int dims[4], const int block[4], const int bcs[4], voi
         delete ctx;
         return DD_HIP_ERROR;
     }
+    if (hipDeviceGetAttribute(&ctx->ncu, hipDeviceAttributeMultiprocessorCount, ctx->device) != hipSuccess ||
+        ctx->ncu < 1) {
+        g_create_error = "dd_create: no compute-unit count";
+        delete ctx;
+        return DD_HIP_ERROR;
+    }
     {
         // the device address of dd_sap_noalloc's fixed scratch array, looked
         // up once per device while that device is current

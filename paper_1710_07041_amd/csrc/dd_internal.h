@@ -140,6 +140,7 @@ struct dd_ctx {
     dd::GeomHost g{};
     hipStream_t stream = nullptr;
     int device = 0;
+    int ncu = 256; // compute units of the device
     bool has_field = false;
     double csw = 0;
     bool link_su3 = false; // every link is SU(3) to FP64 rounding (checked at ingest)

@@ -53,6 +53,7 @@ struct SArgs {
     const int *blocks; // block ids of the swept colour
     int nblk;
     int nrhs;
+    int rpg; // right-hand sides per workgroup (rhs_per_group)
     int nmr;
     int mode; // 0: psi = 0 everywhere; 1: psi_B = 0 on this colour; 2: general
     double m0[MAXRHS];
@@ -64,6 +65,19 @@ struct SArgs {
     int r12;              // links stored as SU(3): read two rows, rebuild the third
     int write_r;          // plain sweep: store the block residual for the next visit
 };
+
+// The block (grid x) and the right-hand sides [r0, r1) (grid y) of this
+// workgroup.  False when none of them is active (uniform: nothing to do).
+__device__ __forceinline__ bool sweep_part(const SArgs &a, int &b, int &r0, int &r1)
+{
+    b = a.blocks[xcd_remap(blockIdx.x, gridDim.x)];
+    r0 = blockIdx.y * a.rpg;
+    r1 = min(r0 + a.rpg, a.nrhs);
+    if (!a.active) return true;
+    bool any = false;
+    for (int r = r0; r < r1; ++r) any |= a.active[r] != 0;
+    return any;
+}
 
 // The MR coefficient of one right-hand side: the dot products <q, r> and
 // <q, q> over the block (DPP sums within each wavefront, then a fixed-order
@@ -124,8 +138,8 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(RES::waves))
     constexpr bool CARRY = SAP_CARRY<S>;
     __shared__ Lds<A> L;
     __shared__ DelStore<A, RES> D;
-    const int i = xcd_remap(blockIdx.x, gridDim.x);
-    const int b = a.blocks[i];
+    int b, rhs0, rhs1;
+    if (!sweep_part(a, b, rhs0, rhs1)) return;
     const int s = threadIdx.x;
     const int lane = s & 63, wave = s >> 6;
     int bc[4];
@@ -141,7 +155,7 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(RES::waves))
         for (int e = 0; e < RES::ncl; ++e) cl[e] = ldc_stream<A>(cp + e * BS);
     }
 
-    for (int r = 0; r < a.nrhs; ++r) {
+    for (int r = rhs0; r < rhs1; ++r) {
         // with nmr = 0 the previous right-hand side's last t-hop reads are
         // not yet fenced by an MR barrier
         __syncthreads();
@@ -428,8 +442,8 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(RES::waves))
     __shared__ cx<A> F1[18][BS / 2]; // Cholesky factor of chiral half 1 of the odd sites
     Lds<A> &L = SH.full;
     EoLds<A> &E = SH.eo;
-    const int i = xcd_remap(blockIdx.x, gridDim.x);
-    const int b = a.blocks[i];
+    int b, rhs0, rhs1;
+    if (!sweep_part(a, b, rhs0, rhs1)) return;
     const int tid = threadIdx.x, s = eo_site(tid), k = tid & (BS / 2 - 1);
     const bool odd = tid >= BS / 2; // uniform over a wavefront
     const int lane = tid & 63, wave = tid >> 6;
@@ -441,7 +455,7 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(RES::waves))
     load_links4<A, true>(links + (long)b * 4 * 9 * BS + s, a.r12, (A)(-0.5), U);
     const vec2_t<S> *cp0 = clov + (long)b * 36 * BS + s;
 
-    for (int r = 0; r < a.nrhs; ++r) {
+    for (int r = rhs0; r < rhs1; ++r) {
         if (a.active && !a.active[r]) continue; // uniform over the workgroup
         const A diag = (A)(4.0 + (a.m0_dev ? a.m0_dev[r] : a.m0[r]));
         const vec2_t<S> *__restrict__ eta = eta0 + (a.eta_off ? a.eta_off[r] : 0);
@@ -601,8 +615,34 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(RES::waves))
     }
 }
 
+// Right-hand sides per workgroup.  A workgroup runs its right-hand sides one
+// after another with the block's fields loaded once, so a lattice that fills
+// the chip takes them all in one workgroup; one with fewer blocks of a colour
+// than `slots` (workgroups that run at once) leaves CUs idle unless the
+// right-hand sides are dealt to several workgroups of the block.  The estimate
+// is rounds of workgroups times the work of one, the field loads counting as a
+// quarter of a right-hand side's visit (32^3x64, FP32: 307 us a sweep with
+// one, 246 us each with twelve).  A split has to promise 5%.  Measured, twelve
+// cycles in FP32: 16^4 with three right-hand sides 1835 -> 873 us a call
+// (three workgroups a block), the 16^3x32 solve with three 14.0 -> 12.0 ms
+// (two and one); one workgroup a block stays where the blocks fill the chip.
+int rhs_per_group(int nblk, int nrhs, int slots)
+{
+    int best = nrhs;
+    double cost = 0;
+    for (int rpg = nrhs; rpg >= 1; --rpg) {
+        const long wgs = (long)nblk * ((nrhs + rpg - 1) / rpg);
+        const double c = (double)((wgs + slots - 1) / slots) * (rpg + 0.25);
+        if (rpg == nrhs || c < 0.95 * cost) {
+            best = rpg;
+            cost = c;
+        }
+    }
+    return best;
+}
+
 template <typename S, typename A, typename RES, bool EO, typename SF = S>
-Status sweep(dd_ctx *ctx, const SArgs &a, int prec, const void *eta, void *psi, void *faces, void *resid, bool quiet)
+Status sweep(dd_ctx *ctx, SArgs a, int prec, const void *eta, void *psi, void *faces, void *resid, bool quiet)
 {
     // algorithmic traffic of one colour sweep: links + clover once, eta (or
     // the carried residual), psi (read only when nonzero), psi written and,
@@ -621,13 +661,16 @@ Status sweep(dd_ctx *ctx, const SArgs &a, int prec, const void *eta, void *psi, 
     const int cls = EO ? (prec == DD_F64 ? K_SAP_EO_F64 : prec == DD_F32 ? K_SAP_EO_F32 : K_SAP_EO_F16)
                        : (prec == DD_F64 ? K_SAP_F64 : prec == DD_F32 ? K_SAP_F32 : K_SAP_F16);
     ProfScope ps(ctx->prof, ctx->stream, cls, by, fl, !quiet);
+    // RES::waves wavefronts per SIMD: that many four-wavefront workgroups per CU
+    a.rpg = rhs_per_group(a.nblk, a.nrhs, ctx->ncu * RES::waves);
+    const dim3 grid(a.nblk, (a.nrhs + a.rpg - 1) / a.rpg);
     if constexpr (EO)
-        k_sap_sweep_eo<S, A, RES><<<a.nblk, BS, 0, ctx->stream>>>(
+        k_sap_sweep_eo<S, A, RES><<<grid, BS, 0, ctx->stream>>>(
             static_cast<const vec2_t<S> *>(eta), static_cast<vec2_t<S> *>(psi),
             static_cast<const vec2_t<S> *>(ctx->links[prec].p), static_cast<const vec2_t<S> *>(ctx->clover[prec].p),
             static_cast<vec2_t<S> *>(faces), a);
     else
-        k_sap_sweep<S, A, RES, SF><<<a.nblk, BS, 0, ctx->stream>>>(
+        k_sap_sweep<S, A, RES, SF><<<grid, BS, 0, ctx->stream>>>(
             static_cast<const vec2_t<S> *>(eta), static_cast<vec2_t<S> *>(psi),
             static_cast<const vec2_t<SF> *>(ctx->links[fprec].p), static_cast<const vec2_t<SF> *>(ctx->clover[fprec].p),
             static_cast<vec2_t<S> *>(faces), static_cast<vec2_t<S> *>(resid), a);
