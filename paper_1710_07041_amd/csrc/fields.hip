@@ -226,6 +226,23 @@ __global__ __launch_bounds__(TPB) void k_su3_deviation(const double2 *__restrict
     }
 }
 
+// flag <- 1 if some site's packed clover half is not sigma . F, i.e. one of its
+// mirrored slots is not the sign change of what load_clover_half puts there.
+__global__ __launch_bounds__(TPB) void k_clover_mirror(const double2 *__restrict__ C, int *__restrict__ flag, int nblocks)
+{
+    const int b = blockIdx.x >> 1, s = threadIdx.x;
+    if (b >= nblocks) return;
+    const double2 *c = C + ((long)b * 36 + (blockIdx.x & 1) * 18) * BS + s;
+    const double2 d0 = c[0], d1 = c[BS], d2 = c[2 * BS];
+    bool bad = !(d1.y == -d0.x && d2.x == -d0.y && d2.y == -d1.x);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        const double2 u = c[SIG_MIRROR[k] * BS], v = c[(15 + k) * BS];
+        bad |= !(v.x == -u.x && v.y == -u.y);
+    }
+    if (__any(bad) && (s % 64) == 0) atomicOr(flag, 1);
+}
+
 // elementwise complex conversion FP64 -> S (round to nearest even)
 template <typename S>
 __global__ __launch_bounds__(TPB) void k_convert_from64(const double2 *__restrict__ in, vec2_t<S> *__restrict__ out,
@@ -317,11 +334,29 @@ Status convert_field(hipStream_t st, const double2 *src, void *dst, int prec, lo
     return Status::ok();
 }
 
+// Finds whether the packed FP64 clover term is sigma . F everywhere (its FP32
+// and FP16 copies then are too: rounding is symmetric in the sign).  Waits.
+Status check_clover_mirror(dd_ctx *ctx)
+{
+    DevBuf flag;
+    DD_TRY(flag.alloc(sizeof(int)));
+    DD_HIP_TRY(hipMemsetAsync(flag.p, 0, sizeof(int), ctx->stream));
+    k_clover_mirror<<<2 * ctx->g.nblocks, TPB, 0, ctx->stream>>>(ctx->clover[DD_F64].as<double2>(), flag.as<int>(),
+                                                                 ctx->g.nblocks);
+    DD_HIP_TRY(hipGetLastError());
+    int h = 1;
+    DD_HIP_TRY(hipMemcpyAsync(&h, flag.p, sizeof(int), hipMemcpyDeviceToHost, ctx->stream));
+    DD_HIP_TRY(hipStreamSynchronize(ctx->stream));
+    ctx->clover_sigma = h == 0;
+    return Status::ok();
+}
+
 } // namespace
 
 Status build_fields(dd_ctx *ctx, const double *U_dev, double csw)
 {
     const GeomHost &g = ctx->g;
+    ctx->clover_sigma = false; // until checked
     CanonGeom cg = canon_geom(g);
     long nl = (long)g.nblocks * 4 * 9 * BS; // complex entries of the link field
     long nc = (long)g.nblocks * 36 * BS;    // complex slots of the clover field
@@ -350,19 +385,20 @@ Status build_fields(dd_ctx *ctx, const double *U_dev, double csw)
     for (double d : hdev) worst = std::max(worst, d);
     ctx->link_su3 = worst <= SU3_TOL;
     ctx->link_r12 = ctx->link_su3;
-    return Status::ok();
+    return check_clover_mirror(ctx);
 }
 
 Status set_clover_canon(dd_ctx *ctx, const double *C_dev)
 {
     const GeomHost &g = ctx->g;
+    ctx->clover_sigma = false; // until checked
     long nc = (long)g.nblocks * 36 * BS;
     k_clover_pack<<<g.nblocks, TPB, 0, ctx->stream>>>(reinterpret_cast<const double2 *>(C_dev),
                                                       ctx->clover[DD_F64].as<double2>(), canon_geom(g), g.nblocks);
     DD_HIP_TRY(hipGetLastError());
     DD_TRY(convert_field(ctx->stream, ctx->clover[DD_F64].as<double2>(), ctx->clover[DD_F32].p, DD_F32, nc));
     DD_TRY(convert_field(ctx->stream, ctx->clover[DD_F64].as<double2>(), ctx->clover[DD_F16].p, DD_F16, nc));
-    return Status::ok();
+    return check_clover_mirror(ctx);
 }
 
 Status pack_spinor(dd_ctx *ctx, const double *canon, void *blocked, int prec, int nrhs)

@@ -63,6 +63,7 @@ struct SArgs {
     const int *active;    // right-hand sides with active[r] == 0 are skipped (nullable)
     int publish;          // write the face buffers for the next sweep
     int r12;              // links stored as SU(3): read two rows, rebuild the third
+    int sig;              // the clover term is sigma . F: mirrored slots are not read
     int write_r;          // plain sweep: store the block residual for the next visit
 };
 
@@ -152,7 +153,8 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(RES::waves))
     if (RES::clover || RES::clover_half) {
         const vec2_t<SF> *cp = clov + (long)b * 36 * BS + s;
 #pragma unroll
-        for (int e = 0; e < RES::ncl; ++e) cl[e] = ldc_stream<A>(cp + e * BS);
+        for (int e = 0; e < RES::ncl; ++e)
+            if (clover_reads(RES::sigma, e)) cl[e] = ldc_stream<A>(cp + e * BS);
     }
 
     for (int r = rhs0; r < rhs1; ++r) {
@@ -464,13 +466,11 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(RES::waves))
         // clover half 0 (odd sites factor it in place below, so it is
         // reloaded for every right-hand side)
         cx<A> cl[18];
-#pragma unroll
-        for (int e = 0; e < 18; ++e) cl[e] = ldc<A>(cp0 + e * BS);
+        load_clover_half<A>(cp0, a.sig, cl);
         if (odd) {
             // factor of chiral half 1 of A_oo = (4 + m0) + C, kept in LDS
             cx<A> c1[18];
-#pragma unroll
-            for (int e = 0; e < 18; ++e) c1[e] = ldc<A>(cp0 + (18 + e) * BS);
+            load_clover_half<A>(cp0 + 18 * BS, a.sig, c1);
             chol_half<A>(c1, diag);
 #pragma unroll
             for (int e = 0; e < 18; ++e) F1[e][k] = c1[e];
@@ -559,8 +559,7 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(RES::waves))
                 // the same address at every MR step: hide that, or the loads
                 // leave the loop and the half is held in registers
                 asm volatile("" : "+v"(cp1));
-#pragma unroll
-                for (int e = 0; e < 18; ++e) c2[e] = ldc<A>(cp1 + e * BS);
+                load_clover_half<A>(cp1, a.sig, c2);
                 clover_half_mac<A>(c2, diag, rr + 6, q + 6);
             }
             // even: q = A_ee r_e - H_eo A_oo^-1 H_oe r_e = S r_e
@@ -682,12 +681,23 @@ Status sweep(dd_ctx *ctx, SArgs a, int prec, const void *eta, void *psi, void *f
 // links in registers and the clover re-read from L2 per block application
 // beat both "everything in registers" (one workgroup per CU, register
 // pressure) and "everything from L2".
-typedef Residency<true, false, 2, true> ResF32;
-typedef Residency<true, false, 2, true> ResF16;
-typedef Residency<true, false, 1, true> ResF64;
+template <bool SIG> using ResF32 = Residency<true, false, 2, true, SIG>;
+template <bool SIG> using ResF16 = Residency<true, false, 2, true, SIG>;
+template <bool SIG> using ResF64 = Residency<true, false, 1, true, SIG>;
 // The even-odd sweep holds more per thread (two vectors, the factor or the
 // clover, the four links) and runs at one wavefront per SIMD.
 typedef Residency<true, false, 1, true> ResEO;
+
+template <bool SIG>
+Status plain_sweep(dd_ctx *ctx, const SArgs &a, int prec, bool half_fields, const void *eta, void *psi, void *faces,
+                   void *resid, bool quiet)
+{
+    if (prec == DD_F64) return sweep<double, double, ResF64<SIG>, false>(ctx, a, prec, eta, psi, faces, resid, quiet);
+    if (prec == DD_F32 && half_fields)
+        return sweep<float, float, ResF32<SIG>, false, __half>(ctx, a, prec, eta, psi, faces, resid, quiet);
+    if (prec == DD_F32) return sweep<float, float, ResF32<SIG>, false>(ctx, a, prec, eta, psi, faces, resid, quiet);
+    return sweep<__half, float, ResF16<SIG>, false>(ctx, a, prec, eta, psi, faces, resid, quiet);
+}
 
 } // namespace
 
@@ -730,6 +740,7 @@ Status run_sap(dd_ctx *ctx, const double *m0, int nrhs, const void *eta, void *p
     a.nrhs = nrhs;
     a.nmr = nmr;
     a.r12 = ctx->link_r12 ? 1 : 0;
+    a.sig = ctx->clover_sigma ? 1 : 0;
     for (int r = 0; r < nrhs && m0; ++r) a.m0[r] = m0[r];
     if (slots) {
         a.m0_dev = slots->m0_dev;
@@ -761,11 +772,8 @@ Status run_sap(dd_ctx *ctx, const double *m0, int nrhs, const void *eta, void *p
                 else if (prec == DD_F32) DD_TRY((sweep<float, float, ResEO, true>(ctx, a, prec, eta, psi, faces, resid, quiet)));
                 else DD_TRY((sweep<__half, float, ResEO, true>(ctx, a, prec, eta, psi, faces, resid, quiet)));
             } else {
-                if (prec == DD_F64) DD_TRY((sweep<double, double, ResF64, false>(ctx, a, prec, eta, psi, faces, resid, quiet)));
-                else if (prec == DD_F32 && half_fields)
-                    DD_TRY((sweep<float, float, ResF32, false, __half>(ctx, a, prec, eta, psi, faces, resid, quiet)));
-                else if (prec == DD_F32) DD_TRY((sweep<float, float, ResF32, false>(ctx, a, prec, eta, psi, faces, resid, quiet)));
-                else DD_TRY((sweep<__half, float, ResF16, false>(ctx, a, prec, eta, psi, faces, resid, quiet)));
+                DD_TRY(a.sig ? plain_sweep<true>(ctx, a, prec, half_fields, eta, psi, faces, resid, quiet)
+                             : plain_sweep<false>(ctx, a, prec, half_fields, eta, psi, faces, resid, quiet));
             }
         }
     return Status::ok();
