@@ -252,56 +252,81 @@ __global__ __launch_bounds__(TPB) void k_convert_from64(const double2 *__restric
     if (i < n) stc(out + i, ldc<double>(in + i));
 }
 
-// canonical spinors [rhs][site][12] (FP64) <-> blocked (precision S)
+// Layout transform of spinors, canonical [rhs][site][12] (FP64) <-> slots
+// slot0, slot0 + 1, .. of a width-wide blocked buffer of precision S; one
+// workgroup per (block, right-hand side).  Bound by HBM: each value crosses it
+// once on either side.  A block's canonical data are 64 runs of four sites
+// (768 B), its blocked data twelve runs of 256 sites, so the workgroup goes
+// through LDS: entry e of the block in canonical order is component e % 12 of
+// the run's site (e / 12) % 4, and thread t takes entries t, t + 256, ..., so
+// both sides move 16-byte (blocked: one complex number) contiguous accesses.
+// Without LDS each thread took its own site's 192 B, i.e. 16 B out of every
+// 192 per instruction: 24^3x48, twelve right-hand sides, FP32 in and out
+// 1076 us, now 778 us (5.9 TB/s; a plain streaming copy reaches 5.8).
+// LROW: the component stride in LDS, padded so that the twelve components of
+// four neighbouring sites (consecutive lanes) fall on different banks.
+constexpr int LROW = BS + 4;
+template <typename S> struct SpinorTile {
+    vec2_t<S> v[12][LROW];
+};
+
+// canonical entry e of block b (see above): its offset in the canonical
+// right-hand side; s and c receive the site and component
+__device__ __forceinline__ long tile_entry(const CanonGeom &g, int b, int e, int &s, int &c)
+{
+    c = e % 12;
+    s = e / 12;
+    return canon_site(g, b, s) * 12 + c;
+}
+
 template <typename S>
 __global__ __launch_bounds__(TPB) void k_spinor_pack(const double2 *__restrict__ in, vec2_t<S> *__restrict__ out,
-                                                     CanonGeom g, int nblocks, int nrhs, long V)
+                                                     CanonGeom g, int nrhs, long V, int width, int slot0,
+                                                     int *__restrict__ nonzero)
 {
-    int b = blockIdx.x / nrhs, r = blockIdx.x % nrhs, s = threadIdx.x;
-    if (b >= nblocks) return;
-    long x = canon_site(g, b, s);
-    const double2 *src = in + ((long)r * V + x) * 12;
-    vec2_t<S> *dst = out + ((long)b * nrhs + r) * 12 * BS + s;
-    for (int c = 0; c < 12; ++c) stc(dst + (long)c * BS, ldc<double>(src + c));
+    __shared__ SpinorTile<S> T;
+    const int b = blockIdx.x / nrhs, r = blockIdx.x % nrhs, t = threadIdx.x;
+    const double2 *src = in + (long)r * V * 12;
+    double2 v[12];
+    int s, c;
+#pragma unroll
+    for (int k = 0; k < 12; ++k) v[k] = ld_stream(src + tile_entry(g, b, k * TPB + t, s, c));
+    bool nz = false;
+#pragma unroll
+    for (int k = 0; k < 12; ++k) {
+        (void)tile_entry(g, b, k * TPB + t, s, c);
+        nz |= v[k].x != 0.0 || v[k].y != 0.0; // NaN counts as nonzero
+        stc(&T.v[c][s], mk<double>(v[k].x, v[k].y));
+    }
+    // set if any entry of the right-hand sides is nonzero
+    if (nonzero && __any(nz) && (t % 64) == 0) atomicOr(nonzero, 1);
+    __syncthreads();
+    vec2_t<S> *dst = out + ((long)b * width + slot0 + r) * 12 * BS + t;
+#pragma unroll
+    for (int k = 0; k < 12; ++k) dst[(long)k * BS] = T.v[k][t];
 }
 
 template <typename S>
 __global__ __launch_bounds__(TPB) void k_spinor_unpack(const vec2_t<S> *__restrict__ in, double2 *__restrict__ out,
-                                                       CanonGeom g, int nblocks, int nrhs, long V)
+                                                       CanonGeom g, int nrhs, long V, int width, int slot0)
 {
-    int b = blockIdx.x / nrhs, r = blockIdx.x % nrhs, s = threadIdx.x;
-    if (b >= nblocks) return;
-    long x = canon_site(g, b, s);
-    const vec2_t<S> *src = in + ((long)b * nrhs + r) * 12 * BS + s;
-    double2 *dst = out + ((long)r * V + x) * 12;
-    for (int c = 0; c < 12; ++c) stc(dst + c, ldc<double>(src + (long)c * BS));
-}
-
-// one canonical FP64 right-hand side <-> slot `slot` of a width-wide blocked buffer
-__global__ __launch_bounds__(TPB) void k_slot_pack(const double2 *__restrict__ in, double2 *__restrict__ out,
-                                                   CanonGeom g, int nblocks, int width, int slot,
-                                                   int *__restrict__ nonzero)
-{
-    int b = blockIdx.x, s = threadIdx.x;
-    if (b >= nblocks) return;
-    long x = canon_site(g, b, s);
-    double2 *dst = out + ((long)b * width + slot) * 12 * BS + s;
-    bool nz = false;
-    for (int c = 0; c < 12; ++c) {
-        const double2 v = in[x * 12 + c];
-        nz |= v.x != 0.0 || v.y != 0.0; // NaN counts as nonzero
-        dst[(long)c * BS] = v;
+    __shared__ SpinorTile<S> T;
+    const int b = blockIdx.x / nrhs, r = blockIdx.x % nrhs, t = threadIdx.x;
+    const vec2_t<S> *src = in + ((long)b * width + slot0 + r) * 12 * BS + t;
+    vec2_t<S> v[12];
+#pragma unroll
+    for (int k = 0; k < 12; ++k) v[k] = src[(long)k * BS];
+#pragma unroll
+    for (int k = 0; k < 12; ++k) T.v[k][t] = v[k];
+    __syncthreads();
+    double2 *dst = out + (long)r * V * 12;
+#pragma unroll
+    for (int k = 0; k < 12; ++k) {
+        int s, c;
+        const long o = tile_entry(g, b, k * TPB + t, s, c);
+        const cx<double> a = ldc<double>(&T.v[c][s]);
+        st_stream(dst + o, make_double2(a.re, a.im));
     }
-    if (nonzero && __any(nz) && (threadIdx.x % 64) == 0) atomicOr(nonzero, 1);
-}
-__global__ __launch_bounds__(TPB) void k_slot_unpack(const double2 *__restrict__ in, double2 *__restrict__ out,
-                                                     CanonGeom g, int nblocks, int width, int slot)
-{
-    int b = blockIdx.x, s = threadIdx.x;
-    if (b >= nblocks) return;
-    long x = canon_site(g, b, s);
-    const double2 *src = in + ((long)b * width + slot) * 12 * BS + s;
-    for (int c = 0; c < 12; ++c) out[x * 12 + c] = src[(long)c * BS];
 }
 
 __global__ __launch_bounds__(TPB) void k_nonfinite(const double *__restrict__ p, long n, int *flag)
@@ -401,19 +426,30 @@ Status set_clover_canon(dd_ctx *ctx, const double *C_dev)
     return check_clover_mirror(ctx);
 }
 
+namespace {
+
+template <typename S>
+void launch_pack(hipStream_t st, const GeomHost &g, const double *in, void *out, int nrhs, int width, int slot0, int *nonzero)
+{
+    k_spinor_pack<S><<<g.nblocks * nrhs, TPB, 0, st>>>(reinterpret_cast<const double2 *>(in), static_cast<vec2_t<S> *>(out),
+                                                       canon_geom(g), nrhs, g.V, width, slot0, nonzero);
+}
+template <typename S>
+void launch_unpack(hipStream_t st, const GeomHost &g, const void *in, double *out, int nrhs, int width, int slot0)
+{
+    k_spinor_unpack<S><<<g.nblocks * nrhs, TPB, 0, st>>>(static_cast<const vec2_t<S> *>(in), reinterpret_cast<double2 *>(out),
+                                                         canon_geom(g), nrhs, g.V, width, slot0);
+}
+
+} // namespace
+
 Status pack_spinor(dd_ctx *ctx, const double *canon, void *blocked, int prec, int nrhs)
 {
     const GeomHost &g = ctx->g;
     ProfScope ps(ctx->prof, ctx->stream, K_PACK, (double)g.V * nrhs * 24.0 * (8 + real_bytes(prec)), 0.0);
-    CanonGeom cg = canon_geom(g);
-    int grid = g.nblocks * nrhs;
-    const double2 *in = reinterpret_cast<const double2 *>(canon);
-    if (prec == DD_F64)
-        k_spinor_pack<double><<<grid, TPB, 0, ctx->stream>>>(in, static_cast<double2 *>(blocked), cg, g.nblocks, nrhs, g.V);
-    else if (prec == DD_F32)
-        k_spinor_pack<float><<<grid, TPB, 0, ctx->stream>>>(in, static_cast<float2 *>(blocked), cg, g.nblocks, nrhs, g.V);
-    else
-        k_spinor_pack<__half><<<grid, TPB, 0, ctx->stream>>>(in, static_cast<__half2 *>(blocked), cg, g.nblocks, nrhs, g.V);
+    if (prec == DD_F64) launch_pack<double>(ctx->stream, g, canon, blocked, nrhs, nrhs, 0, nullptr);
+    else if (prec == DD_F32) launch_pack<float>(ctx->stream, g, canon, blocked, nrhs, nrhs, 0, nullptr);
+    else launch_pack<__half>(ctx->stream, g, canon, blocked, nrhs, nrhs, 0, nullptr);
     DD_HIP_TRY(hipGetLastError());
     return Status::ok();
 }
@@ -422,35 +458,25 @@ Status unpack_spinor(dd_ctx *ctx, const void *blocked, double *canon, int prec, 
 {
     const GeomHost &g = ctx->g;
     ProfScope ps(ctx->prof, ctx->stream, K_PACK, (double)g.V * nrhs * 24.0 * (8 + real_bytes(prec)), 0.0);
-    CanonGeom cg = canon_geom(g);
-    int grid = g.nblocks * nrhs;
-    double2 *out = reinterpret_cast<double2 *>(canon);
-    if (prec == DD_F64)
-        k_spinor_unpack<double><<<grid, TPB, 0, ctx->stream>>>(static_cast<const double2 *>(blocked), out, cg, g.nblocks, nrhs, g.V);
-    else if (prec == DD_F32)
-        k_spinor_unpack<float><<<grid, TPB, 0, ctx->stream>>>(static_cast<const float2 *>(blocked), out, cg, g.nblocks, nrhs, g.V);
-    else
-        k_spinor_unpack<__half><<<grid, TPB, 0, ctx->stream>>>(static_cast<const __half2 *>(blocked), out, cg, g.nblocks, nrhs, g.V);
+    if (prec == DD_F64) launch_unpack<double>(ctx->stream, g, blocked, canon, nrhs, nrhs, 0);
+    else if (prec == DD_F32) launch_unpack<float>(ctx->stream, g, blocked, canon, nrhs, nrhs, 0);
+    else launch_unpack<__half>(ctx->stream, g, blocked, canon, nrhs, nrhs, 0);
     DD_HIP_TRY(hipGetLastError());
     return Status::ok();
 }
 
 Status pack_slot(dd_ctx *ctx, hipStream_t st, const double *canon, void *blocked, int width, int slot, int *nonzero)
 {
-    const GeomHost &g = ctx->g;
-    ProfScope ps(ctx->prof, st, K_PACK, (double)g.V * 24.0 * 16, 0.0);
-    k_slot_pack<<<g.nblocks, TPB, 0, st>>>(reinterpret_cast<const double2 *>(canon), static_cast<double2 *>(blocked),
-                                           canon_geom(g), g.nblocks, width, slot, nonzero);
+    ProfScope ps(ctx->prof, st, K_PACK, (double)ctx->g.V * 24.0 * 16, 0.0);
+    launch_pack<double>(st, ctx->g, canon, blocked, 1, width, slot, nonzero);
     DD_HIP_TRY(hipGetLastError());
     return Status::ok();
 }
 
 Status unpack_slot(dd_ctx *ctx, hipStream_t st, const void *blocked, double *canon, int width, int slot)
 {
-    const GeomHost &g = ctx->g;
-    ProfScope ps(ctx->prof, st, K_PACK, (double)g.V * 24.0 * 16, 0.0);
-    k_slot_unpack<<<g.nblocks, TPB, 0, st>>>(static_cast<const double2 *>(blocked), reinterpret_cast<double2 *>(canon),
-                                             canon_geom(g), g.nblocks, width, slot);
+    ProfScope ps(ctx->prof, st, K_PACK, (double)ctx->g.V * 24.0 * 16, 0.0);
+    launch_unpack<double>(st, ctx->g, blocked, canon, 1, width, slot);
     DD_HIP_TRY(hipGetLastError());
     return Status::ok();
 }
