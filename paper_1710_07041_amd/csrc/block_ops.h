@@ -137,7 +137,7 @@ template <typename A> __device__ __forceinline__ cx<A> lane_fetch(const cx<A> &v
 // rows and keeps ds_bpermute.
 template <int CTRL> __device__ __forceinline__ int dpp_mov(int v)
 {
-    return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xf, 0xf, false);
+    return __builtin_amdgcn_mov_dpp(v, CTRL, 0xf, 0xf, false);
 }
 template <int MU, int DIR, typename A> __device__ __forceinline__ cx<A> lane_hop(const cx<A> &v, int sn)
 {

@@ -6,11 +6,12 @@
 //
 // One launch sweeps every block of one colour.  One 256-thread workgroup owns
 // one 4^4 block, one thread one site, and keeps everything the MR loop needs
-// on chip:
+// on chip (k_sap_sweep, sap_sweep.h):
 //   * the site's four forward links (pre-multiplied by the hop factor -1/2)
-//     and chiral half 0 of its clover term live in registers for the whole
-//     sweep and every right-hand side; clover half 1 is re-read at each block
-//     application and stays in L2; the MR accumulator lives in LDS;
+//     and its clover term live in registers for the whole sweep and every
+//     right-hand side (of a clover term that does not mirror itself, and in
+//     FP64, half 1 is re-read at each block application and stays in L2); the
+//     MR accumulator lives in LDS;
 //   * D_BB is applied direction by direction: each thread provides the
 //     spin-projected half spinor of its site for the +mu hop of site x-mu and
 //     U_mu(x)^+ times the projected half spinor for the -mu hop of site x+mu,
@@ -21,19 +22,15 @@
 //     (deterministic).
 // eta and psi go through the caches (they are re-read by the next sweep and
 // by the operator that follows the smoother, and fit in the 256 MB
-// last-level cache in FP32); links and clover half 0, read once per sweep,
-// stream.
-// With FP32/FP16 storage the block residual rho_B = eta_B - (D psi)_B is
-// carried from visit to visit rather than recomputed (FP64 recomputes it: the
-// carried form does not fit its register budget as well).  Luescher's
-// formulation of the procedure: after its
+// last-level cache in FP32); links and clover, read once per sweep, stream.
+// The block residual rho_B = eta_B - (D psi)_B is carried from visit to visit
+// rather than recomputed.  Luescher's formulation of the procedure: after its
 // MR steps a block stores its MR residual R_B, and the next visit forms
 // rho_B = R_B - D_{B,dB} delta_dB, where delta_dB is the update that the
 // neighbouring blocks of the other colour made in between (on the first
 // visit R_B = eta_B).  The hops of delta arrive through face buffers that the
 // other colour published at the end of its solves (block_ops.h: six dense
-// components per boundary hop).  psi_B before the visit waits in the half of
-// the LDS exchange buffer that the in-wavefront directions leave free.
+// components per boundary hop).
 // Blocks of one colour share no site and read only the other colour's data,
 // so a sweep needs no synchronisation between workgroups.
 //
@@ -43,217 +40,11 @@
 #include "block_ops.h"
 #include "dd_device.h"
 #include "dd_internal.h"
+#include "sap_sweep.h"
 
 namespace dd {
 
 namespace {
-
-struct SArgs {
-    Geom g;
-    const int *blocks; // block ids of the swept colour
-    int nblk;
-    int nrhs;
-    int rpg; // right-hand sides per workgroup (rhs_per_group)
-    int nmr;
-    int mode; // 0: psi = 0 everywhere; 1: psi_B = 0 on this colour; 2: general
-    double m0[MAXRHS];
-    const double *m0_dev; // per-rhs masses in device memory (overrides m0 when set)
-    const long *eta_off;  // per-rhs element offsets of eta and psi (nullable)
-    const long *psi_off;
-    const int *active;    // right-hand sides with active[r] == 0 are skipped (nullable)
-    int publish;          // write the face buffers for the next sweep
-    int r12;              // links stored as SU(3): read two rows, rebuild the third
-    int sig;              // the clover term is sigma . F: mirrored slots are not read
-    int write_r;          // plain sweep: store the block residual for the next visit
-};
-
-// The block (grid x) and the right-hand sides [r0, r1) (grid y) of this
-// workgroup.  False when none of them is active (uniform: nothing to do).
-__device__ __forceinline__ bool sweep_part(const SArgs &a, int &b, int &r0, int &r1)
-{
-    b = a.blocks[xcd_remap(blockIdx.x, gridDim.x)];
-    r0 = blockIdx.y * a.rpg;
-    r1 = min(r0 + a.rpg, a.nrhs);
-    if (!a.active) return true;
-    bool any = false;
-    for (int r = r0; r < r1; ++r) any |= a.active[r] != 0;
-    return any;
-}
-
-// The MR coefficient of one right-hand side: the dot products <q, r> and
-// <q, q> over the block (DPP sums within each wavefront, then a fixed-order
-// combine of the four wavefronts through LDS), alpha = <q, r>/<q, q>; returns
-// false when <q, q> vanishes (uniform over the workgroup).
-template <typename A>
-__device__ __forceinline__ bool mr_alpha(Lds<A> &L, int lane, int wave, const cx<A> q[12], const cx<A> rr[12],
-                                         cx<A> &alpha)
-{
-    A qr_re = 0, qr_im = 0, qq = 0;
-#pragma unroll
-    for (int c = 0; c < 12; ++c) {
-        qr_re = fma(q[c].re, rr[c].re, qr_re);
-        qr_re = fma(q[c].im, rr[c].im, qr_re);
-        qr_im = fma(q[c].re, rr[c].im, qr_im);
-        qr_im = fma(-q[c].im, rr[c].re, qr_im);
-        qq = fma(q[c].re, q[c].re, qq);
-        qq = fma(q[c].im, q[c].im, qq);
-    }
-    qr_re = wave_sum(qr_re);
-    qr_im = wave_sum(qr_im);
-    qq = wave_sum(qq);
-    if (lane == 63) { // where wave_sum leaves the total
-        L.red[wave][0] = qr_re;
-        L.red[wave][1] = qr_im;
-        L.red[wave][2] = qq;
-    }
-    __syncthreads();
-    qr_re = ((L.red[0][0] + L.red[1][0]) + L.red[2][0]) + L.red[3][0];
-    qr_im = ((L.red[0][1] + L.red[1][1]) + L.red[2][1]) + L.red[3][1];
-    qq = ((L.red[0][2] + L.red[1][2]) + L.red[2][2]) + L.red[3][2];
-    if (qq == (A)0) return false;
-    alpha = mk<A>(qr_re / qq, qr_im / qq);
-    return true;
-}
-
-// With the half clover in registers, the MR accumulator delta lives in LDS
-// (each thread touches only its own site's entries, so no barrier guards it).
-template <typename A, typename RES> struct DelStore {
-    cx<A> d[RES::clover_half ? 12 : 1][RES::clover_half ? BS : 1];
-};
-
-// Whether the plain sweep of storage type S carries the block residual.
-template <typename S> constexpr bool SAP_CARRY = !std::is_same<S, double>::value;
-
-// SF is the storage type of the links and the clover term (S, or FP16 fields
-// under FP32 spinors).
-template <typename S, typename A, typename RES, typename SF = S>
-__global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(RES::waves))) void k_sap_sweep(
-    const vec2_t<S> *__restrict__ eta0, vec2_t<S> *__restrict__ psi0, const vec2_t<SF> *__restrict__ links,
-    const vec2_t<SF> *__restrict__ clov, vec2_t<S> *__restrict__ faces, vec2_t<S> *__restrict__ resid, SArgs a)
-{
-    constexpr bool REGLINKS = RES::links;
-    static_assert(REGLINKS, "the face buffers assume register-resident links");
-    static_assert(RES::clover_half, "the MR accumulator lives in LDS");
-    // FP32/FP16 storage carries the block residual between visits; FP64
-    // recomputes it (the carried form spills in FP64's register budget)
-    constexpr bool CARRY = SAP_CARRY<S>;
-    __shared__ Lds<A> L;
-    __shared__ DelStore<A, RES> D;
-    int b, rhs0, rhs1;
-    if (!sweep_part(a, b, rhs0, rhs1)) return;
-    const int s = threadIdx.x;
-    const int lane = s & 63, wave = s >> 6;
-    int bc[4];
-    block_coords(a.g, b, bc);
-
-    // register-resident links carry the hop factor -1/2
-    cx<A> U[4][9];
-    load_links4<A, true>(links + (long)b * 4 * 9 * BS + s, a.r12, (A)(-0.5), U);
-    cx<A> cl[RES::ncl];
-    if (RES::clover || RES::clover_half) {
-        const vec2_t<SF> *cp = clov + (long)b * 36 * BS + s;
-#pragma unroll
-        for (int e = 0; e < RES::ncl; ++e)
-            if (clover_reads(RES::sigma, e)) cl[e] = ldc_stream<A>(cp + e * BS);
-    }
-
-    for (int r = rhs0; r < rhs1; ++r) {
-        // with nmr = 0 the previous right-hand side's last t-hop reads are
-        // not yet fenced by an MR barrier
-        __syncthreads();
-        if (a.active && !a.active[r]) continue; // uniform over the workgroup
-        const A diag = (A)(4.0 + (a.m0_dev ? a.m0_dev[r] : a.m0[r]));
-        const vec2_t<S> *__restrict__ eta = eta0 + (a.eta_off ? a.eta_off[r] : 0);
-        vec2_t<S> *__restrict__ psi = psi0 + (a.psi_off ? a.psi_off[r] : 0);
-        const long sp = ((long)b * a.nrhs + r) * 12 * BS + s;
-        const long rp = ((long)b * a.nrhs + r) * 12 * BS + s; // the carried residual (no slot offsets)
-        cx<A> rr[12], q[12];
-        vec2_t<S> er[12];
-        if constexpr (CARRY) {
-            // psi_B before this visit, in the half of the exchange buffer that
-            // the in-wavefront directions leave unused; delta starts at 0
-            if (a.mode == 2) {
-#pragma unroll
-                for (int c = 0; c < 12; ++c) {
-                    const cx<A> v = ldc<A>(psi + sp + c * BS);
-                    if (c < 6) L.hf[0][c][s] = v;
-                    else L.hb[0][c - 6][s] = v;
-                }
-            }
-#pragma unroll
-            for (int c = 0; c < 12; ++c) D.d[c][s] = mk<A>(0, 0);
-            // rho = R - (hops of the other colour's last update), R being this
-            // block's residual after its previous visit (eta on the first)
-            const vec2_t<S> *__restrict__ src = a.mode == 2 ? resid + rp : eta + sp;
-#pragma unroll
-            for (int c = 0; c < 12; ++c) er[c] = src[c * BS];
-#pragma unroll
-            for (int c = 0; c < 12; ++c) q[c] = mk<A>(0, 0);
-        } else {
-            // rho = eta - (D psi)_B, recomputed: the block part here, the hops
-            // of the other colour's psi below; delta starts at psi_B
-            cx<A> d0[12];
-#pragma unroll
-            for (int c = 0; c < 12; ++c) d0[c] = a.mode == 2 ? ldc<A>(psi + sp + c * BS) : mk<A>(0, 0);
-            if (a.mode == 2) {
-                block_apply<SF, A, RES>(L, a.g, b, bc, s, U, cl, links, clov, diag, d0, q);
-            } else {
-#pragma unroll
-                for (int c = 0; c < 12; ++c) q[c] = mk<A>(0, 0);
-            }
-#pragma unroll
-            for (int c = 0; c < 12; ++c) D.d[c][s] = d0[c];
-            // eta in flight during the face trips (held in the storage type)
-#pragma unroll
-            for (int c = 0; c < 12; ++c) er[c] = eta[sp + c * BS];
-        }
-        if (a.mode != 0) face_consume<S, A>(a.g, b, bc, s, r, a.nrhs, faces, U, q);
-#pragma unroll
-        for (int c = 0; c < 12; ++c) rr[c] = ldc<A>(&er[c]) - q[c];
-        // the recomputed residual's t-hop reads end before the first MR
-        // application rewrites that LDS buffer
-        if (!CARRY && a.mode == 2) __syncthreads();
-        // MR on D_BB: delta += alpha r, r -= alpha q
-        for (int it = 0; it < a.nmr; ++it) {
-            block_apply<SF, A, RES>(L, a.g, b, bc, s, U, cl, links, clov, diag, rr, q);
-            cx<A> alpha;
-            if (!mr_alpha(L, lane, wave, q, rr, alpha)) break;
-#pragma unroll
-            for (int c = 0; c < 12; ++c) {
-                cx<A> d = D.d[c][s];
-                cmac(d, alpha, rr[c]);
-                D.d[c][s] = d;
-                rr[c] = rr[c] - alpha * q[c];
-            }
-        }
-        cx<A> fin[12];
-        if constexpr (CARRY) {
-            // psi_B += delta; the residual carried to the next visit; the
-            // faces of delta for the other colour
-#pragma unroll
-            for (int c = 0; c < 12; ++c) {
-                fin[c] = D.d[c][s];
-                cx<A> v = fin[c];
-                if (a.mode == 2) v = v + (c < 6 ? L.hf[0][c][s] : L.hb[0][c - 6][s]);
-                stc(psi + sp + c * BS, v);
-            }
-            if (a.write_r) {
-#pragma unroll
-                for (int c = 0; c < 12; ++c) stc(resid + rp + c * BS, rr[c]);
-            }
-        } else {
-            // psi_B = delta; the faces of psi as stored
-#pragma unroll
-            for (int c = 0; c < 12; ++c) {
-                vec2_t<S> v;
-                stc(&v, D.d[c][s]);
-                psi[sp + c * BS] = v;
-                fin[c] = ldc<A>(&v);
-            }
-        }
-        if (a.publish) face_publish<S, A>(faces, b, a.nrhs, r, s, fin, U);
-    }
-}
 
 // ---------------------------------------------------------------------------
 // Even-odd preconditioned block solve (site parity p = (x+y+z+t) mod 2).  On
@@ -640,63 +431,58 @@ int rhs_per_group(int nblk, int nrhs, int slots)
     return best;
 }
 
-template <typename S, typename A, typename RES, bool EO, typename SF = S>
+// Algorithmic traffic of one colour sweep: links + clover once (72 reals per
+// site each, also when compressed: the method's volume), eta or the carried
+// residual, psi (read only when nonzero), psi written and, in the plain form,
+// the residual carried to the next visit.
+double sweep_bytes(const SArgs &a, size_t field_bytes, size_t spinor_bytes, bool carry)
+{
+    return 256.0 * a.nblk *
+           (144.0 * field_bytes + a.nrhs * (double)spinor_bytes *
+                                      (48.0 + (a.mode == 2 ? 24.0 : 0.0) + (carry && a.write_r ? 24.0 : 0.0)));
+}
+
+// WAVES wavefronts per SIMD: that many four-wavefront workgroups per CU.
+template <typename S, typename A, typename SF, int WAVES>
 Status sweep(dd_ctx *ctx, SArgs a, int prec, const void *eta, void *psi, void *faces, void *resid, bool quiet)
 {
-    // algorithmic traffic of one colour sweep: links + clover once, eta (or
-    // the carried residual), psi (read only when nonzero), psi written and,
-    // in the plain form, the residual carried to the next visit
-    const double sites = 256.0 * a.nblk, sb = (double)sizeof(S), n = a.nrhs;
-    constexpr bool CARRY = !EO && SAP_CARRY<S>;
     const int fprec = sizeof(SF) == 8 ? DD_F64 : (sizeof(SF) == 4 ? DD_F32 : DD_F16);
-    // (links count 72 reals per site also when compressed: the method's volume)
-    const double by = sites * (144.0 * (double)sizeof(SF) +
-                               n * sb * (24.0 + 24.0 + (a.mode == 2 ? 24.0 : 0.0) + (CARRY && a.write_r ? 24.0 : 0.0)));
-    // recomputing the block residual costs one operator application when
-    // psi_B != 0; carrying it costs none.  The even-odd form adds one
-    // in-block hop application (the right-hand side and the odd
-    // reconstruction) per block solve.
-    const double fl = sites * n * (a.nmr * 2184.0 + (!CARRY && a.mode == 2 ? 1848.0 : 0.0) + (EO ? 1848.0 : 0.0));
-    const int cls = EO ? (prec == DD_F64 ? K_SAP_EO_F64 : prec == DD_F32 ? K_SAP_EO_F32 : K_SAP_EO_F16)
-                       : (prec == DD_F64 ? K_SAP_F64 : prec == DD_F32 ? K_SAP_F32 : K_SAP_F16);
-    ProfScope ps(ctx->prof, ctx->stream, cls, by, fl, !quiet);
-    // RES::waves wavefronts per SIMD: that many four-wavefront workgroups per CU
-    a.rpg = rhs_per_group(a.nblk, a.nrhs, ctx->ncu * RES::waves);
-    const dim3 grid(a.nblk, (a.nrhs + a.rpg - 1) / a.rpg);
-    if constexpr (EO)
-        k_sap_sweep_eo<S, A, RES><<<grid, BS, 0, ctx->stream>>>(
-            static_cast<const vec2_t<S> *>(eta), static_cast<vec2_t<S> *>(psi),
-            static_cast<const vec2_t<S> *>(ctx->links[prec].p), static_cast<const vec2_t<S> *>(ctx->clover[prec].p),
-            static_cast<vec2_t<S> *>(faces), a);
-    else
-        k_sap_sweep<S, A, RES, SF><<<grid, BS, 0, ctx->stream>>>(
-            static_cast<const vec2_t<S> *>(eta), static_cast<vec2_t<S> *>(psi),
-            static_cast<const vec2_t<SF> *>(ctx->links[fprec].p), static_cast<const vec2_t<SF> *>(ctx->clover[fprec].p),
-            static_cast<vec2_t<S> *>(faces), static_cast<vec2_t<S> *>(resid), a);
+    const int cls = prec == DD_F64 ? K_SAP_F64 : prec == DD_F32 ? K_SAP_F32 : K_SAP_F16;
+    ProfScope ps(ctx->prof, ctx->stream, cls, sweep_bytes(a, sizeof(SF), sizeof(S), true),
+                 256.0 * a.nblk * a.nrhs * a.nmr * 2184.0, !quiet);
+    a.rpg = rhs_per_group(a.nblk, a.nrhs, ctx->ncu * WAVES);
+    // a direction that one block spans wraps inside it
+    const bool wrap = a.g.nb[0] == 1 || a.g.nb[1] == 1 || a.g.nb[2] == 1 || a.g.nb[3] == 1;
+    auto kernel = wrap ? (a.sig ? k_sap_sweep<S, A, SF, WAVES, true, true> : k_sap_sweep<S, A, SF, WAVES, true, false>)
+                       : (a.sig ? k_sap_sweep<S, A, SF, WAVES, false, true> : k_sap_sweep<S, A, SF, WAVES, false, false>);
+    kernel<<<dim3(a.nblk, (a.nrhs + a.rpg - 1) / a.rpg), BS, 0, ctx->stream>>>(
+        static_cast<const vec2_t<S> *>(eta), static_cast<vec2_t<S> *>(psi),
+        static_cast<const vec2_t<SF> *>(ctx->links[fprec].p), static_cast<const vec2_t<SF> *>(ctx->clover[fprec].p),
+        static_cast<vec2_t<S> *>(faces), static_cast<vec2_t<S> *>(resid), a);
     DD_HIP_TRY(hipGetLastError());
     return Status::ok();
 }
 
-// Chosen by measurement on MI355X (32^3x64 colour sweep, single RHS):
-// links in registers and the clover re-read from L2 per block application
-// beat both "everything in registers" (one workgroup per CU, register
-// pressure) and "everything from L2".
-template <bool SIG> using ResF32 = Residency<true, false, 2, true, SIG>;
-template <bool SIG> using ResF16 = Residency<true, false, 2, true, SIG>;
-template <bool SIG> using ResF64 = Residency<true, false, 1, true, SIG>;
 // The even-odd sweep holds more per thread (two vectors, the factor or the
 // clover, the four links) and runs at one wavefront per SIMD.
 typedef Residency<true, false, 1, true> ResEO;
 
-template <bool SIG>
-Status plain_sweep(dd_ctx *ctx, const SArgs &a, int prec, bool half_fields, const void *eta, void *psi, void *faces,
-                   void *resid, bool quiet)
+template <typename S, typename A>
+Status sweep_eo(dd_ctx *ctx, SArgs a, int prec, const void *eta, void *psi, void *faces, bool quiet)
 {
-    if (prec == DD_F64) return sweep<double, double, ResF64<SIG>, false>(ctx, a, prec, eta, psi, faces, resid, quiet);
-    if (prec == DD_F32 && half_fields)
-        return sweep<float, float, ResF32<SIG>, false, __half>(ctx, a, prec, eta, psi, faces, resid, quiet);
-    if (prec == DD_F32) return sweep<float, float, ResF32<SIG>, false>(ctx, a, prec, eta, psi, faces, resid, quiet);
-    return sweep<__half, float, ResF16<SIG>, false>(ctx, a, prec, eta, psi, faces, resid, quiet);
+    // recomputing the block residual costs one operator application when
+    // psi_B != 0; the right-hand side and the odd reconstruction one in-block
+    // hop application per block solve
+    const double fl = 256.0 * a.nblk * a.nrhs * (a.nmr * 2184.0 + (a.mode == 2 ? 1848.0 : 0.0) + 1848.0);
+    const int cls = prec == DD_F64 ? K_SAP_EO_F64 : prec == DD_F32 ? K_SAP_EO_F32 : K_SAP_EO_F16;
+    ProfScope ps(ctx->prof, ctx->stream, cls, sweep_bytes(a, sizeof(S), sizeof(S), false), fl, !quiet);
+    a.rpg = rhs_per_group(a.nblk, a.nrhs, ctx->ncu * ResEO::waves);
+    k_sap_sweep_eo<S, A, ResEO><<<dim3(a.nblk, (a.nrhs + a.rpg - 1) / a.rpg), BS, 0, ctx->stream>>>(
+        static_cast<const vec2_t<S> *>(eta), static_cast<vec2_t<S> *>(psi),
+        static_cast<const vec2_t<S> *>(ctx->links[prec].p), static_cast<const vec2_t<S> *>(ctx->clover[prec].p),
+        static_cast<vec2_t<S> *>(faces), a);
+    DD_HIP_TRY(hipGetLastError());
+    return Status::ok();
 }
 
 } // namespace
@@ -768,12 +554,14 @@ Status run_sap(dd_ctx *ctx, const double *m0, int nrhs, const void *eta, void *p
             a.publish = !(cy == ncy - 1 && col == 1);
             a.write_r = cy < ncy - 1;
             if (eo) {
-                if (prec == DD_F64) DD_TRY((sweep<double, double, ResEO, true>(ctx, a, prec, eta, psi, faces, resid, quiet)));
-                else if (prec == DD_F32) DD_TRY((sweep<float, float, ResEO, true>(ctx, a, prec, eta, psi, faces, resid, quiet)));
-                else DD_TRY((sweep<__half, float, ResEO, true>(ctx, a, prec, eta, psi, faces, resid, quiet)));
+                DD_TRY((prec == DD_F64   ? sweep_eo<double, double>(ctx, a, prec, eta, psi, faces, quiet)
+                        : prec == DD_F32 ? sweep_eo<float, float>(ctx, a, prec, eta, psi, faces, quiet)
+                                         : sweep_eo<__half, float>(ctx, a, prec, eta, psi, faces, quiet)));
             } else {
-                DD_TRY(a.sig ? plain_sweep<true>(ctx, a, prec, half_fields, eta, psi, faces, resid, quiet)
-                             : plain_sweep<false>(ctx, a, prec, half_fields, eta, psi, faces, resid, quiet));
+                DD_TRY((prec == DD_F64   ? sweep<double, double, double, 1>(ctx, a, prec, eta, psi, faces, resid, quiet)
+                        : prec == DD_F16 ? sweep<__half, float, __half, 2>(ctx, a, prec, eta, psi, faces, resid, quiet)
+                        : half_fields    ? sweep<float, float, __half, 2>(ctx, a, prec, eta, psi, faces, resid, quiet)
+                                         : sweep<float, float, float, 2>(ctx, a, prec, eta, psi, faces, resid, quiet)));
             }
         }
     return Status::ok();

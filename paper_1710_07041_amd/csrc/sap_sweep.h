@@ -1,0 +1,493 @@
+// The plain Schwarz colour sweep (included by sap.hip): one 256-thread
+// workgroup per block, one thread per site.
+//
+// What bounds it: two workgroups fit a CU (registers, LDS), i.e. two wavefronts
+// per SIMD, and a workgroup's visit is a chain of its loads (8 us of a visit of
+// 35 us at 32^3x64 in FP32), the face trips (5 us), the MR steps (4 x 3.9 us)
+// and its stores.  One wavefront issues a VALU instruction per 5.3 cycles, two
+// per SIMD one per 2.7, four one per 1.8 (a loop of independent FMAs), so an MR
+// step takes what its 1400 instructions take to issue, whether or not another
+// workgroup shares the CU; HBM idles meanwhile (FP32: 3.7 of 5.8 TB/s).
+// Hence few instructions and branches in the step: a lattice without a
+// direction that one block spans takes a kernel without the wrap tests (WRAP),
+// y hops shift zeros in instead of testing lanes, lane moves carry no old
+// value, and with a sigma . F clover term (SIG) both its halves stay in
+// registers (FP32 arithmetic), so no memory load sits inside the step.
+// Measured together, twelve FP32 cycles at 32^3x64: 7.07 -> 6.70 ms a call,
+// ten FP16 ones at 48^3x96: 23.4 -> 22.5 ms, twelve FP64 ones at 24^3x48, which
+// now carry the residual instead of recomputing it: 6.60 -> 6.05 ms.
+// More wavefronts did not pay: three workgroups per CU (168 registers, link
+// rows rebuilt at each use) spill, 15.4 ms in FP32; two threads per site (512
+// threads a block at 128 registers) double the LDS traffic and the barriers,
+// 10.9 ms.
+#pragma once
+
+#include "block_ops.h"
+
+namespace dd {
+
+// FP64 data read psi again at the end of the visit and take the faces in an
+// unrolled loop; FP32 arithmetic, at half the registers a thread, and the FP64
+// kernels with wrap tests or a full clover term spill with either: they keep
+// psi in LDS meanwhile (PL) and one face trip in flight.  24^3x48, FP64: 6.05
+// against 6.75 ms; 32^3x64, FP32: 8.98 against 6.70 ms.
+template <typename S, bool WRAP, bool SIG> constexpr bool PSI_LDS = sizeof(S) < 8 || WRAP || !SIG;
+
+template <typename S, typename A, bool PL> struct SweepLds {
+    cx<A> tf[6][BS];   // projected half spinors for the +t hops
+    cx<A> tb[6][BS];   // U^+ times projected half spinors for the -t hops
+    cx<A> del[12][BS]; // MR accumulator (each thread its own site's entries)
+    vec2_t<S> psi[PL ? 12 : 1][BS]; // psi before the visit
+    A red[4][4];
+};
+
+// ---- one spin (SP = 0, 1) of the projections, SG = -1: (1 - g), +1: (1 + g)
+// h = u_SP + SG (A l)_SP with A_k = -i sigma_k, A_t = 1
+template <int MU, int SG, int SP, typename A>
+__device__ __forceinline__ void proj_spin(const cx<A> u[6], const cx<A> l[6], cx<A> h[3])
+{
+    constexpr int SL = MU < 2 ? 1 - SP : SP; // the lower spin that A mixes in
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        const cx<A> a = u[3 * SP + c], x = l[3 * SL + c];
+        // (A l): x: -i l1, -i l0; y: -l1, l0; z: -i l0, i l1; t: l0, l1
+        if (MU == 0) h[c] = SG > 0 ? a + tmi(x) : a + ti(x);
+        if (MU == 1) h[c] = (SG > 0) == (SP == 0) ? a - x : a + x;
+        if (MU == 2) h[c] = (SG > 0) == (SP == 0) ? a + tmi(x) : a + ti(x);
+        if (MU == 3) h[c] = SG > 0 ? a + x : a - x;
+    }
+}
+// (u, l) += k (t, SG A^+ t) for the spin SP of t (k = 1 when KONE)
+template <int MU, int SG, int SP, bool KONE, typename A>
+__device__ __forceinline__ void recon_spin(cx<A> u[6], cx<A> l[6], const cx<A> t[3], A k)
+{
+    constexpr int SL = MU < 2 ? 1 - SP : SP;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        const cx<A> x = KONE ? t[c] : k * t[c];
+        u[3 * SP + c] = u[3 * SP + c] + x;
+        cx<A> &y = l[3 * SL + c];
+        // A^+ t: x: i t1, i t0 on l0, l1; y: t1, -t0; z: i t0, -i t1; t: t0, t1
+        if (MU == 0) y = y + (SG > 0 ? ti(x) : tmi(x));
+        if (MU == 1) y = (SG > 0) == (SP == 1) ? y + x : y - x;
+        if (MU == 2) y = y + ((SG > 0) == (SP == 0) ? ti(x) : tmi(x));
+        if (MU == 3) y = SG > 0 ? y + x : y - x;
+    }
+}
+// t = W h and t = W^+ h for one spin
+template <typename A> __device__ __forceinline__ void su3_spin(const cx<A> W[9], const cx<A> h[3], cx<A> t[3])
+{
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        cx<A> acc = W[a * 3] * h[0];
+        cmac(acc, W[a * 3 + 1], h[1]);
+        cmac(acc, W[a * 3 + 2], h[2]);
+        t[a] = acc;
+    }
+}
+template <typename A> __device__ __forceinline__ void su3_spin_adj(const cx<A> W[9], const cx<A> h[3], cx<A> t[3])
+{
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        cx<A> acc = conjx(W[a]) * h[0];
+        cmacc(acc, W[3 + a], h[1]);
+        cmacc(acc, W[6 + a], h[2]);
+        t[a] = acc;
+    }
+}
+// row_shl:4 (0x104: lane i reads lane i + 4 of its row) and row_shr:4 (0x114),
+// zero from outside the row
+template <int CTRL> __device__ __forceinline__ int shift_mov(int v)
+{
+    return __builtin_amdgcn_mov_dpp(v, CTRL, 0xf, 0xf, true);
+}
+template <int CTRL, typename A> __device__ __forceinline__ cx<A> row_shift(const cx<A> &v)
+{
+    if constexpr (sizeof(A) == 4) {
+        return mk<A>(__int_as_float(shift_mov<CTRL>(__float_as_int(v.re))), __int_as_float(shift_mov<CTRL>(__float_as_int(v.im))));
+    } else {
+        const long long r = __double_as_longlong(v.re), i = __double_as_longlong(v.im);
+        const int r0 = shift_mov<CTRL>((int)r), r1 = shift_mov<CTRL>((int)(r >> 32));
+        const int i0 = shift_mov<CTRL>((int)i), i1 = shift_mov<CTRL>((int)(i >> 32));
+        return mk<A>(__longlong_as_double(((long long)r1 << 32) | (unsigned)r0),
+                     __longlong_as_double(((long long)i1 << 32) | (unsigned)i0));
+    }
+}
+
+// ---- in-block hops of direction MU across the lanes of a wavefront
+template <int MU, int SP, bool WRAP, typename A>
+__device__ __forceinline__ void blk_hop_spin(const cx<A> W[9], const cx<A> u[6], const cx<A> l[6], cx<A> qu[6],
+                                              cx<A> ql[6], bool inf, bool inb, int snf, int snb, bool wraps, A kf, A kb)
+{
+    cx<A> h[3], t[3];
+    if constexpr (MU == 1 && !WRAP) {
+        // y: a shift within the row of 16 lanes fills with zero where the
+        // neighbour leaves the block, so every lane adds
+        proj_spin<MU, -1, SP>(u, l, h);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) t[c] = row_shift<0x104, A>(h[c]);
+        su3_spin(W, t, h);
+        recon_spin<MU, -1, SP, true>(qu, ql, h, kf);
+        proj_spin<MU, +1, SP>(u, l, h);
+        su3_spin_adj(W, h, t);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) h[c] = row_shift<0x114, A>(t[c]);
+        recon_spin<MU, +1, SP, true>(qu, ql, h, kb);
+        return;
+    }
+    proj_spin<MU, -1, SP>(u, l, h);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) t[c] = lane_hop<MU, +1, A>(h[c], snf);
+    if (inf) {
+        su3_spin(W, t, h);
+        if (WRAP && wraps) recon_spin<MU, -1, SP, false>(qu, ql, h, kf);
+        else recon_spin<MU, -1, SP, true>(qu, ql, h, kf);
+    }
+    proj_spin<MU, +1, SP>(u, l, h);
+    su3_spin_adj(W, h, t);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) h[c] = lane_hop<MU, -1, A>(t[c], snb);
+    if (inb) {
+        if (WRAP && wraps) recon_spin<MU, +1, SP, false>(qu, ql, h, kb);
+        else recon_spin<MU, +1, SP, true>(qu, ql, h, kb);
+    }
+}
+template <int MU, bool WRAP, typename A>
+__device__ __forceinline__ void blk_hop(const Geom &g, int b, const int bc[4], int s, const cx<A> W[9],
+                                         const cx<A> u[6], const cx<A> l[6], cx<A> qu[6], cx<A> ql[6])
+{
+    const bool wraps = g.nb[MU] == 1; // uniform
+    int bn, snf, snb, gf, gb;
+    bool inf, inb;
+    neighbour<MU, +1>(g, b, bc, s, bn, snf, gf, inf);
+    neighbour<MU, -1>(g, b, bc, s, bn, snb, gb, inb);
+    if (!WRAP) {
+        inf = ((s >> (2 * MU)) & 3) < BEXT - 1;
+        inb = ((s >> (2 * MU)) & 3) > 0;
+    }
+    blk_hop_spin<MU, 0, WRAP>(W, u, l, qu, ql, inf, inb, snf, snb, wraps, (A)gf, (A)gb);
+    blk_hop_spin<MU, 1, WRAP>(W, u, l, qu, ql, inf, inb, snf, snb, wraps, (A)gf, (A)gb);
+}
+
+// ---- the t direction through LDS
+template <int SP, typename LT, typename A>
+__device__ __forceinline__ void blk_t_post_spin(LT &L, const cx<A> W[9], int s, const cx<A> u[6], const cx<A> l[6])
+{
+    cx<A> h[3], t[3];
+    proj_spin<3, -1, SP>(u, l, h);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) L.tf[3 * SP + c][s] = h[c];
+    proj_spin<3, +1, SP>(u, l, h);
+    su3_spin_adj(W, h, t);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) L.tb[3 * SP + c][s] = t[c];
+}
+template <int SP, bool WRAP, typename LT, typename A>
+__device__ __forceinline__ void blk_t_take_spin(LT &L, const cx<A> W[9], cx<A> qu[6], cx<A> ql[6], bool inf,
+                                                 bool inb, int snf, int snb, bool wraps, A kf, A kb)
+{
+    cx<A> h[3], t[3];
+    if (inf) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) h[c] = L.tf[3 * SP + c][snf];
+        su3_spin(W, h, t);
+        if (WRAP && wraps) recon_spin<3, -1, SP, false>(qu, ql, t, kf);
+        else recon_spin<3, -1, SP, true>(qu, ql, t, kf);
+    }
+    if (inb) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) h[c] = L.tb[3 * SP + c][snb];
+        if (WRAP && wraps) recon_spin<3, +1, SP, false>(qu, ql, h, kb);
+        else recon_spin<3, +1, SP, true>(qu, ql, h, kb);
+    }
+}
+
+// ---- faces of direction MU (layout and contents: block_ops.h)
+template <int MU, typename S, typename A>
+__device__ __forceinline__ void blk_face_load(const Geom &g, int b, const int bc[4], int s, int r, int nrhs,
+                                               const vec2_t<S> *__restrict__ F, vec2_t<S> raw[6])
+{
+    const int l = (s >> (2 * MU)) & 3;
+    if (g.nb[MU] == 1 || (l != 0 && l != BEXT - 1)) return;
+    const int dir = l == 0 ? -1 : 1;
+    int bn, sn, sign;
+    bool inb;
+    neighbour_rt(g, b, bc, s, MU, dir, bn, sn, sign, inb);
+    const vec2_t<S> *fp = F + ((long)bn * nrhs + r) * FACE_ELEMS + (2 * MU + (dir < 0 ? 1 : 0)) * 6 * 64 + face_index(s, MU);
+#pragma unroll
+    for (int e = 0; e < 6; ++e) raw[e] = fp[e * 64];
+}
+template <int MU, typename S, typename A>
+__device__ __forceinline__ void blk_face_add(const Geom &g, const int bc[4], int s, const vec2_t<S> raw[6],
+                                              const cx<A> W[9], cx<A> qu[6], cx<A> ql[6])
+{
+    if (g.nb[MU] == 1) return; // uniform: the in-block exchange wraps
+    const int l = (s >> (2 * MU)) & 3;
+    // the link and the published half spinors carry -1/2: only the boundary sign remains
+    if (l == 0) {
+        const A k = bc[MU] == 0 ? (A)g.bcs[MU] : (A)1;
+        cx<A> h[6];
+#pragma unroll
+        for (int e = 0; e < 6; ++e) h[e] = ldc<A>(&raw[e]);
+        recon_spin<MU, +1, 0, false>(qu, ql, h, k);
+        recon_spin<MU, +1, 1, false>(qu, ql, h + 3, k);
+    } else if (l == BEXT - 1) {
+        const A k = bc[MU] + 1 == g.nb[MU] ? (A)g.bcs[MU] : (A)1;
+        cx<A> h[6], t[3];
+#pragma unroll
+        for (int e = 0; e < 6; ++e) h[e] = ldc<A>(&raw[e]);
+        su3_spin(W, h, t);
+        recon_spin<MU, -1, 0, false>(qu, ql, t, k);
+        su3_spin(W, h + 3, t);
+        recon_spin<MU, -1, 1, false>(qu, ql, t, k);
+    }
+}
+template <int MU, typename S, typename A>
+__device__ __forceinline__ void blk_face_publish(vec2_t<S> *__restrict__ base, int s, const cx<A> u[6], const cx<A> l[6],
+                                                  const cx<A> W[9])
+{
+    const int lm = (s >> (2 * MU)) & 3;
+    vec2_t<S> *fp = base + (2 * MU) * 6 * 64 + face_index(s, MU);
+    cx<A> h[3], t[3];
+    if (lm == 0) {
+        proj_spin<MU, -1, 0>(u, l, h);
+#pragma unroll
+        for (int e = 0; e < 3; ++e) stc(fp + e * 64, h[e]);
+        proj_spin<MU, -1, 1>(u, l, h);
+#pragma unroll
+        for (int e = 0; e < 3; ++e) stc(fp + (3 + e) * 64, h[e]);
+    } else if (lm == BEXT - 1) {
+        proj_spin<MU, +1, 0>(u, l, h);
+        su3_spin_adj(W, h, t);
+#pragma unroll
+        for (int e = 0; e < 3; ++e) stc(fp + (6 + e) * 64, t[e]);
+        proj_spin<MU, +1, 1>(u, l, h);
+        su3_spin_adj(W, h, t);
+#pragma unroll
+        for (int e = 0; e < 3; ++e) stc(fp + (9 + e) * 64, t[e]);
+    }
+}
+
+struct SArgs {
+    Geom g;
+    const int *blocks; // block ids of the swept colour
+    int nblk;
+    int nrhs;
+    int rpg; // right-hand sides per workgroup (rhs_per_group)
+    int nmr;
+    int mode; // 0: psi = 0 everywhere; 1: psi_B = 0 on this colour; 2: general
+    double m0[MAXRHS];
+    const double *m0_dev; // per-rhs masses in device memory (overrides m0 when set)
+    const long *eta_off;  // per-rhs element offsets of eta and psi (nullable)
+    const long *psi_off;
+    const int *active;    // right-hand sides with active[r] == 0 are skipped (nullable)
+    int publish;          // write the face buffers for the next sweep
+    int r12;              // links stored as SU(3): read two rows, rebuild the third
+    int sig;              // the clover term is sigma . F: mirrored slots are not read
+    int write_r;          // plain sweep: store the block residual for the next visit
+};
+
+// The block (grid x) and the right-hand sides [r0, r1) (grid y) of this
+// workgroup.  False when none of them is active (uniform: nothing to do).
+__device__ __forceinline__ bool sweep_part(const SArgs &a, int &b, int &r0, int &r1)
+{
+    b = a.blocks[xcd_remap(blockIdx.x, gridDim.x)];
+    r0 = blockIdx.y * a.rpg;
+    r1 = min(r0 + a.rpg, a.nrhs);
+    if (!a.active) return true;
+    bool any = false;
+    for (int r = r0; r < r1; ++r) any |= a.active[r] != 0;
+    return any;
+}
+
+// The MR coefficient of one right-hand side: the dot products <q, r> and
+// <q, q> over the block (DPP sums within each wavefront, then a fixed-order
+// combine of the four wavefronts through LDS), alpha = <q, r>/<q, q>; returns
+// false when <q, q> vanishes (uniform over the workgroup).
+template <typename LT, typename A>
+__device__ __forceinline__ bool mr_alpha(LT &L, int lane, int wave, const cx<A> q[12], const cx<A> rr[12],
+                                         cx<A> &alpha)
+{
+    A qr_re = 0, qr_im = 0, qq = 0;
+#pragma unroll
+    for (int c = 0; c < 12; ++c) {
+        qr_re = fma(q[c].re, rr[c].re, qr_re);
+        qr_re = fma(q[c].im, rr[c].im, qr_re);
+        qr_im = fma(q[c].re, rr[c].im, qr_im);
+        qr_im = fma(-q[c].im, rr[c].re, qr_im);
+        qq = fma(q[c].re, q[c].re, qq);
+        qq = fma(q[c].im, q[c].im, qq);
+    }
+    qr_re = wave_sum(qr_re);
+    qr_im = wave_sum(qr_im);
+    qq = wave_sum(qq);
+    if (lane == 63) { // where wave_sum leaves the total
+        L.red[wave][0] = qr_re;
+        L.red[wave][1] = qr_im;
+        L.red[wave][2] = qq;
+    }
+    __syncthreads();
+    qr_re = ((L.red[0][0] + L.red[1][0]) + L.red[2][0]) + L.red[3][0];
+    qr_im = ((L.red[0][1] + L.red[1][1]) + L.red[2][1]) + L.red[3][1];
+    qq = ((L.red[0][2] + L.red[1][2]) + L.red[2][2]) + L.red[3][2];
+    if (qq == (A)0) return false;
+    alpha = mk<A>(qr_re / qq, qr_im / qq);
+    return true;
+}
+
+// SF is the storage type of the links and the clover term (S, or FP16 fields
+// under FP32 spinors).
+template <typename S, typename A, typename SF, int WAVES, bool WRAP, bool SIG>
+__global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(WAVES))) void k_sap_sweep(
+    const vec2_t<S> *__restrict__ eta0, vec2_t<S> *__restrict__ psi0, const vec2_t<SF> *__restrict__ links,
+    const vec2_t<SF> *__restrict__ clov, vec2_t<S> *__restrict__ faces, vec2_t<S> *__restrict__ resid, SArgs a)
+{
+    constexpr bool PL = PSI_LDS<S, WRAP, SIG>;
+    __shared__ SweepLds<S, A, PL> L;
+    int b, rhs0, rhs1;
+    if (!sweep_part(a, b, rhs0, rhs1)) return;
+    const int s = threadIdx.x;
+    const int lane = s & 63, wave = s >> 6;
+    int bc[4];
+    block_coords(a.g, b, bc);
+
+    // register-resident links carry the hop factor -1/2
+    cx<A> U[4][9];
+    load_links4<A, true>(links + (long)b * 4 * 9 * BS + s, a.r12, (A)(-0.5), U);
+    const vec2_t<SF> *cp = clov + (long)b * 36 * BS + s;
+    constexpr bool HOLD = SIG && sizeof(A) == 4; // both clover halves in registers
+    cx<A> cl[HOLD ? 36 : 18];
+#pragma unroll
+    for (int e = 0; e < (HOLD ? 36 : 18); ++e)
+        if (clover_reads(SIG, e % 18)) cl[e] = ldc_stream<A>(cp + e * BS);
+
+    for (int r = rhs0; r < rhs1; ++r) {
+        // no barrier between right-hand sides: the t buffers and the partial
+        // sums are rewritten only after the barriers of this one's first MR
+        // step follow the last reads of the previous one's, the rest is each
+        // thread's own
+        if (a.active && !a.active[r]) continue; // uniform over the workgroup
+        const A diag = (A)(4.0 + (a.m0_dev ? a.m0_dev[r] : a.m0[r]));
+        const vec2_t<S> *__restrict__ eta = eta0 + (a.eta_off ? a.eta_off[r] : 0);
+        vec2_t<S> *__restrict__ psi = psi0 + (a.psi_off ? a.psi_off[r] : 0);
+        const long sp = ((long)b * a.nrhs + r) * 12 * BS + s; // (the carried residual has no slot offsets)
+        // rho = R - (hops of the other colour's last update), R being this
+        // block's residual after its previous visit (eta on the first)
+        if (PL && a.mode == 2) {
+#pragma unroll
+            for (int c = 0; c < 12; ++c) L.psi[c][s] = psi[sp + c * BS];
+        }
+        const vec2_t<S> *__restrict__ src = a.mode == 2 ? resid : eta;
+        vec2_t<S> er[12];
+#pragma unroll
+        for (int c = 0; c < 12; ++c) er[c] = src[sp + c * BS];
+        cx<A> rr[12], q[12];
+#pragma unroll
+        for (int c = 0; c < 12; ++c) q[c] = mk<A>(0, 0);
+        if (!PL && a.mode != 0) {
+            vec2_t<S> f[6];
+            blk_face_load<0, S, A>(a.g, b, bc, s, r, a.nrhs, faces, f);
+            blk_face_add<0, S, A>(a.g, bc, s, f, U[0], q, q + 6);
+            blk_face_load<1, S, A>(a.g, b, bc, s, r, a.nrhs, faces, f);
+            blk_face_add<1, S, A>(a.g, bc, s, f, U[1], q, q + 6);
+            blk_face_load<2, S, A>(a.g, b, bc, s, r, a.nrhs, faces, f);
+            blk_face_add<2, S, A>(a.g, bc, s, f, U[2], q, q + 6);
+            blk_face_load<3, S, A>(a.g, b, bc, s, r, a.nrhs, faces, f);
+            blk_face_add<3, S, A>(a.g, bc, s, f, U[3], q, q + 6);
+        }
+        if (PL && a.mode != 0) face_consume<S, A>(a.g, b, bc, s, r, a.nrhs, faces, U, q);
+#pragma unroll
+        for (int c = 0; c < 12; ++c) rr[c] = ldc<A>(&er[c]) - q[c];
+        // MR on D_BB: delta += alpha r, r -= alpha q
+        int it = 0;
+        for (; it < a.nmr; ++it) {
+            const bool wraps = a.g.nb[3] == 1; // uniform
+            int bn, snf, snb, gf, gb;
+            bool inf, inb;
+            neighbour<3, +1>(a.g, b, bc, s, bn, snf, gf, inf);
+            neighbour<3, -1>(a.g, b, bc, s, bn, snb, gb, inb);
+            if (!WRAP) {
+                inf = s < 3 * 64;
+                inb = s >= 64;
+            }
+#pragma unroll
+            for (int c = 0; c < 12; ++c) q[c] = mk<A>(0, 0);
+            blk_t_post_spin<0>(L, U[3], s, rr, rr + 6);
+            blk_t_post_spin<1>(L, U[3], s, rr, rr + 6);
+            constexpr bool LATE = !HOLD && sizeof(SF) == 2;
+            vec2_t<SF> c2late[LATE ? 18 : 1];
+            if constexpr (HOLD) {
+                clover_half_mac<A, SIG>(cl, diag, rr, q);
+                clover_half_mac<A, SIG>(cl + 18, diag, rr + 6, q + 6);
+            } else {
+                const vec2_t<SF> *cp1 = cp + 18 * BS;
+                // the address is the same at every MR step: hide that, or the
+                // loads leave the loop and the half is held in registers
+                asm volatile("" : "+v"(cp1));
+                if constexpr (LATE) {
+#pragma unroll
+                    for (int e = 0; e < 18; ++e)
+                        if (clover_reads(SIG, e)) c2late[e] = cp1[e * BS];
+                    clover_half_mac<A, SIG>(cl, diag, rr, q);
+                } else {
+                    cx<A> c2[18];
+#pragma unroll
+                    for (int e = 0; e < 18; ++e)
+                        if (clover_reads(SIG, e)) c2[e] = ldc<A>(cp1 + e * BS);
+                    clover_half_mac<A, SIG>(cl, diag, rr, q);
+                    clover_half_mac<A, SIG>(c2, diag, rr + 6, q + 6);
+                }
+            }
+            blk_hop<0, WRAP>(a.g, b, bc, s, U[0], rr, rr + 6, q, q + 6);
+            blk_hop<1, WRAP>(a.g, b, bc, s, U[1], rr, rr + 6, q, q + 6);
+            blk_hop<2, WRAP>(a.g, b, bc, s, U[2], rr, rr + 6, q, q + 6);
+            __syncthreads();
+            blk_t_take_spin<0, WRAP>(L, U[3], q, q + 6, inf, inb, snf, snb, wraps, (A)gf, (A)gb);
+            blk_t_take_spin<1, WRAP>(L, U[3], q, q + 6, inf, inb, snf, snb, wraps, (A)gf, (A)gb);
+            if constexpr (LATE) {
+                cx<A> c2[18];
+#pragma unroll
+                for (int e = 0; e < 18; ++e)
+                    if (clover_reads(SIG, e)) c2[e] = ldc<A>(&c2late[e]);
+                clover_half_mac<A, SIG>(c2, diag, rr + 6, q + 6);
+            }
+            cx<A> alpha;
+            if (!mr_alpha(L, lane, wave, q, rr, alpha)) break;
+#pragma unroll
+            for (int c = 0; c < 12; ++c) {
+                cx<A> d = mk<A>(0, 0);
+                if (it > 0) d = L.del[c][s];
+                cmac(d, alpha, rr[c]);
+                L.del[c][s] = d;
+                rr[c] = rr[c] - alpha * q[c];
+            }
+        }
+        // psi_B += delta; the residual carried to the next visit; the faces
+        // of delta for the other colour
+        if (!PL && a.mode == 2) {
+#pragma unroll
+            for (int c = 0; c < 12; ++c) er[c] = psi[sp + c * BS];
+        }
+        if (a.write_r) {
+#pragma unroll
+            for (int c = 0; c < 12; ++c) stc(resid + sp + c * BS, rr[c]);
+        }
+#pragma unroll
+        for (int c = 0; c < 12; ++c) rr[c] = it > 0 ? L.del[c][s] : mk<A>(0, 0);
+        if (a.publish) {
+            vec2_t<S> *base = faces + ((long)b * a.nrhs + r) * FACE_ELEMS;
+            blk_face_publish<0, S, A>(base, s, rr, rr + 6, U[0]);
+            blk_face_publish<1, S, A>(base, s, rr, rr + 6, U[1]);
+            blk_face_publish<2, S, A>(base, s, rr, rr + 6, U[2]);
+            blk_face_publish<3, S, A>(base, s, rr, rr + 6, U[3]);
+        }
+#pragma unroll
+        for (int c = 0; c < 12; ++c) {
+            cx<A> v = rr[c];
+            if (a.mode == 2) v = v + ldc<A>(PL ? &L.psi[PL ? c : 0][s] : &er[c]);
+            stc(psi + sp + c * BS, v);
+        }
+    }
+}
+
+} // namespace dd

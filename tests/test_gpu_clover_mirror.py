@@ -51,3 +51,28 @@ def test_broken_mirror_is_read(lat, prec, entry):
     assert site_err(out, ref) <= 10 * REL_TOL_APPLY[prec]
     sap = oracle.sap(DIMS, (4, 4, 4, 4), lat.U, full, m0, psi, 2, 4, BC)
     check_sap(gpu_sap(lat.ctx, psi, m0, 2, 4, prec), sap, prec, f"mirror {entry}")
+
+
+@pytest.mark.parametrize("dims", [(8, 8, 8, 8), (4, 8, 8, 8)])
+@pytest.mark.parametrize("prec", ["f64", "f32", "f16"])
+def test_smoother_forms(dims, prec):
+    """The four forms of the sweep (with and without a direction that one
+    block spans, mirrored and explicit clover term), with all nine link
+    entries read too, two right-hand sides each, against the oracle."""
+    lat = Lattice(dims, eps=0.4, seed=53)
+    eta, m0 = synth.gaussian_spinor(dims, nrhs=2, seed=54), np.array([-0.25, 0.1])
+    broken = halves(lat.C)
+    broken[0, 0, 3, 4] += 0.25
+    broken[0, 0, 4, 3] = np.conj(broken[0, 0, 3, 4])
+    full = np.zeros_like(lat.C)
+    full[:, :6, :6], full[:, 6:, 6:] = broken[:, 0], broken[:, 1]
+    for clover in (None, broken):
+        if clover is not None:
+            lat.ctx.set_clover(clover)
+        for compressed in (True, False):
+            lat.ctx.set_link_compression(compressed)
+            out = gpu_sap(lat.ctx, eta, m0, 3, 4, prec, nrhs=2)
+            for r in range(2):
+                C = lat.C if clover is None else full
+                ref = oracle.sap(dims, (4, 4, 4, 4), lat.U, C, m0[r], eta[r], 3, 4, BC)
+                check_sap(out[r], ref, prec, f"form {dims} {clover is None} {compressed} r={r}")
