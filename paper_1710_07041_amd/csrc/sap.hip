@@ -50,8 +50,15 @@ namespace {
 // Even-odd preconditioned block solve (site parity p = (x+y+z+t) mod 2).  On
 // block B, with A = (4 + m0) + C site-local and H the in-block hops,
 //   S = A_ee - H_eo A_oo^-1 H_oe on the even sites,
-//   rhat_e = rho_e - H_eo A_oo^-1 rho_o,  nMR MR steps on S,
-//   delta_o = A_oo^-1 (rho_o - H_oe delta_e).
+//   y_o = A_oo^-1 rho_o,  r_e = rho_e - H_eo y_o,  nMR MR steps on S: with
+//   w_o = A_oo^-1 H_oe r_e, q_e = A_ee r_e - H_eo w_o: delta_e += alpha r_e,
+//   r_e -= alpha q_e, and delta_o = y_o - sum alpha w_o, which is
+//   A_oo^-1 (rho_o - H_oe delta_e) without another exchange and solve.
+// The odd equations hold exactly after the solve, so the block residual that
+// the next visit starts from is r_e on the even sites and zero on the odd ones:
+// FP32 and FP64 carry it, as the plain sweep does.  FP16 storage recomputes the
+// residual from the stored psi, which takes out what rounding psi at every
+// visit left (3.4e-4 against 7e-4 in the result).
 // Threads 0-127 (waves 0-1) own the even sites, threads 128-255 (waves 2-3)
 // the odd ones, so every parity branch is uniform over a wavefront.  A hop
 // exchange between the parities is pipelined: at stage k the publishing
@@ -59,10 +66,14 @@ namespace {
 // the other LDS buffer.  A_oo^-1 is applied through the Cholesky factor of
 // each chiral half (the halves are Hermitian positive definite: the clover
 // term is small against 4 + m0).
+// What bounds it: a chain of 1 + 2 nMR exchanges of five barriers each, with
+// half the wavefronts idle in the first and last stage of each; so what counts
+// are few exchanges and a second workgroup per CU to fill them (FP32
+// arithmetic).  24^3x48, twelve cycles, against the form that recomputed the
+// residual, took the odd sites from an exchange and a solve of their own and
+// ran one workgroup per CU: FP32 6.49 -> 3.67 ms a call, FP16 6.10 -> 3.56,
+// FP64 (one workgroup per CU still) 11.5 -> 10.1.
 // ---------------------------------------------------------------------------
-
-// Whether the even-odd sweep of storage type S uses the face buffers.
-template <typename S> constexpr bool EO_FACES = !std::is_same<S, double>::value;
 
 // Site of thread t: the pair {2k, 2k+1} (k = t mod 128) holds one even and
 // one odd site; which is which follows from (ly + lz + lt) mod 2.
@@ -136,19 +147,14 @@ template <typename A> __device__ __forceinline__ void chol_solve(const cx<A> f[1
     }
 }
 
-// LDS of the even-odd sweep.  The residual on entry uses the plain block
-// exchange (all 256 sites post); the parity exchanges post only one parity
-// at a time, so their buffers are indexed by the ordinal k = s / 2 of the
-// posting site and share the memory of the full exchange, next to rho of
-// the odd sites.
+// LDS of the even-odd sweep.  One parity posts at a time: the exchange buffers
+// are indexed by the ordinal k = s / 2 of the posting site.
 template <typename A> struct EoLds {
     cx<A> hf[2][6][BS / 2];
     cx<A> hb[2][6][BS / 2];
-    cx<A> rho[12][BS / 2]; // rho of the odd sites
-};
-template <typename A> union SapEoShared {
-    Lds<A> full;
-    EoLds<A> eo;
+    cx<A> del[12][BS / 2]; // delta_e (by even ordinal)
+    cx<A> f1[18][BS];      // chiral half 1 by thread: clover (even), Cholesky factor of A_oo (odd)
+    A red[4][4];
 };
 
 // Post direction MU of v (this thread's site s) into buffer X.
@@ -167,15 +173,16 @@ __device__ __forceinline__ void eo_publish(EoLds<A> &L, int X, int s, const cx<A
 }
 
 // Take direction MU from buffer X: q += the two in-block hops of site s.
-template <int MU, typename A>
+template <int MU, bool WRAP, typename A>
 __device__ __forceinline__ void eo_consume(EoLds<A> &L, int X, const Geom &g, int b, const int bc[4], int s,
                                            const cx<A> U[9], cx<A> q[12])
 {
-    const bool wraps = g.nb[MU] == 1; // uniform
+    const bool wraps = WRAP && g.nb[MU] == 1; // uniform
     cx<A> h[6], t[6];
     int bn, sn, sign;
     bool inb;
     neighbour<MU, +1>(g, b, bc, s, bn, sn, sign, inb);
+    if (!WRAP) inb = ((s >> (2 * MU)) & 3) < BEXT - 1;
     if (inb) {
 #pragma unroll
         for (int c = 0; c < 6; ++c) h[c] = L.hf[X][c][sn >> 1];
@@ -184,6 +191,7 @@ __device__ __forceinline__ void eo_consume(EoLds<A> &L, int X, const Geom &g, in
         else recon_minus1<MU>(q, t);
     }
     neighbour<MU, -1>(g, b, bc, s, bn, sn, sign, inb);
+    if (!WRAP) inb = ((s >> (2 * MU)) & 3) > 0;
     if (inb) {
 #pragma unroll
         for (int c = 0; c < 6; ++c) t[c] = L.hb[X][c][sn >> 1];
@@ -197,48 +205,38 @@ __device__ __forceinline__ void eo_consume(EoLds<A> &L, int X, const Geom &g, in
 // k - 1 (the two LDS buffers alternate), one barrier per stage.  Buffer reuse
 // is safe across consecutive calls: a buffer is rewritten only after a
 // barrier that follows its last read.
-template <typename A>
+template <bool WRAP, typename A>
 __device__ __forceinline__ void eo_exchange(EoLds<A> &L, const Geom &g, int b, const int bc[4], int s,
                                             const cx<A> Ur[4][9], bool pub, const cx<A> v[12], cx<A> q[12])
 {
     if (pub) eo_publish<0, A>(L, 0, s, Ur[0], v);
     __syncthreads();
     if (pub) eo_publish<1, A>(L, 1, s, Ur[1], v);
-    else eo_consume<0, A>(L, 0, g, b, bc, s, Ur[0], q);
+    else eo_consume<0, WRAP, A>(L, 0, g, b, bc, s, Ur[0], q);
     __syncthreads();
     if (pub) eo_publish<2, A>(L, 0, s, Ur[2], v);
-    else eo_consume<1, A>(L, 1, g, b, bc, s, Ur[1], q);
+    else eo_consume<1, WRAP, A>(L, 1, g, b, bc, s, Ur[1], q);
     __syncthreads();
     if (pub) eo_publish<3, A>(L, 1, s, Ur[3], v);
-    else eo_consume<2, A>(L, 0, g, b, bc, s, Ur[2], q);
+    else eo_consume<2, WRAP, A>(L, 0, g, b, bc, s, Ur[2], q);
     __syncthreads();
-    if (!pub) eo_consume<3, A>(L, 1, g, b, bc, s, Ur[3], q);
+    if (!pub) eo_consume<3, WRAP, A>(L, 1, g, b, bc, s, Ur[3], q);
 }
 
-// x = M^-1 x in place with the factor of chiral half 1 held in LDS.
-template <typename A> __device__ __forceinline__ void chol_solve_lds(const cx<A> (*F)[BS / 2], int k, cx<A> x[6])
-{
-    cx<A> f[18];
-#pragma unroll
-    for (int e = 0; e < 18; ++e) f[e] = F[e][k];
-    chol_solve<A>(f, x);
-}
+// Whether the even-odd sweep of storage type S carries the block residual.
+template <typename S> constexpr bool EO_CARRY = sizeof(S) > 2;
 
-template <typename S, typename A, typename RES>
-__global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(RES::waves))) void k_sap_sweep_eo(
+template <typename S, typename A, int WAVES, bool WRAP>
+__global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(WAVES))) void k_sap_sweep_eo(
     const vec2_t<S> *__restrict__ eta0, vec2_t<S> *__restrict__ psi0, const vec2_t<S> *__restrict__ links,
-    const vec2_t<S> *__restrict__ clov, vec2_t<S> *__restrict__ faces, SArgs a)
+    const vec2_t<S> *__restrict__ clov, vec2_t<S> *__restrict__ faces, vec2_t<S> *__restrict__ resid, SArgs a)
 {
-    static_assert(RES::links && RES::clover_half, "even-odd sweep: links and clover half 0 in registers");
-    __shared__ SapEoShared<A> SH;
-    __shared__ cx<A> Dd[12][BS / 2]; // delta_e of the even sites (by even ordinal)
-    __shared__ cx<A> F1[18][BS / 2]; // Cholesky factor of chiral half 1 of the odd sites
-    Lds<A> &L = SH.full;
-    EoLds<A> &E = SH.eo;
+    constexpr bool CARRY = EO_CARRY<S>;
+    __shared__ EoLds<A> E;
     int b, rhs0, rhs1;
     if (!sweep_part(a, b, rhs0, rhs1)) return;
     const int tid = threadIdx.x, s = eo_site(tid), k = tid & (BS / 2 - 1);
-    const bool odd = tid >= BS / 2; // uniform over a wavefront
+    const bool odd = __builtin_amdgcn_readfirstlane(tid >> 7) != 0;
     const int lane = tid & 63, wave = tid >> 6;
     int bc[4];
     block_coords(a.g, b, bc);
@@ -246,162 +244,129 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(RES::waves))
     // register-resident links carry the hop factor -1/2
     cx<A> U[4][9];
     load_links4<A, true>(links + (long)b * 4 * 9 * BS + s, a.r12, (A)(-0.5), U);
-    const vec2_t<S> *cp0 = clov + (long)b * 36 * BS + s;
 
+    // no barrier between right-hand sides: every buffer is rewritten only
+    // after a barrier that follows its last read (eo_exchange), or is each
+    // thread's own
     for (int r = rhs0; r < rhs1; ++r) {
         if (a.active && !a.active[r]) continue; // uniform over the workgroup
         const A diag = (A)(4.0 + (a.m0_dev ? a.m0_dev[r] : a.m0[r]));
         const vec2_t<S> *__restrict__ eta = eta0 + (a.eta_off ? a.eta_off[r] : 0);
         vec2_t<S> *__restrict__ psi = psi0 + (a.psi_off ? a.psi_off[r] : 0);
-        const long sp = ((long)b * a.nrhs + r) * 12 * BS + s;
-        // clover half 0 (odd sites factor it in place below, so it is
-        // reloaded for every right-hand side)
-        cx<A> cl[18];
-        load_clover_half<A>(cp0, a.sig, cl);
-        if (odd) {
-            // factor of chiral half 1 of A_oo = (4 + m0) + C, kept in LDS
-            cx<A> c1[18];
-            load_clover_half<A>(cp0 + 18 * BS, a.sig, c1);
-            chol_half<A>(c1, diag);
-#pragma unroll
-            for (int e = 0; e < 18; ++e) F1[e][k] = c1[e];
-        }
+        const long sp = ((long)b * a.nrhs + r) * 12 * BS + s; // (the carried residual has no slot offsets)
+        // the clover term's addresses are the same for every right-hand side:
+        // hide that, or they leave the loop and spill
+        int zero = 0;
+        asm volatile("" : "+s"(zero));
+        const vec2_t<S> *cp = clov + (long)b * 36 * BS + s + zero;
 
-        // rho = eta - (D psi)_B
-        cx<A> rho[12], q[12];
-        {
-            cx<A> p0[12];
+        // rho = R - (hops of the other colour's last update), or
+        // eta - (D psi)_B; rr takes it
+        cx<A> rr[12], q[12], cl[18];
+#pragma unroll
+        for (int c = 0; c < 12; ++c) q[c] = mk<A>(0, 0);
+        if constexpr (!CARRY) {
             if (a.mode == 2) {
 #pragma unroll
-                for (int c = 0; c < 12; ++c) p0[c] = ldc<A>(psi + sp + c * BS);
-                // threads own sites by parity here, not site = thread
-                block_apply<S, A, RES, false, false>(L, a.g, b, bc, s, U, cl, links, clov, diag, p0, q);
-            } else {
-#pragma unroll
-                for (int c = 0; c < 12; ++c) q[c] = mk<A>(0, 0);
+                for (int c = 0; c < 12; ++c) rr[c] = ldc<A>(psi + sp + c * BS);
+#pragma unroll 1
+                for (int h = 0; h < 2; ++h) {
+                    load_clover_half<A>(cp + 18 * h * BS, a.sig, cl);
+                    if (h == 0) clover_half_mac<A>(cl, diag, rr, q);
+                    else clover_half_mac<A>(cl, diag, rr + 6, q + 6);
+                }
+                eo_exchange<WRAP>(E, a.g, b, bc, s, U, odd, rr, q);
+                eo_exchange<WRAP>(E, a.g, b, bc, s, U, !odd, rr, q);
             }
         }
-        // the boundary hops, from the faces the other colour published, with
-        // eta in flight during the face trips (in FP64 the other colour's psi
-        // and links are read instead, and eta afterwards: the face code does
-        // not fit this sweep's FP64 register budget)
-        if constexpr (EO_FACES<S>) {
-            vec2_t<S> er[12];
+        vec2_t<S> er[12];
+        const bool fresh = !CARRY || a.mode != 2; // rho starts from eta
 #pragma unroll
-            for (int c = 0; c < 12; ++c) er[c] = eta[sp + c * BS];
-            if (a.mode != 0) face_consume<S, A>(a.g, b, bc, s, r, a.nrhs, faces, U, q);
+        for (int c = 0; c < 12; ++c) er[c] = fresh ? eta[sp + c * BS] : (odd ? vec2_t<S>{} : resid[sp + c * BS]);
+        if (a.mode != 0) face_consume<S, A>(a.g, b, bc, s, r, a.nrhs, faces, U, q);
 #pragma unroll
-            for (int c = 0; c < 12; ++c) rho[c] = ldc<A>(&er[c]) - q[c];
-        } else {
-            if (a.mode != 0) face_hops<S, S, A, true>(a.g, b, bc, s, r, a.nrhs, psi, links, U, q, a.r12);
-#pragma unroll
-            for (int c = 0; c < 12; ++c) rho[c] = ldc<A>(eta + sp + c * BS) - q[c];
-        }
-        // the parity exchanges reuse the memory of the full one
-        __syncthreads();
+        for (int c = 0; c < 12; ++c) rr[c] = ldc<A>(&er[c]) - q[c];
 
-        // Two vectors per thread from here on: r (even sites) and q.  In each
-        // parity exchange the posting waves read q or r and the receiving
-        // waves accumulate into q, so one array serves both roles.
-        cx<A> rr[12];
+        // the site's clover term (odd sites: the Cholesky factors of A_oo),
+        // half 1 in LDS
+        load_clover_half<A>(cp + 18 * BS, a.sig, cl);
+        if (odd) chol_half<A>(cl, diag);
+#pragma unroll
+        for (int e = 0; e < 18; ++e) E.f1[e][tid] = cl[e];
+        if (odd) chol_solve<A>(cl, rr + 6);
+        load_clover_half<A>(cp, a.sig, cl);
         if (odd) {
-            // rho_o to LDS; factor chiral half 0 in place; q = A_oo^-1 rho_o
-#pragma unroll
-            for (int c = 0; c < 12; ++c) E.rho[c][k] = rho[c];
             chol_half<A>(cl, diag);
-#pragma unroll
-            for (int c = 0; c < 12; ++c) q[c] = rho[c];
-            chol_solve<A>(cl, q);
-            chol_solve_lds<A>(F1, k, q + 6);
-#pragma unroll
-            for (int c = 0; c < 12; ++c) rr[c] = mk<A>(0, 0);
-        } else {
-#pragma unroll
-            for (int c = 0; c < 12; ++c) {
-                rr[c] = rho[c];
-                q[c] = mk<A>(0, 0);
-                Dd[c][k] = mk<A>(0, 0);
-            }
+            chol_solve<A>(cl, rr);
         }
-        // even: r_e = rho_e - H_eo A_oo^-1 rho_o
-        eo_exchange<A>(E, a.g, b, bc, s, U, odd, q, q);
+        // odd: rr = y_o, from here on delta_o; even: r_e = rho_e - H_eo y_o
+#pragma unroll
+        for (int c = 0; c < 12; ++c) q[c] = mk<A>(0, 0);
+        eo_exchange<WRAP>(E, a.g, b, bc, s, U, odd, rr, q);
         if (!odd) {
 #pragma unroll
             for (int c = 0; c < 12; ++c) rr[c] = rr[c] - q[c];
         }
 
-        // MR on S = A_ee - H_eo A_oo^-1 H_oe
-        for (int it = 0; it < a.nmr; ++it) {
+        int it = 0;
+        for (; it < a.nmr; ++it) {
             // odd: q = H_oe r_e
 #pragma unroll
             for (int c = 0; c < 12; ++c) q[c] = mk<A>(0, 0);
-            eo_exchange<A>(E, a.g, b, bc, s, U, !odd, rr, q);
+            eo_exchange<WRAP>(E, a.g, b, bc, s, U, !odd, rr, q);
+            cx<A> f[18];
+#pragma unroll
+            for (int e = 0; e < 18; ++e) f[e] = E.f1[e][tid];
             if (odd) {
-                // q = -A_oo^-1 H_oe r_e
+                // q = -w_o
                 chol_solve<A>(cl, q);
-                chol_solve_lds<A>(F1, k, q + 6);
+                chol_solve<A>(f, q + 6);
 #pragma unroll
                 for (int c = 0; c < 12; ++c) q[c] = mk<A>(-q[c].re, -q[c].im);
             } else {
                 // q = A_ee r_e
                 clover_half_mac<A>(cl, diag, rr, q);
-                cx<A> c2[18];
-                const vec2_t<S> *cp1 = cp0 + 18 * BS;
-                // the same address at every MR step: hide that, or the loads
-                // leave the loop and the half is held in registers
-                asm volatile("" : "+v"(cp1));
-                load_clover_half<A>(cp1, a.sig, c2);
-                clover_half_mac<A>(c2, diag, rr + 6, q + 6);
+                clover_half_mac<A>(f, diag, rr + 6, q + 6);
             }
-            // even: q = A_ee r_e - H_eo A_oo^-1 H_oe r_e = S r_e
-            eo_exchange<A>(E, a.g, b, bc, s, U, odd, q, q);
+            // even: q = A_ee r_e - H_eo w_o = S r_e
+            eo_exchange<WRAP>(E, a.g, b, bc, s, U, odd, q, q);
+            cx<A> alpha;
+            if (!mr_alpha(E, lane, wave, q, rr, alpha, !odd)) break;
             if (odd) {
 #pragma unroll
-                for (int c = 0; c < 12; ++c) q[c] = mk<A>(0, 0);
-            }
-            cx<A> alpha;
-            if (!mr_alpha(L, lane, wave, q, rr, alpha)) break;
-            if (!odd) {
+                for (int c = 0; c < 12; ++c) cmac(rr[c], alpha, q[c]);
+            } else {
 #pragma unroll
                 for (int c = 0; c < 12; ++c) {
-                    cx<A> d = Dd[c][k];
+                    cx<A> d = mk<A>(0, 0);
+                    if (it > 0) d = E.del[c][k];
                     cmac(d, alpha, rr[c]);
-                    Dd[c][k] = d;
+                    E.del[c][k] = d;
                     rr[c] = rr[c] - alpha * q[c];
                 }
             }
         }
 
-        // odd: delta_o = A_oo^-1 (rho_o - H_oe delta_e); even: delta_e
+        // rr = delta; psi_B += delta; the residual carried to the next visit;
+        // the faces of delta (FP16: of psi as stored) for the other colour
+        if (!odd) {
+            if (CARRY && a.write_r) {
 #pragma unroll
-        for (int c = 0; c < 12; ++c) {
-            rr[c] = odd ? mk<A>(0, 0) : Dd[c][k];
-            q[c] = mk<A>(0, 0);
-        }
-        eo_exchange<A>(E, a.g, b, bc, s, U, !odd, rr, q);
-        if (odd) {
+                for (int c = 0; c < 12; ++c) stc(resid + sp + c * BS, rr[c]);
+            }
 #pragma unroll
-            for (int c = 0; c < 12; ++c) rr[c] = E.rho[c][k] - q[c];
-            chol_solve<A>(cl, rr);
-            chol_solve_lds<A>(F1, k, rr + 6);
-        }
-        // psi_B += delta_B
-        if (a.mode == 2) {
-#pragma unroll
-            for (int c = 0; c < 12; ++c) rr[c] = rr[c] + ldc<A>(psi + sp + c * BS);
+            for (int c = 0; c < 12; ++c) rr[c] = it > 0 ? E.del[c][k] : mk<A>(0, 0);
         }
 #pragma unroll
         for (int c = 0; c < 12; ++c) {
-            vec2_t<S> v;
-            stc(&v, rr[c]);
-            psi[sp + c * BS] = v;
-            rr[c] = ldc<A>(&v); // the stored value, as the other colour would read it
+            cx<A> v = rr[c];
+            if (a.mode == 2) v = v + ldc<A>(psi + sp + c * BS);
+            vec2_t<S> st;
+            stc(&st, v);
+            psi[sp + c * BS] = st;
+            if (!CARRY) rr[c] = ldc<A>(&st);
         }
-        if constexpr (EO_FACES<S>) {
-            if (a.publish) face_publish<S, A>(faces, b, a.nrhs, r, s, rr, U);
-        }
-        // the next right-hand side's residual reuses the LDS read above
-        __syncthreads();
+        if (a.publish) face_publish<S, A>(faces, b, a.nrhs, r, s, rr, U);
     }
 }
 
@@ -463,24 +428,23 @@ Status sweep(dd_ctx *ctx, SArgs a, int prec, const void *eta, void *psi, void *f
     return Status::ok();
 }
 
-// The even-odd sweep holds more per thread (two vectors, the factor or the
-// clover, the four links) and runs at one wavefront per SIMD.
-typedef Residency<true, false, 1, true> ResEO;
-
-template <typename S, typename A>
-Status sweep_eo(dd_ctx *ctx, SArgs a, int prec, const void *eta, void *psi, void *faces, bool quiet)
+template <typename S, typename A, int WAVES>
+Status sweep_eo(dd_ctx *ctx, SArgs a, int prec, const void *eta, void *psi, void *faces, void *resid, bool quiet)
 {
     // recomputing the block residual costs one operator application when
     // psi_B != 0; the right-hand side and the odd reconstruction one in-block
     // hop application per block solve
-    const double fl = 256.0 * a.nblk * a.nrhs * (a.nmr * 2184.0 + (a.mode == 2 ? 1848.0 : 0.0) + 1848.0);
+    constexpr bool CARRY = EO_CARRY<S>;
+    const double fl = 256.0 * a.nblk * a.nrhs * (a.nmr * 2184.0 + (!CARRY && a.mode == 2 ? 1848.0 : 0.0) + 1848.0);
     const int cls = prec == DD_F64 ? K_SAP_EO_F64 : prec == DD_F32 ? K_SAP_EO_F32 : K_SAP_EO_F16;
-    ProfScope ps(ctx->prof, ctx->stream, cls, sweep_bytes(a, sizeof(S), sizeof(S), false), fl, !quiet);
-    a.rpg = rhs_per_group(a.nblk, a.nrhs, ctx->ncu * ResEO::waves);
-    k_sap_sweep_eo<S, A, ResEO><<<dim3(a.nblk, (a.nrhs + a.rpg - 1) / a.rpg), BS, 0, ctx->stream>>>(
+    ProfScope ps(ctx->prof, ctx->stream, cls, sweep_bytes(a, sizeof(S), sizeof(S), CARRY), fl, !quiet);
+    a.rpg = rhs_per_group(a.nblk, a.nrhs, ctx->ncu * WAVES);
+    const bool wrap = a.g.nb[0] == 1 || a.g.nb[1] == 1 || a.g.nb[2] == 1 || a.g.nb[3] == 1;
+    auto kernel = wrap ? k_sap_sweep_eo<S, A, WAVES, true> : k_sap_sweep_eo<S, A, WAVES, false>;
+    kernel<<<dim3(a.nblk, (a.nrhs + a.rpg - 1) / a.rpg), BS, 0, ctx->stream>>>(
         static_cast<const vec2_t<S> *>(eta), static_cast<vec2_t<S> *>(psi),
         static_cast<const vec2_t<S> *>(ctx->links[prec].p), static_cast<const vec2_t<S> *>(ctx->clover[prec].p),
-        static_cast<vec2_t<S> *>(faces), a);
+        static_cast<vec2_t<S> *>(faces), static_cast<vec2_t<S> *>(resid), a);
     DD_HIP_TRY(hipGetLastError());
     return Status::ok();
 }
@@ -554,9 +518,9 @@ Status run_sap(dd_ctx *ctx, const double *m0, int nrhs, const void *eta, void *p
             a.publish = !(cy == ncy - 1 && col == 1);
             a.write_r = cy < ncy - 1;
             if (eo) {
-                DD_TRY((prec == DD_F64   ? sweep_eo<double, double>(ctx, a, prec, eta, psi, faces, quiet)
-                        : prec == DD_F32 ? sweep_eo<float, float>(ctx, a, prec, eta, psi, faces, quiet)
-                                         : sweep_eo<__half, float>(ctx, a, prec, eta, psi, faces, quiet)));
+                DD_TRY((prec == DD_F64   ? sweep_eo<double, double, 1>(ctx, a, prec, eta, psi, faces, resid, quiet)
+                        : prec == DD_F32 ? sweep_eo<float, float, 2>(ctx, a, prec, eta, psi, faces, resid, quiet)
+                                         : sweep_eo<__half, float, 2>(ctx, a, prec, eta, psi, faces, resid, quiet)));
             } else {
                 DD_TRY((prec == DD_F64   ? sweep<double, double, double, 1>(ctx, a, prec, eta, psi, faces, resid, quiet)
                         : prec == DD_F16 ? sweep<__half, float, __half, 2>(ctx, a, prec, eta, psi, faces, resid, quiet)

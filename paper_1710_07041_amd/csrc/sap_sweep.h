@@ -306,17 +306,19 @@ __device__ __forceinline__ bool sweep_part(const SArgs &a, int &b, int &r0, int 
 // false when <q, q> vanishes (uniform over the workgroup).
 template <typename LT, typename A>
 __device__ __forceinline__ bool mr_alpha(LT &L, int lane, int wave, const cx<A> q[12], const cx<A> rr[12],
-                                         cx<A> &alpha)
+                                         cx<A> &alpha, bool mine = true)
 {
     A qr_re = 0, qr_im = 0, qq = 0;
+    if (mine) { // whether this wavefront's sites count
 #pragma unroll
-    for (int c = 0; c < 12; ++c) {
-        qr_re = fma(q[c].re, rr[c].re, qr_re);
-        qr_re = fma(q[c].im, rr[c].im, qr_re);
-        qr_im = fma(q[c].re, rr[c].im, qr_im);
-        qr_im = fma(-q[c].im, rr[c].re, qr_im);
-        qq = fma(q[c].re, q[c].re, qq);
-        qq = fma(q[c].im, q[c].im, qq);
+        for (int c = 0; c < 12; ++c) {
+            qr_re = fma(q[c].re, rr[c].re, qr_re);
+            qr_re = fma(q[c].im, rr[c].im, qr_re);
+            qr_im = fma(q[c].re, rr[c].im, qr_im);
+            qr_im = fma(-q[c].im, rr[c].re, qr_im);
+            qq = fma(q[c].re, q[c].re, qq);
+            qq = fma(q[c].im, q[c].im, qq);
+        }
     }
     qr_re = wave_sum(qr_re);
     qr_im = wave_sum(qr_im);
