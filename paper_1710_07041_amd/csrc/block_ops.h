@@ -1,34 +1,19 @@
-// Block-local building blocks shared by the SAP sweep and the operator
-// kernel that works block by block: the LDS exchange that applies the hops
-// inside a 4^4 block, the clover term, and the hops that leave the block.
+// Block-local building blocks shared by the Schwarz sweeps and the operator
+// kernel that works block by block: the hops inside a 4^4 block, the hops that
+// leave it, and the sums over a wavefront.
 //
 // One 256-thread workgroup owns one block, one thread one site.  D_BB is
 // applied direction by direction: each thread publishes the spin-projected
 // half spinor of its site for the +mu hop of site x-mu, and U_mu(x)^+ times
-// the projected half spinor for the -mu hop of site x+mu, through LDS; so
-// every link of the block is read once and no in-block spinor is re-read
-// from memory.
+// the projected half spinor for the -mu hop of site x+mu, across the lanes of
+// a wavefront (one t-slice) for x, y and z and through LDS for t; so every
+// link of the block is read once and no in-block spinor is re-read from
+// memory.
 #pragma once
 
 #include "dd_device.h"
 
 namespace dd {
-
-// Two buffers, used by alternate directions: direction mu + 2 overwrites the
-// buffer of direction mu only after every thread has passed the barrier of
-// direction mu + 1, i.e. after all reads of direction mu; so each direction
-// needs one barrier, not two, as long as all four directions go through LDS.
-// When the x, y and z hops go across lanes (exchange_dir with LANES) only
-// buffer 1 (t) is used, with one barrier per application: two applications
-// in a row then need a barrier between them (the caller's), or a slow
-// wavefront could still be reading the first one's t hops while a fast one
-// writes the second's.  The plain Schwarz sweep keeps each site's psi_B in
-// buffer 0 meanwhile.
-template <typename A> struct Lds {
-    cx<A> hf[2][6][BS]; // projected half spinors for +mu hops
-    cx<A> hb[2][6][BS]; // U^+ times projected half spinors for -mu hops
-    A red[4][4];
-};
 
 // Direction-dispatched spin algebra for run-time loops over mu (a switch on a
 // uniform value; each case is the compile-time specialisation).
@@ -66,50 +51,6 @@ template <typename A> __device__ __forceinline__ void recon_p(int mu, cx<A> q[12
     case 1: recon_plus<1>(q, t, k); break;
     case 2: recon_plus<2>(q, t, k); break;
     default: recon_plus<3>(q, t, k); break;
-    }
-}
-
-// Where the per-site fields live during a sweep: in registers for the whole
-// sweep, or re-read (from L2: one block's fields stay resident while its
-// workgroup runs) at every block application.  CLOVH keeps chiral half 0 of
-// the clover term in registers and re-reads only half 1, which halves the
-// clover footprint that has to stay in L2 across the MR steps.  SIG: the
-// clover term is sigma . F and its mirrored slots are neither read nor held
-// (dd_device.h).
-template <bool REGLINKS, bool REGCLOV, int WAVES, bool CLOVH = false, bool SIG = false> struct Residency {
-    static constexpr bool links = REGLINKS, clover = REGCLOV, clover_half = CLOVH && !REGCLOV;
-    static constexpr int waves = WAVES;
-    static constexpr bool sigma = SIG;
-    static constexpr int ncl = REGCLOV ? 36 : (CLOVH ? 18 : 1); // clover entries held in registers
-};
-
-template <bool REG, typename S, typename A>
-__device__ __forceinline__ void get_link(const cx<A> Ur[4][9], const vec2_t<S> *__restrict__ links, int b, int s,
-                                         int mu, cx<A> U[9])
-{
-    if (REG) {
-        switch (mu) {
-        case 0:
-#pragma unroll
-            for (int e = 0; e < 9; ++e) U[e] = Ur[0][e];
-            break;
-        case 1:
-#pragma unroll
-            for (int e = 0; e < 9; ++e) U[e] = Ur[REG ? 1 : 0][e];
-            break;
-        case 2:
-#pragma unroll
-            for (int e = 0; e < 9; ++e) U[e] = Ur[REG ? 2 : 0][e];
-            break;
-        default:
-#pragma unroll
-            for (int e = 0; e < 9; ++e) U[e] = Ur[REG ? 3 : 0][e];
-            break;
-        }
-    } else {
-        const vec2_t<S> *u = links + ((long)b * 4 + mu) * 9 * BS + s;
-#pragma unroll
-        for (int e = 0; e < 9; ++e) U[e] = ldc<A>(u + e * BS);
     }
 }
 
@@ -161,189 +102,182 @@ template <int MU, int DIR, typename A> __device__ __forceinline__ cx<A> lane_hop
     }
 }
 
-// One direction of the in-block exchange with the link given in registers,
-// already multiplied by the hop factor -1/2.  With LANES (site s = x + 4y +
-// 16z + 64t of the 4^4 block is thread s) a wavefront holds one t-slice: the
-// x, y and z neighbours are lanes of the same wavefront and are read across
-// lanes; only the t direction goes through LDS and a barrier.  Without LANES
-// (another site-to-thread map) every direction goes through LDS.  In-block
-// neighbours carry the boundary sign only when the block spans the whole
-// direction (one block per direction); otherwise the reconstruction is a
-// plain sum.
-//
-// PHASE splits a direction that goes through LDS: 1 posts this site's half
-// spinors and returns, 2 waits at the barrier and takes the neighbours'
-// (0 does both), so that other work can sit between the two.
-template <int MU, typename S, typename A, bool LANES, int PHASE = 0>
-__device__ __forceinline__ void exchange_dir(Lds<A> &L, const Geom &g, int b, const int bc[4], int s,
-                                             const cx<A> U[9], const cx<A> v[12], cx<A> q[12])
+// ---- one spin (SP = 0, 1) of the projections, SG = -1: (1 - g), +1: (1 + g)
+// h = u_SP + SG (A l)_SP with A_k = -i sigma_k, A_t = 1
+template <int MU, int SG, int SP, typename A>
+__device__ __forceinline__ void proj_spin(const cx<A> u[6], const cx<A> l[6], cx<A> h[3])
 {
-    const bool wraps = g.nb[MU] == 1; // uniform
-    if constexpr (LANES && MU < 3) {
-        cx<A> h[6], t[6];
-        int bn, snf, snb, sign_f, sign_b;
-        bool inf, inbk;
-        neighbour<MU, +1>(g, b, bc, s, bn, snf, sign_f, inf);
-        neighbour<MU, -1>(g, b, bc, s, bn, snb, sign_b, inbk);
-        // +mu hop: the neighbour's projected half spinor, times this site's link
-        proj_minus<MU>(v, h);
+    constexpr int SL = MU < 2 ? 1 - SP : SP; // the lower spin that A mixes in
 #pragma unroll
-        for (int c = 0; c < 6; ++c) t[c] = lane_hop<MU, +1, A>(h[c], snf);
-        if (inf) {
-            su3_mul(U, t, h);
-            if (wraps) recon_minus<MU>(q, h, (A)sign_f);
-            else recon_minus1<MU>(q, h);
-        }
-        // -mu hop: U^+ of the neighbour times its projected half spinor
-        proj_plus<MU>(v, h);
-        su3_mul_adj(U, h, t);
-#pragma unroll
-        for (int c = 0; c < 6; ++c) h[c] = lane_hop<MU, -1, A>(t[c], snb);
-        if (inbk) {
-            if (wraps) recon_plus<MU>(q, h, (A)sign_b);
-            else recon_plus1<MU>(q, h);
-        }
-        return;
+    for (int c = 0; c < 3; ++c) {
+        const cx<A> a = u[3 * SP + c], x = l[3 * SL + c];
+        // (A l): x: -i l1, -i l0; y: -l1, l0; z: -i l0, i l1; t: l0, l1
+        if (MU == 0) h[c] = SG > 0 ? a + tmi(x) : a + ti(x);
+        if (MU == 1) h[c] = (SG > 0) == (SP == 0) ? a - x : a + x;
+        if (MU == 2) h[c] = (SG > 0) == (SP == 0) ? a + tmi(x) : a + ti(x);
+        if (MU == 3) h[c] = SG > 0 ? a + x : a - x;
     }
-    constexpr int X = MU & 1;
-    cx<A> h[6], t[6];
-    if constexpr (PHASE != 2) {
-        proj_minus<MU>(v, h);
+}
+// (u, l) += k (t, SG A^+ t) for the spin SP of t (k = 1 when KONE)
+template <int MU, int SG, int SP, bool KONE, typename A>
+__device__ __forceinline__ void recon_spin(cx<A> u[6], cx<A> l[6], const cx<A> t[3], A k)
+{
+    constexpr int SL = MU < 2 ? 1 - SP : SP;
 #pragma unroll
-        for (int c = 0; c < 6; ++c) L.hf[X][c][s] = h[c];
-        proj_plus<MU>(v, h);
-        su3_mul_adj(U, h, t);
-#pragma unroll
-        for (int c = 0; c < 6; ++c) L.hb[X][c][s] = t[c];
+    for (int c = 0; c < 3; ++c) {
+        const cx<A> x = KONE ? t[c] : k * t[c];
+        u[3 * SP + c] = u[3 * SP + c] + x;
+        cx<A> &y = l[3 * SL + c];
+        // A^+ t: x: i t1, i t0 on l0, l1; y: t1, -t0; z: i t0, -i t1; t: t0, t1
+        if (MU == 0) y = y + (SG > 0 ? ti(x) : tmi(x));
+        if (MU == 1) y = (SG > 0) == (SP == 1) ? y + x : y - x;
+        if (MU == 2) y = y + ((SG > 0) == (SP == 0) ? ti(x) : tmi(x));
+        if (MU == 3) y = SG > 0 ? y + x : y - x;
     }
-    if constexpr (PHASE == 1) return;
-    __syncthreads();
-    int bn, sn, sign;
-    bool inb;
-    neighbour<MU, +1>(g, b, bc, s, bn, sn, sign, inb);
-    if (inb) {
+}
+// t = W h and t = W^+ h for one spin
+template <typename A> __device__ __forceinline__ void su3_spin(const cx<A> W[9], const cx<A> h[3], cx<A> t[3])
+{
 #pragma unroll
-        for (int c = 0; c < 6; ++c) h[c] = L.hf[X][c][sn];
-        su3_mul(U, h, t);
-        if (wraps) recon_minus<MU>(q, t, (A)sign);
-        else recon_minus1<MU>(q, t);
+    for (int a = 0; a < 3; ++a) {
+        cx<A> acc = W[a * 3] * h[0];
+        cmac(acc, W[a * 3 + 1], h[1]);
+        cmac(acc, W[a * 3 + 2], h[2]);
+        t[a] = acc;
     }
-    neighbour<MU, -1>(g, b, bc, s, bn, sn, sign, inb);
-    if (inb) {
+}
+template <typename A> __device__ __forceinline__ void su3_spin_adj(const cx<A> W[9], const cx<A> h[3], cx<A> t[3])
+{
 #pragma unroll
-        for (int c = 0; c < 6; ++c) t[c] = L.hb[X][c][sn];
-        if (wraps) recon_plus<MU>(q, t, (A)sign);
-        else recon_plus1<MU>(q, t);
+    for (int a = 0; a < 3; ++a) {
+        cx<A> acc = conjx(W[a]) * h[0];
+        cmacc(acc, W[3 + a], h[1]);
+        cmacc(acc, W[6 + a], h[2]);
+        t[a] = acc;
+    }
+}
+// row_shl:4 (0x104: lane i reads lane i + 4 of its row) and row_shr:4 (0x114),
+// zero from outside the row
+template <int CTRL> __device__ __forceinline__ int shift_mov(int v)
+{
+    return __builtin_amdgcn_mov_dpp(v, CTRL, 0xf, 0xf, true);
+}
+template <int CTRL, typename A> __device__ __forceinline__ cx<A> row_shift(const cx<A> &v)
+{
+    if constexpr (sizeof(A) == 4) {
+        return mk<A>(__int_as_float(shift_mov<CTRL>(__float_as_int(v.re))), __int_as_float(shift_mov<CTRL>(__float_as_int(v.im))));
+    } else {
+        const long long r = __double_as_longlong(v.re), i = __double_as_longlong(v.im);
+        const int r0 = shift_mov<CTRL>((int)r), r1 = shift_mov<CTRL>((int)(r >> 32));
+        const int i0 = shift_mov<CTRL>((int)i), i1 = shift_mov<CTRL>((int)(i >> 32));
+        return mk<A>(__longlong_as_double(((long long)r1 << 32) | (unsigned)r0),
+                     __longlong_as_double(((long long)i1 << 32) | (unsigned)i0));
     }
 }
 
-// q = D_BB v on the block (all threads of the workgroup take part; LANES:
-// thread s holds site s, which lets the x, y and z hops stay inside a
-// wavefront).  The loops over clover halves and directions are kept as loops
-// so that only one step's loads are in flight per thread (unrolled, the
-// compiler hoists them all and spills).
-template <typename S, typename A, typename RES, bool NTC = false, bool LANES = true>
-__device__ __forceinline__ void block_apply(Lds<A> &L, const Geom &g, int b, const int bc[4], int s,
-                                            const cx<A> Ur[RES::links ? 4 : 1][9], const cx<A> cl[RES::ncl],
-                                            const vec2_t<S> *__restrict__ links_g,
-                                            const vec2_t<S> *__restrict__ clov_g, A diag, const cx<A> v[12],
-                                            cx<A> q[12])
+// ---- in-block hops of direction MU across the lanes of a wavefront
+template <int MU, int SP, bool WRAP, typename A>
+__device__ __forceinline__ void blk_hop_spin(const cx<A> W[9], const cx<A> u[6], const cx<A> l[6], cx<A> qu[6],
+                                              cx<A> ql[6], bool inf, bool inb, int snf, int snb, bool wraps, A kf, A kb)
 {
+    cx<A> h[3], t[3];
+    if constexpr (MU == 1 && !WRAP) {
+        // y: a shift within the row of 16 lanes fills with zero where the
+        // neighbour leaves the block, so every lane adds
+        proj_spin<MU, -1, SP>(u, l, h);
 #pragma unroll
-    for (int c = 0; c < 12; ++c) q[c] = mk<A>(0, 0);
-    // FP16 fields: clover half 1 stays in flight as FP16 pairs across the
-    // in-block hops and is applied after them, so its L2 latency hides behind
-    // the hops (with FP32 fields the pending loads take twice the registers,
-    // and that form measured slower)
-    constexpr bool LATE = RES::clover_half && RES::links && sizeof(S) == 2;
-    vec2_t<S> c2late[LATE ? 18 : 1];
-    if constexpr (RES::clover) {
-        clover_mac(cl, diag, v, q);
-    } else if constexpr (RES::clover_half) {
-        const vec2_t<S> *cp = clov_g + ((long)b * 36 + 18) * BS + s;
-        // the address is the same at every MR step: hide that, or the loads
-        // are hoisted out of the MR loop and the half is held in registers
-        asm volatile("" : "+v"(cp));
-        if constexpr (LATE) {
+        for (int c = 0; c < 3; ++c) t[c] = row_shift<0x104, A>(h[c]);
+        su3_spin(W, t, h);
+        recon_spin<MU, -1, SP, true>(qu, ql, h, kf);
+        proj_spin<MU, +1, SP>(u, l, h);
+        su3_spin_adj(W, h, t);
 #pragma unroll
-            for (int e = 0; e < 18; ++e)
-                if (clover_reads(RES::sigma, e)) c2late[e] = cp[e * BS];
-            clover_half_mac<A, RES::sigma>(cl, diag, v, q);
-        } else {
-            // half 1's loads are in flight while half 0 (registers) is applied
-            cx<A> c2[18];
-#pragma unroll
-            for (int e = 0; e < 18; ++e)
-                if (clover_reads(RES::sigma, e)) c2[e] = ldc<A>(cp + e * BS);
-            clover_half_mac<A, RES::sigma>(cl, diag, v, q);
-            clover_half_mac<A, RES::sigma>(c2, diag, v + 6, q + 6);
-        }
-    } else {
-#pragma unroll 1
-        for (int k = 0; k < 2; ++k) {
-            cx<A> c2[18];
-            const vec2_t<S> *cp = clov_g + ((long)b * 36 + 18 * k) * BS + s;
-#pragma unroll
-            for (int e = 0; e < 18; ++e) c2[e] = NTC ? ldc_stream<A>(cp + e * BS) : ldc<A>(cp + e * BS);
-            if (k == 0) clover_half_mac<A>(c2, diag, v, q);
-            else clover_half_mac<A>(c2, diag, v + 6, q + 6);
-        }
+        for (int c = 0; c < 3; ++c) h[c] = row_shift<0x114, A>(t[c]);
+        recon_spin<MU, +1, SP, true>(qu, ql, h, kb);
+        return;
     }
-    if constexpr (RES::links) {
-        // links already in registers: no loads to hoist, unroll the
-        // directions.  Across lanes, t alone goes through LDS: its half
-        // spinors are posted first and taken last, so the x, y and z hops
-        // run while the other wavefronts reach the barrier.
-        if constexpr (LANES) {
-            exchange_dir<3, S, A, LANES, 1>(L, g, b, bc, s, Ur[RES::links ? 3 : 0], v, q);
-            exchange_dir<0, S, A, LANES>(L, g, b, bc, s, Ur[0], v, q);
-            exchange_dir<1, S, A, LANES>(L, g, b, bc, s, Ur[RES::links ? 1 : 0], v, q);
-            exchange_dir<2, S, A, LANES>(L, g, b, bc, s, Ur[RES::links ? 2 : 0], v, q);
-            exchange_dir<3, S, A, LANES, 2>(L, g, b, bc, s, Ur[RES::links ? 3 : 0], v, q);
-        } else {
-            exchange_dir<0, S, A, LANES>(L, g, b, bc, s, Ur[0], v, q);
-            exchange_dir<1, S, A, LANES>(L, g, b, bc, s, Ur[RES::links ? 1 : 0], v, q);
-            exchange_dir<2, S, A, LANES>(L, g, b, bc, s, Ur[RES::links ? 2 : 0], v, q);
-            exchange_dir<3, S, A, LANES>(L, g, b, bc, s, Ur[RES::links ? 3 : 0], v, q);
-        }
-        if constexpr (LATE) {
-            cx<A> c2[18];
+    proj_spin<MU, -1, SP>(u, l, h);
 #pragma unroll
-            for (int e = 0; e < 18; ++e)
-                if (clover_reads(RES::sigma, e)) c2[e] = ldc<A>(&c2late[e]);
-            clover_half_mac<A, RES::sigma>(c2, diag, v + 6, q + 6);
-        }
-    } else {
-#pragma unroll 1
-    for (int mu = 0; mu < 4; ++mu) {
-        cx<A> U[9], h[6], t[6];
-        get_link<RES::links, S, A>(Ur, links_g, b, s, mu, U);
-        const int X = mu & 1;
-        proj_m(mu, v, h);
-#pragma unroll
-        for (int c = 0; c < 6; ++c) L.hf[X][c][s] = h[c];
-        proj_p(mu, v, h);
-        su3_mul_adj(U, h, t);
-#pragma unroll
-        for (int c = 0; c < 6; ++c) L.hb[X][c][s] = t[c];
-        __syncthreads();
-        int bn, sn, sign;
-        bool inb;
-        neighbour_rt(g, b, bc, s, mu, +1, bn, sn, sign, inb);
-        if (inb) {
-#pragma unroll
-            for (int c = 0; c < 6; ++c) h[c] = L.hf[X][c][sn];
-            su3_mul(U, h, t);
-            recon_m(mu, q, t, (A)(sign > 0 ? -0.5f : 0.5f));
-        }
-        neighbour_rt(g, b, bc, s, mu, -1, bn, sn, sign, inb);
-        if (inb) {
-#pragma unroll
-            for (int c = 0; c < 6; ++c) t[c] = L.hb[X][c][sn];
-            recon_p(mu, q, t, (A)(sign > 0 ? -0.5f : 0.5f));
-        }
+    for (int c = 0; c < 3; ++c) t[c] = lane_hop<MU, +1, A>(h[c], snf);
+    if (inf) {
+        su3_spin(W, t, h);
+        if (WRAP && wraps) recon_spin<MU, -1, SP, false>(qu, ql, h, kf);
+        else recon_spin<MU, -1, SP, true>(qu, ql, h, kf);
     }
+    proj_spin<MU, +1, SP>(u, l, h);
+    su3_spin_adj(W, h, t);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) h[c] = lane_hop<MU, -1, A>(t[c], snb);
+    if (inb) {
+        if (WRAP && wraps) recon_spin<MU, +1, SP, false>(qu, ql, h, kb);
+        else recon_spin<MU, +1, SP, true>(qu, ql, h, kb);
     }
+}
+template <int MU, bool WRAP, typename A>
+__device__ __forceinline__ void blk_hop(const Geom &g, int b, const int bc[4], int s, const cx<A> W[9],
+                                         const cx<A> u[6], const cx<A> l[6], cx<A> qu[6], cx<A> ql[6])
+{
+    const bool wraps = g.nb[MU] == 1; // uniform
+    int bn, snf, snb, gf, gb;
+    bool inf, inb;
+    neighbour<MU, +1>(g, b, bc, s, bn, snf, gf, inf);
+    neighbour<MU, -1>(g, b, bc, s, bn, snb, gb, inb);
+    if (!WRAP) {
+        inf = ((s >> (2 * MU)) & 3) < BEXT - 1;
+        inb = ((s >> (2 * MU)) & 3) > 0;
+    }
+    blk_hop_spin<MU, 0, WRAP>(W, u, l, qu, ql, inf, inb, snf, snb, wraps, (A)gf, (A)gb);
+    blk_hop_spin<MU, 1, WRAP>(W, u, l, qu, ql, inf, inb, snf, snb, wraps, (A)gf, (A)gb);
+}
+
+// ---- the t direction through LDS
+template <int SP, typename LT, typename A>
+__device__ __forceinline__ void blk_t_post_spin(LT &L, const cx<A> W[9], int s, const cx<A> u[6], const cx<A> l[6])
+{
+    cx<A> h[3], t[3];
+    proj_spin<3, -1, SP>(u, l, h);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) L.tf[3 * SP + c][s] = h[c];
+    proj_spin<3, +1, SP>(u, l, h);
+    su3_spin_adj(W, h, t);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) L.tb[3 * SP + c][s] = t[c];
+}
+template <int SP, bool WRAP, typename LT, typename A>
+__device__ __forceinline__ void blk_t_take_spin(LT &L, const cx<A> W[9], cx<A> qu[6], cx<A> ql[6], bool inf,
+                                                 bool inb, int snf, int snb, bool wraps, A kf, A kb)
+{
+    cx<A> h[3], t[3];
+    if (inf) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) h[c] = L.tf[3 * SP + c][snf];
+        su3_spin(W, h, t);
+        if (WRAP && wraps) recon_spin<3, -1, SP, false>(qu, ql, t, kf);
+        else recon_spin<3, -1, SP, true>(qu, ql, t, kf);
+    }
+    if (inb) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) h[c] = L.tb[3 * SP + c][snb];
+        if (WRAP && wraps) recon_spin<3, +1, SP, false>(qu, ql, h, kb);
+        else recon_spin<3, +1, SP, true>(qu, ql, h, kb);
+    }
+}
+
+template <bool WRAP, typename LT, typename A>
+__device__ __forceinline__ void blk_t_take(LT &L, const Geom &g, int b, const int bc[4], int s, const cx<A> W[9], cx<A> qu[6],
+                                           cx<A> ql[6])
+{
+    const bool wraps = g.nb[3] == 1; // uniform
+    int bn, snf, snb, gf, gb;
+    bool inf, inb;
+    neighbour<3, +1>(g, b, bc, s, bn, snf, gf, inf);
+    neighbour<3, -1>(g, b, bc, s, bn, snb, gb, inb);
+    if (!WRAP) {
+        inf = s < 3 * 64;
+        inb = s >= 64;
+    }
+    blk_t_take_spin<0, WRAP>(L, W, qu, ql, inf, inb, snf, snb, wraps, (A)gf, (A)gb);
+    blk_t_take_spin<1, WRAP>(L, W, qu, ql, inf, inb, snf, snb, wraps, (A)gf, (A)gb);
 }
 
 // ---------------------------------------------------------------------------
@@ -370,56 +304,70 @@ __device__ __forceinline__ int face_index(int s, int mu)
     return lo | ((s >> (2 * mu + 2)) << (2 * mu));
 }
 
-// The same hops computed cooperatively by the workgroup: the 8 faces x 64
-// sites of a 4^4 block are 512 hops, two per thread, with the face (and so
-// mu and the direction) uniform over each wavefront: wavefront w takes face
-// w (mu = w/2) and face w + 4 (mu = 2 + w/2), face 2 mu being the sites with
-// l_mu = 0 (hop from x - mu) and face 2 mu + 1 those with l_mu = 3.  Each
-// hop's transported half spinor, times -1/2 and the boundary sign, goes to
-// FB0 (faces 0-3) or FB1 (faces 4-7) at [component][face mod 4][64], i.e. at
+// The hops that leave a block, computed cooperatively by the workgroup: the
+// 8 faces x 64 sites of a 4^4 block are 512 hops, two per thread, with the
+// face (and so mu and the direction) uniform over each wavefront: wavefront w
+// takes face w (hop j = 0, mu = w/2) and face w + 4 (j = 1, mu = 2 + w/2),
+// face 2 mu being the sites with l_mu = 0 (hop from x - mu) and face 2 mu + 1
+// those with l_mu = 3.  Each hop's transported half spinor, times -1/2 and the
+// boundary sign, goes to FB[j] at [component][face mod 4][64], i.e. at
 // [component][thread]; after the caller's next barrier face_gather adds them
-// to their sites.  Compared with the per-site loop this takes two memory
-// round trips per right-hand side instead of four, and no lane idles.
-template <typename SP, typename SF, typename A>
-__device__ __forceinline__ void face_hops_coop(const Geom &g, int b, const int bc[4], int s, int r, int nrhs,
-                                               const vec2_t<SP> *__restrict__ psi,
-                                               const vec2_t<SF> *__restrict__ links, bool r12, cx<A> *FB0,
-                                               cx<A> *FB1)
+// to their sites.
+struct FaceHop {
+    int mu, dir;  // uniform over the wavefront
+    bool inblk;   // the block spans the direction: the in-block exchange wraps (uniform)
+    int bn, sn;   // the neighbour's block (uniform) and site
+    int lb, ls;   // block and site whose link the hop takes
+    int sign;
+};
+__device__ __forceinline__ FaceHop face_hop(const Geom &g, int b, const int bc[4], int tid, int j)
 {
-    const int w = s >> 6, k = s & 63;
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-        const int f = w + 4 * j;
-        const int mu = f >> 1, dir = (f & 1) ? 1 : -1;
-        if (g.nb[mu] == 1) continue; // uniform: the in-block exchange wraps
-        const int lo = k & ((1 << (2 * mu)) - 1);
-        const int x = lo | ((dir > 0 ? BEXT - 1 : 0) << (2 * mu)) | ((k >> (2 * mu)) << (2 * mu + 2));
-        int bn, sn, sign;
-        bool inb;
-        neighbour_rt(g, b, bc, x, mu, dir, bn, sn, sign, inb);
-        cx<A> p[12], h[6], t[6], U[9];
-        const vec2_t<SP> *pp = psi + ((long)bn * nrhs + r) * 12 * BS + sn;
-#pragma unroll
-        for (int c = 0; c < 12; ++c) p[c] = ldc<A>(pp + c * BS);
-        // the forward hop takes this site's link, the backward one the
-        // neighbour's (both as stored: the factor -1/2 is applied below)
-        const int lb = dir > 0 ? b : bn, ls = dir > 0 ? x : sn;
-        load_link<A>(links + ((long)lb * 4 + mu) * 9 * BS + ls, r12, U);
-        if (dir > 0) {
-            proj_m(mu, p, h);
-            su3_mul(U, h, t);
-        } else {
-            proj_p(mu, p, h);
-            su3_mul_adj(U, h, t);
-        }
-        const A kk = (A)(-0.5f * sign);
-        cx<A> *fb = j == 0 ? FB0 : FB1;
-#pragma unroll
-        for (int c = 0; c < 6; ++c) fb[c * BS + s] = kk * t[c];
+    FaceHop h;
+    const int f = __builtin_amdgcn_readfirstlane(tid >> 6) + 4 * j, k = tid & 63;
+    h.mu = f >> 1;
+    h.dir = (f & 1) ? 1 : -1;
+    // values, not addresses, are selected: an address into the argument block
+    // or bc would put it in scratch memory
+    const int n0 = g.nb[0], n1 = g.nb[1], n2 = g.nb[2], n3 = g.nb[3];
+    const int s0 = g.bstride[0], s1 = g.bstride[1], s2 = g.bstride[2], s3 = g.bstride[3];
+    const int p0 = g.bcs[0], p1 = g.bcs[1], p2 = g.bcs[2], p3 = g.bcs[3];
+    const int c0 = bc[0], c1 = bc[1], c2 = bc[2], c3 = bc[3];
+    const int mu = h.mu;
+    const int nb = mu < 2 ? (mu == 0 ? n0 : n1) : (mu == 2 ? n2 : n3);
+    const int st = mu < 2 ? (mu == 0 ? s0 : s1) : (mu == 2 ? s2 : s3);
+    const int bs = mu < 2 ? (mu == 0 ? p0 : p1) : (mu == 2 ? p2 : p3);
+    const int cm = mu < 2 ? (mu == 0 ? c0 : c1) : (mu == 2 ? c2 : c3);
+    const int lo = k & ((1 << (2 * mu)) - 1), up = (k >> (2 * mu)) << (2 * mu + 2);
+    const int x0 = lo | up, x3 = x0 | ((BEXT - 1) << (2 * mu)); // the face sites with l_mu = 0 and 3
+    const int s = h.dir > 0 ? x3 : x0;
+    h.sn = h.dir > 0 ? x0 : x3;
+    h.inblk = nb == 1;
+    const bool edge = h.dir > 0 ? cm + 1 == nb : cm == 0;
+    h.bn = h.dir > 0 ? (edge ? b - (nb - 1) * st : b + st) : (edge ? b + (nb - 1) * st : b - st);
+    h.sign = edge ? bs : 1;
+    h.lb = h.dir > 0 ? b : h.bn;
+    h.ls = h.dir > 0 ? s : h.sn;
+    return h;
+}
+// One such hop of the spinor p with the link W (as stored) to fb[component].
+template <typename A>
+__device__ __forceinline__ void face_hop_post(const FaceHop &f, const cx<A> p[12], const cx<A> W[9], int tid,
+                                              cx<A> (*fb)[BS])
+{
+    cx<A> h[6], t[6];
+    if (f.dir > 0) {
+        proj_m(f.mu, p, h);
+        su3_mul(W, h, t);
+    } else {
+        proj_p(f.mu, p, h);
+        su3_mul_adj(W, h, t);
     }
+    const A kk = (A)(-0.5f * f.sign);
+#pragma unroll
+    for (int c = 0; c < 6; ++c) fb[c][tid] = kk * t[c];
 }
 
-// q += the face hops of site s from the buffers face_hops_coop wrote.
+// q += the face hops of site s from the buffers FB0, FB1 that face_hop_post wrote.
 template <int MU, typename A>
 __device__ __forceinline__ void face_gather_dir(const Geom &g, int s, const cx<A> *FB0, const cx<A> *FB1,
                                                 cx<A> q[12])

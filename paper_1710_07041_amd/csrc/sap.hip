@@ -370,32 +370,6 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(WAVES))) voi
     }
 }
 
-// Right-hand sides per workgroup.  A workgroup runs its right-hand sides one
-// after another with the block's fields loaded once, so a lattice that fills
-// the chip takes them all in one workgroup; one with fewer blocks of a colour
-// than `slots` (workgroups that run at once) leaves CUs idle unless the
-// right-hand sides are dealt to several workgroups of the block.  The estimate
-// is rounds of workgroups times the work of one, the field loads counting as a
-// quarter of a right-hand side's visit (32^3x64, FP32: 307 us a sweep with
-// one, 246 us each with twelve).  A split has to promise 5%.  Measured, twelve
-// cycles in FP32: 16^4 with three right-hand sides 1835 -> 873 us a call
-// (three workgroups a block), the 16^3x32 solve with three 14.0 -> 12.0 ms
-// (two and one); one workgroup a block stays where the blocks fill the chip.
-int rhs_per_group(int nblk, int nrhs, int slots)
-{
-    int best = nrhs;
-    double cost = 0;
-    for (int rpg = nrhs; rpg >= 1; --rpg) {
-        const long wgs = (long)nblk * ((nrhs + rpg - 1) / rpg);
-        const double c = (double)((wgs + slots - 1) / slots) * (rpg + 0.25);
-        if (rpg == nrhs || c < 0.95 * cost) {
-            best = rpg;
-            cost = c;
-        }
-    }
-    return best;
-}
-
 // Algorithmic traffic of one colour sweep: links + clover once (72 reals per
 // site each, also when compressed: the method's volume), eta or the carried
 // residual, psi (read only when nonzero), psi written and, in the plain form,

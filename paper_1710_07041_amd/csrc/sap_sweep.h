@@ -41,167 +41,6 @@ template <typename S, typename A, bool PL> struct SweepLds {
     A red[4][4];
 };
 
-// ---- one spin (SP = 0, 1) of the projections, SG = -1: (1 - g), +1: (1 + g)
-// h = u_SP + SG (A l)_SP with A_k = -i sigma_k, A_t = 1
-template <int MU, int SG, int SP, typename A>
-__device__ __forceinline__ void proj_spin(const cx<A> u[6], const cx<A> l[6], cx<A> h[3])
-{
-    constexpr int SL = MU < 2 ? 1 - SP : SP; // the lower spin that A mixes in
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-        const cx<A> a = u[3 * SP + c], x = l[3 * SL + c];
-        // (A l): x: -i l1, -i l0; y: -l1, l0; z: -i l0, i l1; t: l0, l1
-        if (MU == 0) h[c] = SG > 0 ? a + tmi(x) : a + ti(x);
-        if (MU == 1) h[c] = (SG > 0) == (SP == 0) ? a - x : a + x;
-        if (MU == 2) h[c] = (SG > 0) == (SP == 0) ? a + tmi(x) : a + ti(x);
-        if (MU == 3) h[c] = SG > 0 ? a + x : a - x;
-    }
-}
-// (u, l) += k (t, SG A^+ t) for the spin SP of t (k = 1 when KONE)
-template <int MU, int SG, int SP, bool KONE, typename A>
-__device__ __forceinline__ void recon_spin(cx<A> u[6], cx<A> l[6], const cx<A> t[3], A k)
-{
-    constexpr int SL = MU < 2 ? 1 - SP : SP;
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-        const cx<A> x = KONE ? t[c] : k * t[c];
-        u[3 * SP + c] = u[3 * SP + c] + x;
-        cx<A> &y = l[3 * SL + c];
-        // A^+ t: x: i t1, i t0 on l0, l1; y: t1, -t0; z: i t0, -i t1; t: t0, t1
-        if (MU == 0) y = y + (SG > 0 ? ti(x) : tmi(x));
-        if (MU == 1) y = (SG > 0) == (SP == 1) ? y + x : y - x;
-        if (MU == 2) y = y + ((SG > 0) == (SP == 0) ? ti(x) : tmi(x));
-        if (MU == 3) y = SG > 0 ? y + x : y - x;
-    }
-}
-// t = W h and t = W^+ h for one spin
-template <typename A> __device__ __forceinline__ void su3_spin(const cx<A> W[9], const cx<A> h[3], cx<A> t[3])
-{
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        cx<A> acc = W[a * 3] * h[0];
-        cmac(acc, W[a * 3 + 1], h[1]);
-        cmac(acc, W[a * 3 + 2], h[2]);
-        t[a] = acc;
-    }
-}
-template <typename A> __device__ __forceinline__ void su3_spin_adj(const cx<A> W[9], const cx<A> h[3], cx<A> t[3])
-{
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        cx<A> acc = conjx(W[a]) * h[0];
-        cmacc(acc, W[3 + a], h[1]);
-        cmacc(acc, W[6 + a], h[2]);
-        t[a] = acc;
-    }
-}
-// row_shl:4 (0x104: lane i reads lane i + 4 of its row) and row_shr:4 (0x114),
-// zero from outside the row
-template <int CTRL> __device__ __forceinline__ int shift_mov(int v)
-{
-    return __builtin_amdgcn_mov_dpp(v, CTRL, 0xf, 0xf, true);
-}
-template <int CTRL, typename A> __device__ __forceinline__ cx<A> row_shift(const cx<A> &v)
-{
-    if constexpr (sizeof(A) == 4) {
-        return mk<A>(__int_as_float(shift_mov<CTRL>(__float_as_int(v.re))), __int_as_float(shift_mov<CTRL>(__float_as_int(v.im))));
-    } else {
-        const long long r = __double_as_longlong(v.re), i = __double_as_longlong(v.im);
-        const int r0 = shift_mov<CTRL>((int)r), r1 = shift_mov<CTRL>((int)(r >> 32));
-        const int i0 = shift_mov<CTRL>((int)i), i1 = shift_mov<CTRL>((int)(i >> 32));
-        return mk<A>(__longlong_as_double(((long long)r1 << 32) | (unsigned)r0),
-                     __longlong_as_double(((long long)i1 << 32) | (unsigned)i0));
-    }
-}
-
-// ---- in-block hops of direction MU across the lanes of a wavefront
-template <int MU, int SP, bool WRAP, typename A>
-__device__ __forceinline__ void blk_hop_spin(const cx<A> W[9], const cx<A> u[6], const cx<A> l[6], cx<A> qu[6],
-                                              cx<A> ql[6], bool inf, bool inb, int snf, int snb, bool wraps, A kf, A kb)
-{
-    cx<A> h[3], t[3];
-    if constexpr (MU == 1 && !WRAP) {
-        // y: a shift within the row of 16 lanes fills with zero where the
-        // neighbour leaves the block, so every lane adds
-        proj_spin<MU, -1, SP>(u, l, h);
-#pragma unroll
-        for (int c = 0; c < 3; ++c) t[c] = row_shift<0x104, A>(h[c]);
-        su3_spin(W, t, h);
-        recon_spin<MU, -1, SP, true>(qu, ql, h, kf);
-        proj_spin<MU, +1, SP>(u, l, h);
-        su3_spin_adj(W, h, t);
-#pragma unroll
-        for (int c = 0; c < 3; ++c) h[c] = row_shift<0x114, A>(t[c]);
-        recon_spin<MU, +1, SP, true>(qu, ql, h, kb);
-        return;
-    }
-    proj_spin<MU, -1, SP>(u, l, h);
-#pragma unroll
-    for (int c = 0; c < 3; ++c) t[c] = lane_hop<MU, +1, A>(h[c], snf);
-    if (inf) {
-        su3_spin(W, t, h);
-        if (WRAP && wraps) recon_spin<MU, -1, SP, false>(qu, ql, h, kf);
-        else recon_spin<MU, -1, SP, true>(qu, ql, h, kf);
-    }
-    proj_spin<MU, +1, SP>(u, l, h);
-    su3_spin_adj(W, h, t);
-#pragma unroll
-    for (int c = 0; c < 3; ++c) h[c] = lane_hop<MU, -1, A>(t[c], snb);
-    if (inb) {
-        if (WRAP && wraps) recon_spin<MU, +1, SP, false>(qu, ql, h, kb);
-        else recon_spin<MU, +1, SP, true>(qu, ql, h, kb);
-    }
-}
-template <int MU, bool WRAP, typename A>
-__device__ __forceinline__ void blk_hop(const Geom &g, int b, const int bc[4], int s, const cx<A> W[9],
-                                         const cx<A> u[6], const cx<A> l[6], cx<A> qu[6], cx<A> ql[6])
-{
-    const bool wraps = g.nb[MU] == 1; // uniform
-    int bn, snf, snb, gf, gb;
-    bool inf, inb;
-    neighbour<MU, +1>(g, b, bc, s, bn, snf, gf, inf);
-    neighbour<MU, -1>(g, b, bc, s, bn, snb, gb, inb);
-    if (!WRAP) {
-        inf = ((s >> (2 * MU)) & 3) < BEXT - 1;
-        inb = ((s >> (2 * MU)) & 3) > 0;
-    }
-    blk_hop_spin<MU, 0, WRAP>(W, u, l, qu, ql, inf, inb, snf, snb, wraps, (A)gf, (A)gb);
-    blk_hop_spin<MU, 1, WRAP>(W, u, l, qu, ql, inf, inb, snf, snb, wraps, (A)gf, (A)gb);
-}
-
-// ---- the t direction through LDS
-template <int SP, typename LT, typename A>
-__device__ __forceinline__ void blk_t_post_spin(LT &L, const cx<A> W[9], int s, const cx<A> u[6], const cx<A> l[6])
-{
-    cx<A> h[3], t[3];
-    proj_spin<3, -1, SP>(u, l, h);
-#pragma unroll
-    for (int c = 0; c < 3; ++c) L.tf[3 * SP + c][s] = h[c];
-    proj_spin<3, +1, SP>(u, l, h);
-    su3_spin_adj(W, h, t);
-#pragma unroll
-    for (int c = 0; c < 3; ++c) L.tb[3 * SP + c][s] = t[c];
-}
-template <int SP, bool WRAP, typename LT, typename A>
-__device__ __forceinline__ void blk_t_take_spin(LT &L, const cx<A> W[9], cx<A> qu[6], cx<A> ql[6], bool inf,
-                                                 bool inb, int snf, int snb, bool wraps, A kf, A kb)
-{
-    cx<A> h[3], t[3];
-    if (inf) {
-#pragma unroll
-        for (int c = 0; c < 3; ++c) h[c] = L.tf[3 * SP + c][snf];
-        su3_spin(W, h, t);
-        if (WRAP && wraps) recon_spin<3, -1, SP, false>(qu, ql, t, kf);
-        else recon_spin<3, -1, SP, true>(qu, ql, t, kf);
-    }
-    if (inb) {
-#pragma unroll
-        for (int c = 0; c < 3; ++c) h[c] = L.tb[3 * SP + c][snb];
-        if (WRAP && wraps) recon_spin<3, +1, SP, false>(qu, ql, h, kb);
-        else recon_spin<3, +1, SP, true>(qu, ql, h, kb);
-    }
-}
-
 // ---- faces of direction MU (layout and contents: block_ops.h)
 template <int MU, typename S, typename A>
 __device__ __forceinline__ void blk_face_load(const Geom &g, int b, const int bc[4], int s, int r, int nrhs,
@@ -403,15 +242,6 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(WAVES))) voi
         // MR on D_BB: delta += alpha r, r -= alpha q
         int it = 0;
         for (; it < a.nmr; ++it) {
-            const bool wraps = a.g.nb[3] == 1; // uniform
-            int bn, snf, snb, gf, gb;
-            bool inf, inb;
-            neighbour<3, +1>(a.g, b, bc, s, bn, snf, gf, inf);
-            neighbour<3, -1>(a.g, b, bc, s, bn, snb, gb, inb);
-            if (!WRAP) {
-                inf = s < 3 * 64;
-                inb = s >= 64;
-            }
 #pragma unroll
             for (int c = 0; c < 12; ++c) q[c] = mk<A>(0, 0);
             blk_t_post_spin<0>(L, U[3], s, rr, rr + 6);
@@ -444,8 +274,7 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(WAVES))) voi
             blk_hop<1, WRAP>(a.g, b, bc, s, U[1], rr, rr + 6, q, q + 6);
             blk_hop<2, WRAP>(a.g, b, bc, s, U[2], rr, rr + 6, q, q + 6);
             __syncthreads();
-            blk_t_take_spin<0, WRAP>(L, U[3], q, q + 6, inf, inb, snf, snb, wraps, (A)gf, (A)gb);
-            blk_t_take_spin<1, WRAP>(L, U[3], q, q + 6, inf, inb, snf, snb, wraps, (A)gf, (A)gb);
+            blk_t_take<WRAP>(L, a.g, b, bc, s, U[3], q, q + 6);
             if constexpr (LATE) {
                 cx<A> c2[18];
 #pragma unroll
