@@ -175,10 +175,15 @@ template <int CTRL, typename A> __device__ __forceinline__ cx<A> row_shift(const
     }
 }
 
-// ---- in-block hops of direction MU across the lanes of a wavefront
+// ---- in-block hops of direction MU across the lanes of a wavefront.  With
+// WRAP every hop is multiplied by its sign (one unless it wraps): a branch on
+// whether the direction wraps saved those multiplications and made the code of
+// an MR step twice as long, which cost more (4x16^3, FP32, eleven cycles of
+// three steps: 501 -> 478 us; FP64 691 -> 658; 4x24^2x48 with twelve right-hand
+// sides 2796 -> 2719; the operator 10.0 -> 9.5).
 template <int MU, int SP, bool WRAP, typename A>
 __device__ __forceinline__ void blk_hop_spin(const cx<A> W[9], const cx<A> u[6], const cx<A> l[6], cx<A> qu[6],
-                                              cx<A> ql[6], bool inf, bool inb, int snf, int snb, bool wraps, A kf, A kb)
+                                              cx<A> ql[6], bool inf, bool inb, int snf, int snb, A kf, A kb)
 {
     cx<A> h[3], t[3];
     if constexpr (MU == 1 && !WRAP) {
@@ -201,23 +206,20 @@ __device__ __forceinline__ void blk_hop_spin(const cx<A> W[9], const cx<A> u[6],
     for (int c = 0; c < 3; ++c) t[c] = lane_hop<MU, +1, A>(h[c], snf);
     if (inf) {
         su3_spin(W, t, h);
-        if (WRAP && wraps) recon_spin<MU, -1, SP, false>(qu, ql, h, kf);
-        else recon_spin<MU, -1, SP, true>(qu, ql, h, kf);
+        recon_spin<MU, -1, SP, !WRAP>(qu, ql, h, kf);
     }
     proj_spin<MU, +1, SP>(u, l, h);
     su3_spin_adj(W, h, t);
 #pragma unroll
     for (int c = 0; c < 3; ++c) h[c] = lane_hop<MU, -1, A>(t[c], snb);
     if (inb) {
-        if (WRAP && wraps) recon_spin<MU, +1, SP, false>(qu, ql, h, kb);
-        else recon_spin<MU, +1, SP, true>(qu, ql, h, kb);
+        recon_spin<MU, +1, SP, !WRAP>(qu, ql, h, kb);
     }
 }
 template <int MU, bool WRAP, typename A>
 __device__ __forceinline__ void blk_hop(const Geom &g, int b, const int bc[4], int s, const cx<A> W[9],
                                          const cx<A> u[6], const cx<A> l[6], cx<A> qu[6], cx<A> ql[6])
 {
-    const bool wraps = g.nb[MU] == 1; // uniform
     int bn, snf, snb, gf, gb;
     bool inf, inb;
     neighbour<MU, +1>(g, b, bc, s, bn, snf, gf, inf);
@@ -226,8 +228,8 @@ __device__ __forceinline__ void blk_hop(const Geom &g, int b, const int bc[4], i
         inf = ((s >> (2 * MU)) & 3) < BEXT - 1;
         inb = ((s >> (2 * MU)) & 3) > 0;
     }
-    blk_hop_spin<MU, 0, WRAP>(W, u, l, qu, ql, inf, inb, snf, snb, wraps, (A)gf, (A)gb);
-    blk_hop_spin<MU, 1, WRAP>(W, u, l, qu, ql, inf, inb, snf, snb, wraps, (A)gf, (A)gb);
+    blk_hop_spin<MU, 0, WRAP>(W, u, l, qu, ql, inf, inb, snf, snb, (A)gf, (A)gb);
+    blk_hop_spin<MU, 1, WRAP>(W, u, l, qu, ql, inf, inb, snf, snb, (A)gf, (A)gb);
 }
 
 // ---- the t direction through LDS
@@ -245,21 +247,19 @@ __device__ __forceinline__ void blk_t_post_spin(LT &L, const cx<A> W[9], int s, 
 }
 template <int SP, bool WRAP, typename LT, typename A>
 __device__ __forceinline__ void blk_t_take_spin(LT &L, const cx<A> W[9], cx<A> qu[6], cx<A> ql[6], bool inf,
-                                                 bool inb, int snf, int snb, bool wraps, A kf, A kb)
+                                                 bool inb, int snf, int snb, A kf, A kb)
 {
     cx<A> h[3], t[3];
     if (inf) {
 #pragma unroll
         for (int c = 0; c < 3; ++c) h[c] = L.tf[3 * SP + c][snf];
         su3_spin(W, h, t);
-        if (WRAP && wraps) recon_spin<3, -1, SP, false>(qu, ql, t, kf);
-        else recon_spin<3, -1, SP, true>(qu, ql, t, kf);
+        recon_spin<3, -1, SP, !WRAP>(qu, ql, t, kf);
     }
     if (inb) {
 #pragma unroll
         for (int c = 0; c < 3; ++c) h[c] = L.tb[3 * SP + c][snb];
-        if (WRAP && wraps) recon_spin<3, +1, SP, false>(qu, ql, h, kb);
-        else recon_spin<3, +1, SP, true>(qu, ql, h, kb);
+        recon_spin<3, +1, SP, !WRAP>(qu, ql, h, kb);
     }
 }
 
@@ -267,7 +267,6 @@ template <bool WRAP, typename LT, typename A>
 __device__ __forceinline__ void blk_t_take(LT &L, const Geom &g, int b, const int bc[4], int s, const cx<A> W[9], cx<A> qu[6],
                                            cx<A> ql[6])
 {
-    const bool wraps = g.nb[3] == 1; // uniform
     int bn, snf, snb, gf, gb;
     bool inf, inb;
     neighbour<3, +1>(g, b, bc, s, bn, snf, gf, inf);
@@ -276,8 +275,8 @@ __device__ __forceinline__ void blk_t_take(LT &L, const Geom &g, int b, const in
         inf = s < 3 * 64;
         inb = s >= 64;
     }
-    blk_t_take_spin<0, WRAP>(L, W, qu, ql, inf, inb, snf, snb, wraps, (A)gf, (A)gb);
-    blk_t_take_spin<1, WRAP>(L, W, qu, ql, inf, inb, snf, snb, wraps, (A)gf, (A)gb);
+    blk_t_take_spin<0, WRAP>(L, W, qu, ql, inf, inb, snf, snb, (A)gf, (A)gb);
+    blk_t_take_spin<1, WRAP>(L, W, qu, ql, inf, inb, snf, snb, (A)gf, (A)gb);
 }
 
 // ---------------------------------------------------------------------------
