@@ -1,0 +1,50 @@
+"""The coarse correction's kernels at the counts where their loops end: one,
+an odd number of and the most test vectors, and groups of right-hand sides
+that are whole, ragged and single, against the oracle on the device's own
+interpolation and coarse operator (the bounds of test_gpu_amg)."""
+import numpy as np
+import pytest
+
+from gpu_util import Lattice, rel, to_dev, to_host
+from oracle import amg
+from paper_1710_07041_amd import synth
+from test_gpu_amg import oracle_P
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", params=[1, 3, 12, 16])
+def lat(request):
+    """4x8x8x8: a direction with a single block and three with two."""
+    from paper_1710_07041_amd import ddsap
+    n = request.param
+    lat = Lattice((4, 8, 8, 8), eps=0.3, seed=3, oracle_clover=False)
+    p = ddsap.default_amg_params()
+    p.nvec, p.setup_iters, p.setup_ncy, p.setup_nmr, p.setup_prec, p.adapt = n, 1, 2, 4, ddsap.DD_F64, 0
+    lat.ctx.amg_setup(-0.2, to_dev(synth.gaussian_spinor(lat.dims, nrhs=n, seed=80)), p)
+    lat.P = oracle_P(lat.ctx.amg_interpolation())
+    return lat
+
+
+@pytest.mark.parametrize("nrhs", [1, 2, 3, 4, 7])
+@pytest.mark.parametrize("prec,tol", [("f64", 1e-14), ("f32", 2e-6)])
+def test_transfer(lat, prec, tol, nrhs):
+    import torch
+    eta = synth.gaussian_spinor(lat.dims, nrhs=nrhs, seed=81)
+    x = to_dev(eta)
+    xb = lat.ctx.empty_blocked(prec, nrhs)
+    lat.ctx.pack(x, xb, prec, nrhs)
+    xc = torch.empty((nrhs, lat.ctx.amg_coarse_size()), dtype=torch.complex128, device="cuda")
+    lat.ctx.amg_restrict(xb, xc, prec, nrhs)
+    got = to_host(xc)
+    rng = np.random.default_rng(82)
+    yc = rng.standard_normal(got.shape) + 1j * rng.standard_normal(got.shape)
+    yb = lat.ctx.empty_blocked(prec, nrhs)
+    lat.ctx.amg_prolong(to_dev(yc), yb, prec, nrhs)
+    y = torch.empty_like(x)
+    lat.ctx.unpack(yb, y, prec, nrhs)
+    lat.ctx.synchronize()
+    fine = to_host(y)
+    for r in range(nrhs):
+        assert rel(got[r], amg.restrict(lat.dims, (4, 4, 4, 4), lat.P, eta[r]).reshape(-1)) < tol
+        assert rel(fine[r], amg.prolong(lat.dims, (4, 4, 4, 4), lat.P, yc[r])) < tol
