@@ -467,13 +467,6 @@ __device__ __forceinline__ int cnbr(const Geom &g, int b, const int bc[4], int d
     return bc[mu] + 1 == g.nb[mu] ? b - (g.nb[mu] - 1) * g.bstride[mu] : b + g.bstride[mu];
 }
 
-// One thread per (coarse site, row): y_r = (D_c + m0_r) x_r for the slots
-// (slot r reads x + r * xs and writes y + r * ys; [nblocks][2N] each), the
-// FP16 copy of D_c with FP64 vectors and accumulation.
-// The nine 2N x 2N blocks of a row are read column by column, so the 2N
-// threads of a coarse site read consecutive entries; x of the source block
-// is the same for all of them.
-struct GState;
 
 // Per-slot state of the device GMRES (k <= CK steps).
 struct GState {
@@ -706,40 +699,66 @@ __global__ __launch_bounds__(CTPB) void k_cg_next(double2 *__restrict__ V, const
     }
 }
 
+// y_r = (D_c + m0_r) x_r for the slots (slot r reads x + r * xs and writes
+// y + r * ys; [nblocks][2N] each), the FP16 copy of D_c with FP64 vectors and
+// accumulation.  A workgroup takes CS coarse sites, a thread one row of one of a
+// site's nine 2N x 2N blocks, read column by column, so the 2N threads of a
+// block read consecutive entries; the source vectors wait in LDS, and the nine
+// partial sums of a row are added in order through LDS.
+// Bound by latency on small lattices and by the 576-entry blocks coming from
+// the cache on large ones.  One thread per row, all nine blocks in turn and the
+// source entries loaded by every lane, took 16.4 us a launch at 24^3x48 (N = 12)
+// where this takes 12, and 15.9 us at 16^4 where this takes 6.2; the whole
+// preconditioner 2.91 -> 2.84 ms, 1.16 -> 1.00 ms (8^4: 1.05 -> 0.95).
+template <int N2> constexpr int CS = 256 / (9 * N2) > 0 ? 256 / (9 * N2) : 1; // sites per workgroup
+template <int N2> constexpr int CT = (9 * N2 * CS<N2> + 63) / 64 * 64;        // threads
 // N2 = 2N is a compile-time constant so that the loads of a block row are
 // issued together (a run-time loop waits on each pair of loads in turn)
 template <int N2>
-__global__ __launch_bounds__(CTPB) void k_coarse_apply(const __half2 *__restrict__ Ah, const double2 *__restrict__ x,
-                                                       long xs, double2 *__restrict__ y, long ys,
-                                                       const GState *__restrict__ st, CArgs a)
+__global__ __launch_bounds__(CT<N2>) void k_coarse_apply(const __half2 *__restrict__ Ah, const double2 *__restrict__ x,
+                                                         long xs, double2 *__restrict__ y, long ys,
+                                                         const GState *__restrict__ st, CArgs a)
 {
-    const int r = blockIdx.y;
+    __shared__ double2 X[CS<N2> * 9][N2]; // source vectors, then the partial sums
+    const int r = blockIdx.y, t = threadIdx.x;
     if ((a.active && !a.active[r]) || (st && st[r].closed)) return;
-    const double m0 = a.m0_dev[r];
-    const long nrow = (long)a.nblocks * N2;
+    const int sd = t / N2, k = t - sd * N2; // block (site, direction) of the workgroup, row
+    const int site = sd / 9, d = sd - 9 * site;
+    const int b = blockIdx.x * CS<N2> + site;
+    const bool on = site < CS<N2> && b < a.nblocks;
     const double2 *xr = x + (long)r * xs;
-    for (long t = (long)blockIdx.x * CTPB + threadIdx.x; t < nrow; t += (long)gridDim.x * CTPB) {
-        const int b = (int)(t / N2), k = (int)(t % N2);
+    cx<double> acc = mk<double>(0, 0);
+    __half2 A[N2];
+    if (on) {
+        const __half2 *Ac = Ah + ((long)b * 9 + d) * N2 * N2 + k;
+#pragma unroll
+        for (int kp = 0; kp < N2; ++kp) A[kp] = Ac[kp * N2];
         int bc[4];
         block_coords(a.g, b, bc);
-        cx<double> acc = m0 * ldc<double>(xr + t);
-#pragma unroll 1
-        for (int d = 0; d < 9; ++d) {
-            const int src = d == 0 ? b : cnbr(a.g, b, bc, d);
-            const __half2 *Ac = Ah + ((long)b * 9 + d) * N2 * N2 + k;
-            const double2 *xsrc = xr + (long)src * N2;
-#pragma unroll 16
-            for (int kp = 0; kp < N2; ++kp) cmac(acc, ldc<double>(Ac + (long)kp * N2), ldc<double>(xsrc + kp));
-        }
-        stc(y + (long)r * ys + t, acc);
+        const int src = d == 0 ? b : cnbr(a.g, b, bc, d);
+        X[sd][k] = xr[(long)src * N2 + k];
+    }
+    __syncthreads();
+    if (on) {
+        if (d == 0) acc = a.m0_dev[r] * ldc<double>(&X[sd][k]);
+#pragma unroll
+        for (int kp = 0; kp < N2; ++kp) cmac(acc, ldc<double>(&A[kp]), ldc<double>(&X[sd][kp]));
+    }
+    __syncthreads();
+    if (on) stc(&X[sd][k], acc);
+    __syncthreads();
+    if (on && d == 0) {
+#pragma unroll
+        for (int e = 1; e < 9; ++e) acc = acc + ldc<double>(&X[sd + e][k]);
+        stc(y + (long)r * ys + (long)b * N2 + k, acc);
     }
 }
 
-void coarse_apply(int N, dim3 grid, hipStream_t st, const __half2 *Ah, const double2 *x, long xs, double2 *y, long ys,
+void coarse_apply(const dd_ctx *ctx, int W, const __half2 *Ah, const double2 *x, long xs, double2 *y, long ys,
                   const GState *S, const CArgs &a)
 {
-    switch (N) {
-#define DD_CA(n) case n: k_coarse_apply<2 * n><<<grid, CTPB, 0, st>>>(Ah, x, xs, y, ys, S, a); break;
+    switch (a.N) {
+#define DD_CA(n) case n: k_coarse_apply<2 * n><<<dim3((a.nblocks + CS<2 * n> - 1) / CS<2 * n>, W), CT<2 * n>, 0, ctx->stream>>>(Ah, x, xs, y, ys, S, a); break;
         DD_CA(1) DD_CA(2) DD_CA(3) DD_CA(4) DD_CA(5) DD_CA(6) DD_CA(7) DD_CA(8)
         DD_CA(9) DD_CA(10) DD_CA(11) DD_CA(12) DD_CA(13) DD_CA(14) DD_CA(15) DD_CA(16)
 #undef DD_CA
@@ -945,14 +964,11 @@ Status coarse_gmres(dd_ctx *ctx, AmgWork &wk, int W, int k, const double *m0_dev
     const long nrow = (long)ncoarse(ctx);
     double2 *V = wk.V.as<double2>(), *w = wk.w.as<double2>();
     GState *S = wk.st.as<GState>();
-    // the operator: one row per thread (latency-bound at fewer); the
-    // reductions: CG workgroups, one partial sum each
-    const dim3 agrid((unsigned)std::min<long>((nrow + CTPB - 1) / CTPB, 8192), W);
     k_cg_norm<<<grid, CTPB, 0, st>>>(wk.xb.as<double2>(), wk.partN.as<double2>(), a);
     k_cg_init<<<grid, CTPB, 0, st>>>(wk.xb.as<double2>(), V, wk.partN.as<double2>(), S, a, kmax);
     for (int j = 0; j < k; ++j) {
         // w = (D_c + m0) v_j
-        coarse_apply(A.N, agrid, st, A.Ah.as<__half2>(), V + (long)j * nrow, (long)(kmax + 1) * nrow, w, nrow, S, a);
+        coarse_apply(ctx, W, A.Ah.as<__half2>(), V + (long)j * nrow, (long)(kmax + 1) * nrow, w, nrow, S, a);
         k_cg_dots<<<grid, CTPB, 0, st>>>(V, w, wk.partA.as<double2>(), S, a, kmax, j);
         k_cg_orth<<<grid, CTPB, 0, st>>>(V, w, wk.partA.as<double2>(), wk.partB.as<double2>(), S, a, kmax, j, 1);
         k_cg_orth<<<grid, CTPB, 0, st>>>(V, w, wk.partB.as<double2>(), wk.partN.as<double2>(), S, a, kmax, j, 2);
@@ -1153,8 +1169,7 @@ Status amg_standalone(dd_ctx *ctx, int op, const double *m0, int nrhs, const voi
             amg_prolong<float>(nb, nrhs, ctx->stream, in, A.Pf, out, nullptr, nullptr, N);
         break;
     case 2: // coarse apply
-        coarse_apply(N, dim3((unsigned)std::min<long>(((long)ncoarse(ctx) + CTPB - 1) / CTPB, 8192), nrhs),
-                     ctx->stream, A.Ah.as<__half2>(), static_cast<const double2 *>(in), (long)ncoarse(ctx),
+        coarse_apply(ctx, nrhs, A.Ah.as<__half2>(), static_cast<const double2 *>(in), (long)ncoarse(ctx),
                      static_cast<double2 *>(out), (long)ncoarse(ctx), nullptr, a);
         break;
     case 3: // coarse solve with k steps

@@ -8,7 +8,7 @@ import pytest
 from gpu_util import Lattice, rel, to_dev, to_host
 from oracle import amg
 from paper_1710_07041_amd import synth
-from test_gpu_amg import oracle_P
+from test_gpu_amg import dense_from_blocks, oracle_P
 
 pytestmark = pytest.mark.gpu
 
@@ -48,3 +48,24 @@ def test_transfer(lat, prec, tol, nrhs):
     for r in range(nrhs):
         assert rel(got[r], amg.restrict(lat.dims, (4, 4, 4, 4), lat.P, eta[r]).reshape(-1)) < tol
         assert rel(fine[r], amg.prolong(lat.dims, (4, 4, 4, 4), lat.P, yc[r])) < tol
+
+
+def f16(z):
+    """The device's copy of D_c: each real part rounded once, FP64 to FP16."""
+    r = lambda a: a.astype(np.float16).astype(np.float64)
+    return r(z.real) + 1j * r(z.imag)
+
+
+@pytest.mark.parametrize("nrhs", [1, 3])
+def test_coarse_apply(lat, nrhs):
+    """The bound of test_gpu_amg: FP64 sums over the FP16 copy."""
+    import torch
+    Dc = dense_from_blocks(lat.dims, f16(lat.ctx.amg_coarse_operator()))
+    rng = np.random.default_rng(83)
+    x = rng.standard_normal((nrhs, Dc.shape[0])) + 1j * rng.standard_normal((nrhs, Dc.shape[0]))
+    m0 = np.linspace(-0.2, 0.1, nrhs)
+    y = torch.empty((nrhs, Dc.shape[0]), dtype=torch.complex128, device="cuda")
+    lat.ctx.amg_coarse_apply(m0, to_dev(x), y, nrhs)
+    lat.ctx.synchronize()
+    for r in range(nrhs):
+        assert rel(to_host(y)[r], Dc @ x[r] + m0[r] * x[r]) < 1e-13
