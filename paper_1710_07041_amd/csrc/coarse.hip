@@ -480,7 +480,7 @@ struct GState {
 };
 
 // The totals of values 0..count-1 over the CG group partials
-// (part[(r * CG + group) * nvals + v]), computed by the whole workgroup --
+// (part[(r * nvals + v) * CG + group]), computed by the whole workgroup --
 // wavefront w takes values w, w + 4, ...; each lane adds CG / 64 partials,
 // then a fixed-order DPP sum -- into out[] (shared).  Every workgroup gets
 // the same totals.  Ends with a barrier.
@@ -490,17 +490,57 @@ __device__ __forceinline__ void group_totals(const double2 *__restrict__ part, i
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     for (int v = wave; v < count; v += CTPB / 64) {
         double re = 0, im = 0;
+        double2 x[CG / 64];
+#pragma unroll
+        for (int q = 0; q < CG / 64; ++q) x[q] = part[((long)r * nvals + v) * CG + q * 64 + lane];
 #pragma unroll
         for (int q = 0; q < CG / 64; ++q) {
-            const double2 x = part[((long)r * CG + q * 64 + lane) * nvals + v];
-            re += x.x;
-            im += x.y;
+            re += x[q].x;
+            im += x[q].y;
         }
         re = wave_sum(re);
         im = wave_sum(im);
         if (lane == 63) out[v] = make_double2(re, im);
     }
     __syncthreads();
+}
+
+// The partial dots <v_i, w>, i <= j, of this workgroup's rows of w, four
+// vectors at a time (their loads and sums overlap).
+__device__ __forceinline__ void group_dots(Red &R, const double2 *__restrict__ Vr, const double2 *w, long nrow, int j,
+                                           double2 *__restrict__ part, int r, int nvals)
+{
+    const int s = threadIdx.x, lane = s & 63, wave = s >> 6;
+    for (int i0 = 0; i0 <= j; i0 += 4) {
+        double re[4] = {0, 0, 0, 0}, im[4] = {0, 0, 0, 0};
+        for (long t = (long)blockIdx.x * CTPB + s; t < nrow; t += (long)gridDim.x * CTPB) {
+            const double2 x = w[t];
+            double2 v[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) v[u] = Vr[(long)min(i0 + u, j) * nrow + t];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                re[u] += v[u].x * x.x + v[u].y * x.y;
+                im[u] += v[u].x * x.y - v[u].y * x.x;
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            re[u] = wave_sum(re[u]);
+            im[u] = wave_sum(im[u]);
+        }
+        if (lane == 63) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                if (i0 + u <= j) {
+                    R.v[wave][i0 + u][0] = re[u];
+                    R.v[wave][i0 + u][1] = im[u];
+                }
+            }
+        }
+    }
+    __syncthreads();
+    if (s <= j) stc(part + ((long)r * nvals + s) * CG + blockIdx.x, wave_get(R, s));
 }
 
 // |b|^2 partials (stage 0 of the solve)
@@ -550,89 +590,6 @@ __global__ __launch_bounds__(CTPB) void k_cg_init(const double2 *__restrict__ bv
     }
 }
 
-// dots <v_i, w> for i <= j: partials per group
-__global__ __launch_bounds__(CTPB) void k_cg_dots(const double2 *__restrict__ V, const double2 *__restrict__ w,
-                                                  double2 *__restrict__ part, const GState *__restrict__ st, CArgs a,
-                                                  int kmax, int j)
-{
-    __shared__ Red R;
-    const int r = blockIdx.y, s = threadIdx.x;
-    if ((a.active && !a.active[r]) || st[r].closed) return;
-    const long nrow = (long)a.nblocks * 2 * a.N;
-    const double2 *Vr = V + (long)r * (kmax + 1) * nrow;
-    for (int i0 = 0; i0 <= j; i0 += 2 * NMAX) {
-        const int ni = min(2 * NMAX, j + 1 - i0);
-        for (int i = 0; i < ni; ++i) {
-            double re = 0, im = 0;
-            for (long t = (long)blockIdx.x * CTPB + s; t < nrow; t += (long)gridDim.x * CTPB) {
-                const double2 v = Vr[(long)(i0 + i) * nrow + t], x = w[(long)r * nrow + t];
-                re += v.x * x.x + v.y * x.y;
-                im += v.x * x.y - v.y * x.x;
-            }
-            wave_put(R, s & 63, s >> 6, i, re, im);
-        }
-        __syncthreads();
-        if (s < ni) stc(part + ((long)r * CG + blockIdx.x) * (kmax + 1) + i0 + s, wave_get(R, s));
-        __syncthreads();
-    }
-}
-
-// w -= sum_i h_i v_i (i <= j) with h_i the totals of the dot partials of
-// the previous kernel; group 0 adds this pass's h into column j of H.  Then
-// mode 1: the partial dots <v_i, w> of the updated w (the second pass of
-// classical Gram-Schmidt); mode 2: the partials of |w|^2.
-__global__ __launch_bounds__(CTPB) void k_cg_orth(const double2 *__restrict__ V, double2 *__restrict__ w,
-                                                  const double2 *__restrict__ part, double2 *__restrict__ part_out,
-                                                  GState *__restrict__ st, CArgs a, int kmax, int j, int mode)
-{
-    __shared__ Red R;
-    __shared__ double2 h[CK + 1];
-    const int r = blockIdx.y, s = threadIdx.x;
-    if ((a.active && !a.active[r]) || st[r].closed) return;
-    const long nrow = (long)a.nblocks * 2 * a.N;
-    group_totals(part, r, kmax + 1, j + 1, h);
-    const double2 *Vr = V + (long)r * (kmax + 1) * nrow;
-    double2 *wr = w + (long)r * nrow;
-    double n2 = 0;
-    for (long t = (long)blockIdx.x * CTPB + s; t < nrow; t += (long)gridDim.x * CTPB) {
-        cx<double> x = ldc<double>(wr + t);
-#pragma unroll 4
-        for (int i = 0; i <= j; ++i) x = x - ldc<double>(&h[i]) * ldc<double>(Vr + (long)i * nrow + t);
-        stc(wr + t, x);
-        n2 += x.re * x.re + x.im * x.im;
-    }
-    if (blockIdx.x == 0 && s == 0) {
-        GState &S = st[r];
-        for (int i = 0; i <= j; ++i) {
-            double2 &e = S.H[i * CK + j];
-            e.x += h[i].x;
-            e.y += h[i].y;
-        }
-    }
-    if (mode == 1) {
-        // the rows of this thread were written by this thread: no barrier needed
-        for (int i0 = 0; i0 <= j; i0 += 2 * NMAX) {
-            const int ni = min(2 * NMAX, j + 1 - i0);
-            for (int i = 0; i < ni; ++i) {
-                double re = 0, im = 0;
-                for (long t = (long)blockIdx.x * CTPB + s; t < nrow; t += (long)gridDim.x * CTPB) {
-                    const double2 v = Vr[(long)(i0 + i) * nrow + t], x = wr[t];
-                    re += v.x * x.x + v.y * x.y;
-                    im += v.x * x.y - v.y * x.x;
-                }
-                wave_put(R, s & 63, s >> 6, i, re, im);
-            }
-            __syncthreads();
-            if (s < ni) stc(part_out + ((long)r * CG + blockIdx.x) * (kmax + 1) + i0 + s, wave_get(R, s));
-            __syncthreads();
-        }
-    } else if (mode == 2) {
-        wave_put(R, s & 63, s >> 6, 0, n2, 0.0);
-        __syncthreads();
-        if (s == 0) stc(part_out + ((long)r * CG + blockIdx.x), wave_get(R, 0));
-    }
-}
-
 // Givens rotation in the convention of LAPACK's zlartg: [c s; -conj(s) c]
 // [f; g] = [r; 0] with c real >= 0
 __device__ __forceinline__ void givens(cx<double> f, cx<double> g, double &c, cx<double> &sn, cx<double> &rr)
@@ -655,47 +612,122 @@ __device__ __forceinline__ void givens(cx<double> f, cx<double> g, double &c, cx
     }
 }
 
-// beta = |w|; v_{j+1} = w / beta; column j of H rotated (group 0); a space
-// that closed (beta tiny against |b|) stops growing
-__global__ __launch_bounds__(CTPB) void k_cg_next(double2 *__restrict__ V, const double2 *__restrict__ w,
-                                                  const double2 *__restrict__ part, GState *__restrict__ st, CArgs a,
+// One Arnoldi step is three kernels after the operator: the dots of w with the
+// basis; a first Gram-Schmidt pass, with the dots and the norm of what it
+// leaves; a second pass, which also normalises.  The norm after the second
+// pass is |w|^2 - sum |h|^2 with the norm after the first and the second pass's
+// h (the basis is orthonormal, and those h are of rounding size, so nothing
+// cancels; where w is all rounding, the space has closed either way): the
+// vector needs no kernel of its own to be normalised.  Bound by the launches
+// (4.5 us each) and a chain of a few memory round trips.  Four kernels, partial
+// sums read across lines and one vector's dot after another took 32.5 us a step
+// at 24^3x48 (N = 12, sixteen steps) where this takes 23, and 28 us at 16^4 where
+// this takes 19; the preconditioner 2.83 -> 2.68 and 0.99 -> 0.87 ms.
+__global__ __launch_bounds__(CTPB) void k_cg_dots(const double2 *__restrict__ V, const double2 *__restrict__ w,
+                                                  double2 *__restrict__ part, const GState *__restrict__ st, CArgs a,
                                                   int kmax, int j)
 {
+    __shared__ Red R;
+    const int r = blockIdx.y;
+    if ((a.active && !a.active[r]) || st[r].closed) return;
+    const long nrow = (long)a.nblocks * 2 * a.N;
+    group_dots(R, V + (long)r * (kmax + 1) * nrow, w + (long)r * nrow, nrow, j, part, r, kmax + 1);
+}
+
+// First pass: w -= sum_i h_i v_i (i <= j), h_i the totals of part; the partial
+// dots of the new w (partB) and of |w|^2 (partN).
+__global__ __launch_bounds__(CTPB) void k_cg_orth(const double2 *__restrict__ V, double2 *__restrict__ w,
+                                                  const double2 *__restrict__ part, double2 *__restrict__ partB,
+                                                  double2 *__restrict__ partN, const GState *__restrict__ st, CArgs a,
+                                                  int kmax, int j)
+{
+    __shared__ Red R, Rn;
+    __shared__ double2 h[CK + 1];
     const int r = blockIdx.y, s = threadIdx.x;
     if ((a.active && !a.active[r]) || st[r].closed) return;
     const long nrow = (long)a.nblocks * 2 * a.N;
-    __shared__ double2 tot[1];
-    group_totals(part, r, 1, 1, tot);
-    const double beta = sqrt(tot[0].x);
+    group_totals(part, r, kmax + 1, j + 1, h);
+    const double2 *Vr = V + (long)r * (kmax + 1) * nrow;
+    double2 *wr = w + (long)r * nrow;
+    double n2 = 0;
+    for (long t = (long)blockIdx.x * CTPB + s; t < nrow; t += (long)gridDim.x * CTPB) {
+        cx<double> x = ldc<double>(wr + t);
+#pragma unroll 4
+        for (int i = 0; i <= j; ++i) x = x - ldc<double>(&h[i]) * ldc<double>(Vr + (long)i * nrow + t);
+        stc(wr + t, x);
+        n2 += x.re * x.re + x.im * x.im;
+    }
+    wave_put(Rn, s & 63, s >> 6, 0, n2, 0.0);
+    // the rows of this thread were written by this thread: no barrier needed
+    group_dots(R, Vr, wr, nrow, j, partB, r, kmax + 1);
+    if (s == 0) stc(partN + ((long)r * CG + blockIdx.x), wave_get(Rn, 0));
+}
+
+// Second pass, h the totals of partB: v_{j+1} = (w - sum_i h_i v_i) / beta;
+// group 0 sets column j of H, the totals of both passes, and rotates it; a
+// space that closed (beta tiny against |b|) stops growing.
+__global__ __launch_bounds__(CTPB) void k_cg_next(double2 *__restrict__ V, const double2 *__restrict__ w,
+                                                  const double2 *__restrict__ partA, const double2 *__restrict__ partB,
+                                                  const double2 *__restrict__ partN, GState *__restrict__ st, CArgs a,
+                                                  int kmax, int j)
+{
+    __shared__ double2 h[CK + 1], h1[CK + 1], tot[1];
+    const int r = blockIdx.y, s = threadIdx.x;
+    // group 0 may set closed while others are still to start: they then have
+    // nothing to write, since this step's vector is not used
+    if ((a.active && !a.active[r]) || st[r].closed) return;
+    const long nrow = (long)a.nblocks * 2 * a.N;
+    group_totals(partN, r, 1, 1, tot);
+    group_totals(partB, r, kmax + 1, j + 1, h);
+    double n2 = tot[0].x;
+    for (int i = 0; i <= j; ++i) n2 -= h[i].x * h[i].x + h[i].y * h[i].y;
+    const double beta = n2 > 0 ? sqrt(n2) : n2 == n2 ? 0.0 : n2; // (a NaN stays one)
     const bool closes = !(beta > 1e-14 * st[r].bnorm);
     if (!closes && j + 1 <= kmax) {
         const double inv = 1.0 / beta;
-        double2 *Vn = V + ((long)r * (kmax + 1) + j + 1) * nrow;
+        double2 *Vr = V + (long)r * (kmax + 1) * nrow;
         for (long t = (long)blockIdx.x * CTPB + s; t < nrow; t += (long)gridDim.x * CTPB) {
-            const double2 x = w[(long)r * nrow + t];
-            Vn[t] = make_double2(x.x * inv, x.y * inv);
+            cx<double> x = ldc<double>(w + (long)r * nrow + t);
+#pragma unroll 4
+            for (int i = 0; i <= j; ++i) x = x - ldc<double>(&h[i]) * ldc<double>(Vr + (long)i * nrow + t);
+            stc(Vr + (long)(j + 1) * nrow + t, inv * x);
         }
     }
-    if (blockIdx.x == 0 && s == 0) {
+    if (blockIdx.x == 0) { // uniform
+        group_totals(partA, r, kmax + 1, j + 1, h1);
         GState &S = st[r];
-        // apply the earlier rotations to column j, then form rotation j
-        for (int i = 0; i < j; ++i) {
-            const cx<double> x0 = ldc<double>(&S.H[i * CK + j]), x1 = ldc<double>(&S.H[(i + 1) * CK + j]);
-            const cx<double> sn = ldc<double>(&S.sn[i]);
-            stc(&S.H[i * CK + j], S.cs[i] * x0 + sn * x1);
-            stc(&S.H[(i + 1) * CK + j], S.cs[i] * x1 - conjx(sn) * x0);
+        if (s <= j) {
+            h[s].x += h1[s].x;
+            h[s].y += h1[s].y;
         }
-        double c;
-        cx<double> sn, rr;
-        givens(ldc<double>(&S.H[j * CK + j]), mk<double>(closes ? 0.0 : beta, 0), c, sn, rr);
-        S.cs[j] = c;
-        stc(&S.sn[j], sn);
-        stc(&S.H[j * CK + j], rr);
-        const cx<double> gj = ldc<double>(&S.g[j]);
-        stc(&S.g[j], c * gj);
-        stc(&S.g[j + 1], mk<double>(0, 0) - conjx(sn) * gj);
-        S.ncol = j + 1;
-        if (closes) S.closed = 1;
+        // the earlier rotations, all at hand before the chain
+        __shared__ double2 sn_[CK];
+        __shared__ double cs_[CK];
+        if (s < j) {
+            sn_[s] = S.sn[s];
+            cs_[s] = S.cs[s];
+        }
+        __syncthreads();
+        if (s == 0) {
+            // apply the earlier rotations to column j, then form rotation j
+            cx<double> x0 = ldc<double>(&h[0]);
+            for (int i = 0; i < j; ++i) {
+                const cx<double> x1 = ldc<double>(&h[i + 1]), sn = ldc<double>(&sn_[i]);
+                stc(&S.H[i * CK + j], cs_[i] * x0 + sn * x1);
+                x0 = cs_[i] * x1 - conjx(sn) * x0;
+            }
+            double c;
+            cx<double> sn, rr;
+            givens(x0, mk<double>(closes ? 0.0 : beta, 0), c, sn, rr);
+            S.cs[j] = c;
+            stc(&S.sn[j], sn);
+            stc(&S.H[j * CK + j], rr);
+            const cx<double> gj = ldc<double>(&S.g[j]);
+            stc(&S.g[j], c * gj);
+            stc(&S.g[j + 1], mk<double>(0, 0) - conjx(sn) * gj);
+            S.ncol = j + 1;
+            if (closes) S.closed = 1;
+        }
     }
 }
 
@@ -970,9 +1002,8 @@ Status coarse_gmres(dd_ctx *ctx, AmgWork &wk, int W, int k, const double *m0_dev
         // w = (D_c + m0) v_j
         coarse_apply(ctx, W, A.Ah.as<__half2>(), V + (long)j * nrow, (long)(kmax + 1) * nrow, w, nrow, S, a);
         k_cg_dots<<<grid, CTPB, 0, st>>>(V, w, wk.partA.as<double2>(), S, a, kmax, j);
-        k_cg_orth<<<grid, CTPB, 0, st>>>(V, w, wk.partA.as<double2>(), wk.partB.as<double2>(), S, a, kmax, j, 1);
-        k_cg_orth<<<grid, CTPB, 0, st>>>(V, w, wk.partB.as<double2>(), wk.partN.as<double2>(), S, a, kmax, j, 2);
-        k_cg_next<<<grid, CTPB, 0, st>>>(V, w, wk.partN.as<double2>(), S, a, kmax, j);
+        k_cg_orth<<<grid, CTPB, 0, st>>>(V, w, wk.partA.as<double2>(), wk.partB.as<double2>(), wk.partN.as<double2>(), S, a, kmax, j);
+        k_cg_next<<<grid, CTPB, 0, st>>>(V, w, wk.partA.as<double2>(), wk.partB.as<double2>(), wk.partN.as<double2>(), S, a, kmax, j);
     }
     k_cg_finish<<<grid, CTPB, 0, st>>>(V, wk.xx.as<double2>(), S, a, kmax);
     DD_HIP_TRY(hipGetLastError());
