@@ -275,7 +275,7 @@ __global__ __launch_bounds__(BS) void k_amg_build(const double2 *__restrict__ Pd
 // (P read once per right-hand side before: 16^3x32 FP32 with eight, restriction
 // 192 -> 85 us and prolongation 173 -> 63 us, the whole preconditioner 3.81 ->
 // 3.60 ms; 16^4 FP64 with four 2.29 -> 2.28.  One right-hand side, 24^3x48
-// FP32: 168 and 160 us either way, 4.9 and 5.2 TB/s with the fine vector.)
+// FP32: 168 and 160 us either way.)
 template <typename S> using PT = vec2_t<S>;
 template <typename S> struct alignas(2 * sizeof(vec2_t<S>) > 16 ? 16 : 2 * sizeof(vec2_t<S>)) Pair {
     vec2_t<S> e[2];
@@ -283,13 +283,20 @@ template <typename S> struct alignas(2 * sizeof(vec2_t<S>) > 16 ? 16 : 2 * sizeo
 // right-hand sides that share a read of P, as many as registers hold
 template <typename S> constexpr int rr_max() { return sizeof(S) == 4 ? 4 : 2; }
 
-template <typename S> __device__ __forceinline__ void load_p(const Pair<S> *__restrict__ p, Pair<S> q[6])
+template <typename S, bool NT> __device__ __forceinline__ void load_p(const Pair<S> *__restrict__ p, Pair<S> q[6])
 {
 #pragma unroll
-    for (int x = 0; x < 6; ++x) q[x] = p[x * (BS / 2)];
+    for (int x = 0; x < 6; ++x) {
+        if (NT) {
+            q[x].e[0] = ld_stream(&p[x * (BS / 2)].e[0]);
+            q[x].e[1] = ld_stream(&p[x * (BS / 2)].e[1]);
+        } else {
+            q[x] = p[x * (BS / 2)];
+        }
+    }
 }
 
-template <typename S, int RR>
+template <typename S, int RR, bool NT>
 __global__ __launch_bounds__(BS) void k_amg_restrict(const vec2_t<S> *__restrict__ in, const PT<S> *__restrict__ P,
                                                      double2 *__restrict__ xc, const int *__restrict__ active, int N,
                                                      int nblocks, int W)
@@ -303,8 +310,8 @@ __global__ __launch_bounds__(BS) void k_amg_restrict(const vec2_t<S> *__restrict
     if (!on) return; // uniform
     const Pair<S> *p = reinterpret_cast<const Pair<S> *>(P + pidx(b, c, 0, N, 0, 0)) + h;
     Pair<S> q[2][6], qn[2][6];
-    load_p(p, q[0]);
-    if (N > 1) load_p(p + 6 * (BS / 2), q[1]);
+    load_p<S, NT>(p, q[0]);
+    if (N > 1) load_p<S, NT>(p + 6 * (BS / 2), q[1]);
     cx<S> v[RR][6][2];
 #pragma unroll
     for (int rr = 0; rr < RR; ++rr) {
@@ -317,8 +324,8 @@ __global__ __launch_bounds__(BS) void k_amg_restrict(const vec2_t<S> *__restrict
     }
 #pragma unroll 1
     for (int i = 0; i < N; i += 2) {
-        if (i + 2 < N) load_p(p + (long)(i + 2) * 6 * (BS / 2), qn[0]);
-        if (i + 3 < N) load_p(p + (long)(i + 3) * 6 * (BS / 2), qn[1]);
+        if (i + 2 < N) load_p<S, NT>(p + (long)(i + 2) * 6 * (BS / 2), qn[0]);
+        if (i + 3 < N) load_p<S, NT>(p + (long)(i + 3) * 6 * (BS / 2), qn[1]);
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
             if (i + u < N) {
@@ -356,7 +363,7 @@ __global__ __launch_bounds__(BS) void k_amg_restrict(const vec2_t<S> *__restrict
     }
 }
 
-template <typename S, int RR>
+template <typename S, int RR, bool NT>
 __global__ __launch_bounds__(BS) void k_amg_prolong(const double2 *__restrict__ xc, const PT<S> *__restrict__ P,
                                                     vec2_t<S> *__restrict__ out, const long *__restrict__ off,
                                                     const int *__restrict__ active, int N, int nblocks, int W)
@@ -370,8 +377,8 @@ __global__ __launch_bounds__(BS) void k_amg_prolong(const double2 *__restrict__ 
     if (!on) return; // uniform
     const Pair<S> *p = reinterpret_cast<const Pair<S> *>(P + pidx(b, c, 0, N, 0, 0)) + h;
     Pair<S> q[2][6], qn[2][6];
-    load_p(p, q[0]);
-    if (N > 1) load_p(p + 6 * (BS / 2), q[1]);
+    load_p<S, NT>(p, q[0]);
+    if (N > 1) load_p<S, NT>(p + 6 * (BS / 2), q[1]);
     if (s < 2 * N * RR) {
         const int rr = s / (2 * N), k = s - rr * 2 * N;
         xs[rr][k] = ldc<S>(xc + ((long)min(r0 + rr, W - 1) * nblocks + b) * 2 * N + k);
@@ -384,8 +391,8 @@ __global__ __launch_bounds__(BS) void k_amg_prolong(const double2 *__restrict__ 
         for (int x = 0; x < 6; ++x) acc[rr][x][0] = acc[rr][x][1] = mk<S>(0, 0);
 #pragma unroll 1
     for (int i = 0; i < N; i += 2) {
-        if (i + 2 < N) load_p(p + (long)(i + 2) * 6 * (BS / 2), qn[0]);
-        if (i + 3 < N) load_p(p + (long)(i + 3) * 6 * (BS / 2), qn[1]);
+        if (i + 2 < N) load_p<S, NT>(p + (long)(i + 2) * 6 * (BS / 2), qn[0]);
+        if (i + 3 < N) load_p<S, NT>(p + (long)(i + 3) * 6 * (BS / 2), qn[1]);
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
             if (i + u < N) {
@@ -416,17 +423,26 @@ __global__ __launch_bounds__(BS) void k_amg_prolong(const double2 *__restrict__ 
     }
 }
 
+// An FP32 P that outgrows the 256 MB cache in front of HBM is read past it
+// (24^3x48, 764 MB: restriction 168 -> 146 us, prolongation 160 -> 149).  A
+// smaller one stays cached from call to call, and FP64, two loads for a pair,
+// lost by it (24^3x48: 310 -> 346 and 320 -> 357 us).
+template <typename S> bool p_streams(int nb, int N)
+{
+    return sizeof(S) == 4 && (size_t)nb * N * 12 * BS * sizeof(vec2_t<S>) > (256u << 20);
+}
+
 template <typename S, int RR>
 void restrict_rr(int nb, int W, hipStream_t st, const void *in, const DevBuf &P, void *xc, const int *active, int N)
 {
-    k_amg_restrict<S, RR><<<dim3(nb, (W + RR - 1) / RR), BS, 0, st>>>(
+    (p_streams<S>(nb, N) ? k_amg_restrict<S, RR, sizeof(S) == 4> : k_amg_restrict<S, RR, false>)<<<dim3(nb, (W + RR - 1) / RR), BS, 0, st>>>(
         static_cast<const vec2_t<S> *>(in), static_cast<const vec2_t<S> *>(P.p), static_cast<double2 *>(xc), active, N, nb, W);
 }
 template <typename S, int RR>
 void prolong_rr(int nb, int W, hipStream_t st, const void *xc, const DevBuf &P, void *out, const long *off, const int *active,
                 int N)
 {
-    k_amg_prolong<S, RR><<<dim3(nb, (W + RR - 1) / RR), BS, 0, st>>>(
+    (p_streams<S>(nb, N) ? k_amg_prolong<S, RR, sizeof(S) == 4> : k_amg_prolong<S, RR, false>)<<<dim3(nb, (W + RR - 1) / RR), BS, 0, st>>>(
         static_cast<const double2 *>(xc), static_cast<const vec2_t<S> *>(P.p), static_cast<vec2_t<S> *>(out), off, active, N,
         nb, W);
 }
@@ -802,16 +818,19 @@ void coarse_apply(const dd_ctx *ctx, int W, const __half2 *Ah, const double2 *x,
 __global__ __launch_bounds__(CTPB) void k_cg_finish(const double2 *__restrict__ V, double2 *__restrict__ x,
                                                     const GState *__restrict__ st, CArgs a, int kmax)
 {
-    __shared__ double2 y[CK];
+    __shared__ double2 y[CK], H[CK * CK];
     const int r = blockIdx.y, s = threadIdx.x;
     if (a.active && !a.active[r]) return;
     const GState &S = st[r];
     const int n = S.ncol;
-    if (s == 0) {
+    for (int e = s; e < n * CK; e += CTPB) H[e] = S.H[e];
+    if (s < n) y[s] = S.g[s];
+    __syncthreads();
+    if (s == 0) { // the chain works in LDS (on global memory it took 5 us more)
         for (int i = n - 1; i >= 0; --i) {
-            cx<double> acc = ldc<double>(&S.g[i]);
-            for (int k = i + 1; k < n; ++k) acc = acc - ldc<double>(&S.H[i * CK + k]) * ldc<double>(&y[k]);
-            const cx<double> d = ldc<double>(&S.H[i * CK + i]);
+            cx<double> acc = ldc<double>(&y[i]);
+            for (int k = i + 1; k < n; ++k) acc = acc - ldc<double>(&H[i * CK + k]) * ldc<double>(&y[k]);
+            const cx<double> d = ldc<double>(&H[i * CK + i]);
             const double dd = d.re * d.re + d.im * d.im;
             // a zero pivot only if the coarse operator is singular on the space
             const cx<double> q = dd > 0 ? (1.0 / dd) * (acc * conjx(d)) : mk<double>(0, 0);

@@ -69,3 +69,23 @@ def test_coarse_apply(lat, nrhs):
     lat.ctx.synchronize()
     for r in range(nrhs):
         assert rel(to_host(y)[r], Dc @ x[r] + m0[r] * x[r]) < 1e-13
+
+
+def test_large_interpolation():
+    """16^3x48 with 16 test vectors: 302 MB of FP32 interpolation, which is
+    read past the cache.  P^+ P = 1 to FP32 rounding, one right-hand side alone
+    and three together."""
+    import torch
+    from paper_1710_07041_amd import ddsap
+    dims, n = (16, 16, 16, 48), 16
+    lat = Lattice(dims, eps=0.3, seed=5, oracle_clover=False)
+    p = ddsap.default_amg_params()
+    p.nvec, p.setup_iters, p.setup_ncy, p.setup_nmr, p.setup_prec, p.adapt = n, 1, 1, 2, ddsap.DD_F32, 0
+    lat.ctx.amg_setup(-0.2, torch.randn((n, lat.V, 4, 3), dtype=torch.complex128, device="cuda"), p)
+    for nrhs in (1, 3):
+        x = torch.randn((nrhs, lat.ctx.amg_coarse_size()), dtype=torch.complex128, device="cuda")
+        fine, y = lat.ctx.empty_blocked("f32", nrhs), torch.empty_like(x)
+        lat.ctx.amg_prolong(x, fine, "f32", nrhs)
+        lat.ctx.amg_restrict(fine, y, "f32", nrhs)
+        lat.ctx.synchronize()
+        assert rel(to_host(y), to_host(x)) < 2e-6
