@@ -348,6 +348,52 @@ __device__ __forceinline__ FaceHop face_hop(const Geom &g, int b, const int bc[4
     h.ls = h.dir > 0 ? s : h.sn;
     return h;
 }
+// The products of a face hop and the third row of its link, as explicit
+// multiply-adds.  Which of two products a sum fuses is otherwise the compiler's
+// choice and changes with the code around it, and the adaptive rounds of the
+// two-level setup magnify a last bit of the FP32 residual (8^4, twelve vectors,
+// two rounds: 1e-8 in the residual moves the interpolation by 6e-6).  In this
+// order an interpolation stays what it was, bit for bit; it costs no time.
+template <typename A> __device__ __forceinline__ void face_mul(const cx<A> U[9], const cx<A> h[6], cx<A> out[6])
+{
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            const cx<A> u = U[a * 3], x = h[s * 3];
+            cx<A> acc = mk<A>(fma(u.re, x.re, -(u.im * x.im)),
+                              s == 0 ? fma(u.re, x.im, u.im * x.re) : fma(u.im, x.re, u.re * x.im));
+            cmac(acc, U[a * 3 + 1], h[s * 3 + 1]);
+            cmac(acc, U[a * 3 + 2], h[s * 3 + 2]);
+            out[s * 3 + a] = acc;
+        }
+}
+template <typename A> __device__ __forceinline__ void face_mul_adj(const cx<A> U[9], const cx<A> h[6], cx<A> out[6])
+{
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            const cx<A> u = U[a], x = h[s * 3];
+            cx<A> acc = mk<A>(s == 0 ? fma(u.im, x.im, u.re * x.re) : fma(u.re, x.re, u.im * x.im),
+                              fma(u.re, x.im, -(u.im * x.re)));
+            cmacc(acc, U[3 + a], h[s * 3 + 1]);
+            cmacc(acc, U[6 + a], h[s * 3 + 2]);
+            out[s * 3 + a] = acc;
+        }
+}
+// conj(a b - c d)
+template <typename A> __device__ __forceinline__ cx<A> face_minor(cx<A> a, cx<A> b, cx<A> c, cx<A> d)
+{
+    return mk<A>(fma(a.re, b.re, -(a.im * b.im)) - fma(c.re, d.re, -(c.im * d.im)),
+                 fma(c.im, d.re, c.re * d.im) - fma(a.im, b.re, a.re * b.im));
+}
+template <typename A> __device__ __forceinline__ void face_third_row(cx<A> U[9])
+{
+    U[6] = face_minor(U[1], U[5], U[2], U[4]);
+    U[7] = face_minor(U[2], U[3], U[0], U[5]);
+    U[8] = face_minor(U[0], U[4], U[1], U[3]);
+}
 // One such hop of the spinor p with the link W (as stored) to fb[component].
 template <typename A>
 __device__ __forceinline__ void face_hop_post(const FaceHop &f, const cx<A> p[12], const cx<A> W[9], int tid,
@@ -356,10 +402,10 @@ __device__ __forceinline__ void face_hop_post(const FaceHop &f, const cx<A> p[12
     cx<A> h[6], t[6];
     if (f.dir > 0) {
         proj_m(f.mu, p, h);
-        su3_mul(W, h, t);
+        face_mul(W, h, t);
     } else {
         proj_p(f.mu, p, h);
-        su3_mul_adj(W, h, t);
+        face_mul_adj(W, h, t);
     }
     const A kk = (A)(-0.5f * f.sign);
 #pragma unroll

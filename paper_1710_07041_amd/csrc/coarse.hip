@@ -331,16 +331,16 @@ __global__ __launch_bounds__(BS) void k_amg_restrict(const vec2_t<S> *__restrict
             if (i + u < N) {
 #pragma unroll
                 for (int rr = 0; rr < RR; ++rr) {
-                    S re = 0, im = 0;
+                    S re[2] = {0, 0}, im[2] = {0, 0}; // a site's sum in S, all further in FP64
 #pragma unroll
                     for (int x = 0; x < 6; ++x)
 #pragma unroll
                         for (int k = 0; k < 2; ++k) {
                             const cx<S> a = ldc<S>(&q[u][x].e[k]), f = v[rr][x][k];
-                            re = fma(a.re, f.re, fma(a.im, f.im, re));
-                            im = fma(a.re, f.im, fma(-a.im, f.re, im));
+                            re[k] = fma(a.re, f.re, fma(a.im, f.im, re[k]));
+                            im[k] = fma(a.re, f.im, fma(-a.im, f.re, im[k]));
                         }
-                    const double tre = wave_sum((double)re), tim = wave_sum((double)im);
+                    const double tre = wave_sum((double)re[0] + (double)re[1]), tim = wave_sum((double)im[0] + (double)im[1]);
                     if (lane == 63) {
                         part[wave][rr][i + u][0] = tre;
                         part[wave][rr][i + u][1] = tim;

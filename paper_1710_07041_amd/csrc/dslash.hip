@@ -346,7 +346,7 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(WAVES))) voi
             if constexpr (FAST) {
 #pragma unroll
                 for (int e = 0; e < 6; ++e) W[e] = ldc<A>(&L.fl[j][e][s]);
-                su3_third_row(W);
+                face_third_row(W);
             } else {
                 load_link<A>(j == 0 ? l0 : l1, a.r12, W);
             }

@@ -15,7 +15,9 @@
 // registers (FP32 arithmetic), so no memory load sits inside the step.
 // Measured together, twelve FP32 cycles at 32^3x64: 7.07 -> 6.70 ms a call,
 // ten FP16 ones at 48^3x96: 23.4 -> 22.5 ms, twelve FP64 ones at 24^3x48, which
-// now carry the residual instead of recomputing it: 6.60 -> 6.05 ms.
+// now carry the residual instead of recomputing it: 6.60 -> 6.05 ms.  The faces
+// are published by the even-odd sweep's routine, a whole half spinor at a time:
+// 6.70 -> 6.64 and 6.14 -> 6.01 ms against one that goes spin by spin.
 // More wavefronts did not pay: three workgroups per CU (168 registers, link
 // rows rebuilt at each use) spill, 15.4 ms in FP32; two threads per site (512
 // threads a block at 128 registers) double the LDS traffic and the barriers,
@@ -79,31 +81,6 @@ __device__ __forceinline__ void blk_face_add(const Geom &g, const int bc[4], int
         recon_spin<MU, -1, 0, false>(qu, ql, t, k);
         su3_spin(W, h + 3, t);
         recon_spin<MU, -1, 1, false>(qu, ql, t, k);
-    }
-}
-template <int MU, typename S, typename A>
-__device__ __forceinline__ void blk_face_publish(vec2_t<S> *__restrict__ base, int s, const cx<A> u[6], const cx<A> l[6],
-                                                  const cx<A> W[9])
-{
-    const int lm = (s >> (2 * MU)) & 3;
-    vec2_t<S> *fp = base + (2 * MU) * 6 * 64 + face_index(s, MU);
-    cx<A> h[3], t[3];
-    if (lm == 0) {
-        proj_spin<MU, -1, 0>(u, l, h);
-#pragma unroll
-        for (int e = 0; e < 3; ++e) stc(fp + e * 64, h[e]);
-        proj_spin<MU, -1, 1>(u, l, h);
-#pragma unroll
-        for (int e = 0; e < 3; ++e) stc(fp + (3 + e) * 64, h[e]);
-    } else if (lm == BEXT - 1) {
-        proj_spin<MU, +1, 0>(u, l, h);
-        su3_spin_adj(W, h, t);
-#pragma unroll
-        for (int e = 0; e < 3; ++e) stc(fp + (6 + e) * 64, t[e]);
-        proj_spin<MU, +1, 1>(u, l, h);
-        su3_spin_adj(W, h, t);
-#pragma unroll
-        for (int e = 0; e < 3; ++e) stc(fp + (9 + e) * 64, t[e]);
     }
 }
 
@@ -306,11 +283,7 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(WAVES))) voi
 #pragma unroll
         for (int c = 0; c < 12; ++c) rr[c] = it > 0 ? L.del[c][s] : mk<A>(0, 0);
         if (a.publish) {
-            vec2_t<S> *base = faces + ((long)b * a.nrhs + r) * FACE_ELEMS;
-            blk_face_publish<0, S, A>(base, s, rr, rr + 6, U[0]);
-            blk_face_publish<1, S, A>(base, s, rr, rr + 6, U[1]);
-            blk_face_publish<2, S, A>(base, s, rr, rr + 6, U[2]);
-            blk_face_publish<3, S, A>(base, s, rr, rr + 6, U[3]);
+            face_publish<S, A>(faces, b, a.nrhs, r, s, rr, U);
         }
 #pragma unroll
         for (int c = 0; c < 12; ++c) {
