@@ -135,22 +135,26 @@ __device__ __forceinline__ void recon_spin(cx<A> u[6], cx<A> l[6], const cx<A> t
         if (MU == 3) y = SG > 0 ? y + x : y - x;
     }
 }
-// t = W h and t = W^+ h for one spin
+// t = W h and t = W^+ h for one spin, in explicit multiply-adds (their order: see
+// face_mul)
 template <typename A> __device__ __forceinline__ void su3_spin(const cx<A> W[9], const cx<A> h[3], cx<A> t[3])
 {
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-        cx<A> acc = W[a * 3] * h[0];
+        const cx<A> u = W[a * 3], x = h[0];
+        cx<A> acc = mk<A>(fma(u.re, x.re, -(u.im * x.im)), fma(u.im, x.re, u.re * x.im));
         cmac(acc, W[a * 3 + 1], h[1]);
         cmac(acc, W[a * 3 + 2], h[2]);
         t[a] = acc;
     }
 }
-template <typename A> __device__ __forceinline__ void su3_spin_adj(const cx<A> W[9], const cx<A> h[3], cx<A> t[3])
+template <int MU, typename A> __device__ __forceinline__ void su3_spin_adj(const cx<A> W[9], const cx<A> h[3], cx<A> t[3])
 {
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-        cx<A> acc = conjx(W[a]) * h[0];
+        const cx<A> u = W[a], x = h[0];
+        cx<A> acc = mk<A>(MU % 2 == 0 ? fma(u.im, x.im, u.re * x.re) : fma(u.re, x.re, u.im * x.im),
+                          fma(u.re, x.im, -(u.im * x.re)));
         cmacc(acc, W[3 + a], h[1]);
         cmacc(acc, W[6 + a], h[2]);
         t[a] = acc;
@@ -195,7 +199,7 @@ __device__ __forceinline__ void blk_hop_spin(const cx<A> W[9], const cx<A> u[6],
         su3_spin(W, t, h);
         recon_spin<MU, -1, SP, true>(qu, ql, h, kf);
         proj_spin<MU, +1, SP>(u, l, h);
-        su3_spin_adj(W, h, t);
+        su3_spin_adj<MU>(W, h, t);
 #pragma unroll
         for (int c = 0; c < 3; ++c) h[c] = row_shift<0x114, A>(t[c]);
         recon_spin<MU, +1, SP, true>(qu, ql, h, kb);
@@ -209,7 +213,7 @@ __device__ __forceinline__ void blk_hop_spin(const cx<A> W[9], const cx<A> u[6],
         recon_spin<MU, -1, SP, !WRAP>(qu, ql, h, kf);
     }
     proj_spin<MU, +1, SP>(u, l, h);
-    su3_spin_adj(W, h, t);
+    su3_spin_adj<MU>(W, h, t);
 #pragma unroll
     for (int c = 0; c < 3; ++c) h[c] = lane_hop<MU, -1, A>(t[c], snb);
     if (inb) {
@@ -241,7 +245,7 @@ __device__ __forceinline__ void blk_t_post_spin(LT &L, const cx<A> W[9], int s, 
 #pragma unroll
     for (int c = 0; c < 3; ++c) L.tf[3 * SP + c][s] = h[c];
     proj_spin<3, +1, SP>(u, l, h);
-    su3_spin_adj(W, h, t);
+    su3_spin_adj<3>(W, h, t);
 #pragma unroll
     for (int c = 0; c < 3; ++c) L.tb[3 * SP + c][s] = t[c];
 }
