@@ -27,10 +27,10 @@ CLASS_PATTERNS = [
     (r"k_sap_sweep<float,", "sap_sweep_f32"),
     (r"k_sap_sweep<double,", "sap_sweep_f64"),
     (r"k_sap_sweep<__half,", "sap_sweep_f16"),
-    (r"k_dslash<float, double,", "dslash_f32in_f64"),
-    (r"k_dslash<double, double,", "dslash_f64"),
-    (r"k_dslash<float, float,", "dslash_f32"),
-    (r"k_dslash<__half,", "dslash_f16"),
+    (r"k_dslash(?:_block)?<float, double,", "dslash_f32in_f64"),
+    (r"k_dslash(?:_block)?<double, double,", "dslash_f64"),
+    (r"k_dslash(?:_block)?<float, float,", "dslash_f32"),
+    (r"k_dslash(?:_block)?<__half,", "dslash_f16"),
     (r"k_dots_lag<", "cgs_dots"),
     (r"k_update_lag<", "cgs_update"),
     (r"k_update_dots<", "restart_norm"),
