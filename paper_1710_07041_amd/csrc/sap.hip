@@ -54,11 +54,14 @@ namespace {
 //   w_o = A_oo^-1 H_oe r_e, q_e = A_ee r_e - H_eo w_o: delta_e += alpha r_e,
 //   r_e -= alpha q_e, and delta_o = y_o - sum alpha w_o, which is
 //   A_oo^-1 (rho_o - H_oe delta_e) without another exchange and solve.
-// The odd equations hold exactly after the solve, so the block residual that
-// the next visit starts from is r_e on the even sites and zero on the odd ones:
-// FP32 and FP64 carry it, as the plain sweep does.  FP16 storage recomputes the
-// residual from the stored psi, which takes out what rounding psi at every
-// visit left (3.4e-4 against 7e-4 in the result).
+// Each visit forms the block residual anew from the stored psi, so that what
+// rounding psi left is taken out again by the next visit (a residual carried
+// from visit to visit, one exchange less, let the rounding add up: FP32 at 8^4
+// 1.87e-7 after twelve cycles and 2.19e-7 after 32, where this stays at 1.5e-7;
+// 3.67 against 3.78 ms a call at 24^3x48).  It takes one exchange: with
+// z_o = psi_o + y_o,
+//   rho_o = eta_o - (hops from outside) - A_oo psi_o - H_oe psi_e,
+//   r_e = eta_e - (hops from outside) - A_ee psi_e - H_eo z_o.
 // Threads 0-127 (waves 0-1) own the even sites, threads 128-255 (waves 2-3)
 // the odd ones, so every parity branch is uniform over a wavefront.  A hop
 // exchange between the parities is pipelined: at stage k the publishing
@@ -66,13 +69,13 @@ namespace {
 // the other LDS buffer.  A_oo^-1 is applied through the Cholesky factor of
 // each chiral half (the halves are Hermitian positive definite: the clover
 // term is small against 4 + m0).
-// What bounds it: a chain of 1 + 2 nMR exchanges of five barriers each, with
-// half the wavefronts idle in the first and last stage of each; so what counts
-// are few exchanges and a second workgroup per CU to fill them (FP32
-// arithmetic).  24^3x48, twelve cycles, against the form that recomputed the
-// residual, took the odd sites from an exchange and a solve of their own and
-// ran one workgroup per CU: FP32 6.49 -> 3.67 ms a call, FP16 6.10 -> 3.56,
-// FP64 (one workgroup per CU still) 11.5 -> 10.1.
+// What bounds it: a chain of 2 + 2 nMR exchanges of five stages and four
+// barriers each, with half the wavefronts idle in the first and last stage of
+// each; so what counts are few exchanges and a second workgroup per CU to fill
+// them (FP32 arithmetic).  24^3x48, twelve cycles, against a form that took
+// 4 + 2 nMR (the odd sites from an exchange and a solve of their own) and ran
+// one workgroup per CU: FP32 6.56 -> 3.78 ms a call, FP16 6.28 -> 3.49, FP64
+// (one workgroup per CU still; 46 registers spilled) 11.9 -> 9.66.
 // ---------------------------------------------------------------------------
 
 // Site of thread t: the pair {2k, 2k+1} (k = t mod 128) holds one even and
@@ -223,15 +226,13 @@ __device__ __forceinline__ void eo_exchange(EoLds<A> &L, const Geom &g, int b, c
     if (!pub) eo_consume<3, WRAP, A>(L, 1, g, b, bc, s, Ur[3], q);
 }
 
-// Whether the even-odd sweep of storage type S carries the block residual.
-template <typename S> constexpr bool EO_CARRY = sizeof(S) > 2;
-
-template <typename S, typename A, int WAVES, bool WRAP>
+template <typename S, typename A, int WAVES, bool WRAP, bool SIG>
 __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(WAVES))) void k_sap_sweep_eo(
     const vec2_t<S> *__restrict__ eta0, vec2_t<S> *__restrict__ psi0, const vec2_t<S> *__restrict__ links,
-    const vec2_t<S> *__restrict__ clov, vec2_t<S> *__restrict__ faces, vec2_t<S> *__restrict__ resid, SArgs a)
+    const vec2_t<S> *__restrict__ clov, vec2_t<S> *__restrict__ faces, SArgs a)
 {
-    constexpr bool CARRY = EO_CARRY<S>;
+    // FP32 at two workgroups per CU: no room for eta meanwhile, it is read again
+    constexpr bool AGAIN = WAVES == 2 && sizeof(S) == 4;
     __shared__ EoLds<A> E;
     int b, rhs0, rhs1;
     if (!sweep_part(a, b, rhs0, rhs1)) return;
@@ -253,59 +254,58 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(WAVES))) voi
         const A diag = (A)(4.0 + (a.m0_dev ? a.m0_dev[r] : a.m0[r]));
         const vec2_t<S> *__restrict__ eta = eta0 + (a.eta_off ? a.eta_off[r] : 0);
         vec2_t<S> *__restrict__ psi = psi0 + (a.psi_off ? a.psi_off[r] : 0);
-        const long sp = ((long)b * a.nrhs + r) * 12 * BS + s; // (the carried residual has no slot offsets)
+        const long sp = ((long)b * a.nrhs + r) * 12 * BS + s;
         // the clover term's addresses are the same for every right-hand side:
         // hide that, or they leave the loop and spill
         int zero = 0;
         asm volatile("" : "+s"(zero));
         const vec2_t<S> *cp = clov + (long)b * 36 * BS + s + zero;
 
-        // rho = R - (hops of the other colour's last update), or
-        // eta - (D psi)_B; rr takes it
+        // q = A psi of the site; the site's clover term (odd sites: the
+        // Cholesky factors of A_oo) stays, half 0 in registers, half 1 in LDS
         cx<A> rr[12], q[12], cl[18];
 #pragma unroll
-        for (int c = 0; c < 12; ++c) q[c] = mk<A>(0, 0);
-        if constexpr (!CARRY) {
-            if (a.mode == 2) {
-#pragma unroll
-                for (int c = 0; c < 12; ++c) rr[c] = ldc<A>(psi + sp + c * BS);
-#pragma unroll 1
-                for (int h = 0; h < 2; ++h) {
-                    load_clover_half<A>(cp + 18 * h * BS, a.sig, cl);
-                    if (h == 0) clover_half_mac<A>(cl, diag, rr, q);
-                    else clover_half_mac<A>(cl, diag, rr + 6, q + 6);
-                }
-                eo_exchange<WRAP>(E, a.g, b, bc, s, U, odd, rr, q);
-                eo_exchange<WRAP>(E, a.g, b, bc, s, U, !odd, rr, q);
-            }
+        for (int c = 0; c < 12; ++c) {
+            q[c] = mk<A>(0, 0);
+            rr[c] = a.mode == 2 ? ldc<A>(psi + sp + c * BS) : mk<A>(0, 0);
         }
-        vec2_t<S> er[12];
-        const bool fresh = !CARRY || a.mode != 2; // rho starts from eta
-#pragma unroll
-        for (int c = 0; c < 12; ++c) er[c] = fresh ? eta[sp + c * BS] : (odd ? vec2_t<S>{} : resid[sp + c * BS]);
-        if (a.mode != 0) face_consume<S, A>(a.g, b, bc, s, r, a.nrhs, faces, U, q);
-#pragma unroll
-        for (int c = 0; c < 12; ++c) rr[c] = ldc<A>(&er[c]) - q[c];
-
-        // the site's clover term (odd sites: the Cholesky factors of A_oo),
-        // half 1 in LDS
-        load_clover_half<A>(cp + 18 * BS, a.sig, cl);
+        load_clover_half<A>(cp + 18 * BS, SIG, cl);
+        if (a.mode == 2) clover_half_mac<A>(cl, diag, rr + 6, q + 6);
         if (odd) chol_half<A>(cl, diag);
 #pragma unroll
         for (int e = 0; e < 18; ++e) E.f1[e][tid] = cl[e];
-        if (odd) chol_solve<A>(cl, rr + 6);
-        load_clover_half<A>(cp, a.sig, cl);
+        load_clover_half<A>(cp, SIG, cl);
+        if (a.mode == 2) clover_half_mac<A>(cl, diag, rr, q);
+        if (odd) chol_half<A>(cl, diag);
+        // odd: q = A_oo psi_o + H_oe psi_e
+        if (a.mode == 2) eo_exchange<WRAP>(E, a.g, b, bc, s, U, !odd, rr, q);
+
+        vec2_t<S> er[12];
+#pragma unroll
+        for (int c = 0; c < 12; ++c) er[c] = eta[sp + c * BS];
+        if (a.mode != 0) face_consume<S, A>(a.g, b, bc, s, r, a.nrhs, faces, U, q);
         if (odd) {
-            chol_half<A>(cl, diag);
+            // rr = y_o, from here on delta_o; q = z_o
+#pragma unroll
+            for (int c = 0; c < 12; ++c) rr[c] = ldc<A>(&er[c]) - q[c];
+            cx<A> f[18];
+#pragma unroll
+            for (int e = 0; e < 18; ++e) f[e] = E.f1[e][tid];
             chol_solve<A>(cl, rr);
+            chol_solve<A>(f, rr + 6);
+#pragma unroll
+            for (int c = 0; c < 12; ++c) q[c] = a.mode == 2 ? rr[c] + ldc<A>(psi + sp + c * BS) : rr[c];
         }
-        // odd: rr = y_o, from here on delta_o; even: r_e = rho_e - H_eo y_o
-#pragma unroll
-        for (int c = 0; c < 12; ++c) q[c] = mk<A>(0, 0);
-        eo_exchange<WRAP>(E, a.g, b, bc, s, U, odd, rr, q);
+        // even: rr = r_e
+        if constexpr (AGAIN) asm volatile("" : "+s"(zero));
+        eo_exchange<WRAP>(E, a.g, b, bc, s, U, odd, q, q);
         if (!odd) {
+            if constexpr (AGAIN) {
 #pragma unroll
-            for (int c = 0; c < 12; ++c) rr[c] = rr[c] - q[c];
+                for (int c = 0; c < 12; ++c) er[c] = eta[sp + zero + c * BS];
+            }
+#pragma unroll
+            for (int c = 0; c < 12; ++c) rr[c] = ldc<A>(&er[c]) - q[c];
         }
 
         int it = 0;
@@ -347,24 +347,16 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(WAVES))) voi
             }
         }
 
-        // rr = delta; psi_B += delta; the residual carried to the next visit;
-        // the faces of delta (FP16: of psi as stored) for the other colour
-        if (!odd) {
-            if (CARRY && a.write_r) {
-#pragma unroll
-                for (int c = 0; c < 12; ++c) stc(resid + sp + c * BS, rr[c]);
-            }
-#pragma unroll
-            for (int c = 0; c < 12; ++c) rr[c] = it > 0 ? E.del[c][k] : mk<A>(0, 0);
-        }
+        // psi_B += delta and, for the other colour, its faces as stored
 #pragma unroll
         for (int c = 0; c < 12; ++c) {
             cx<A> v = rr[c];
+            if (!odd) v = it > 0 ? E.del[c][k] : mk<A>(0, 0);
             if (a.mode == 2) v = v + ldc<A>(psi + sp + c * BS);
             vec2_t<S> st;
             stc(&st, v);
             psi[sp + c * BS] = st;
-            if (!CARRY) rr[c] = ldc<A>(&st);
+            rr[c] = ldc<A>(&st);
         }
         if (a.publish) face_publish<S, A>(faces, b, a.nrhs, r, s, rr, U);
     }
@@ -403,22 +395,27 @@ Status sweep(dd_ctx *ctx, SArgs a, int prec, const void *eta, void *psi, void *f
 }
 
 template <typename S, typename A, int WAVES>
-Status sweep_eo(dd_ctx *ctx, SArgs a, int prec, const void *eta, void *psi, void *faces, void *resid, bool quiet)
+Status sweep_eo(dd_ctx *ctx, SArgs a, int prec, const void *eta, void *psi, void *faces, bool quiet)
 {
-    // recomputing the block residual costs one operator application when
-    // psi_B != 0; the right-hand side and the odd reconstruction one in-block
-    // hop application per block solve
-    constexpr bool CARRY = EO_CARRY<S>;
-    const double fl = 256.0 * a.nblk * a.nrhs * (a.nmr * 2184.0 + (!CARRY && a.mode == 2 ? 1848.0 : 0.0) + 1848.0);
+    // the block residual costs one operator application when psi_B != 0; the
+    // right-hand side and the odd reconstruction one in-block hop application
+    // per block solve
+    const double fl = 256.0 * a.nblk * a.nrhs * (a.nmr * 2184.0 + (a.mode == 2 ? 1848.0 : 0.0) + 1848.0);
     const int cls = prec == DD_F64 ? K_SAP_EO_F64 : prec == DD_F32 ? K_SAP_EO_F32 : K_SAP_EO_F16;
-    ProfScope ps(ctx->prof, ctx->stream, cls, sweep_bytes(a, sizeof(S), sizeof(S), CARRY), fl, !quiet);
+    ProfScope ps(ctx->prof, ctx->stream, cls, sweep_bytes(a, sizeof(S), sizeof(S), false), fl, !quiet);
     a.rpg = rhs_per_group(a.nblk, a.nrhs, ctx->ncu * WAVES);
     const bool wrap = a.g.nb[0] == 1 || a.g.nb[1] == 1 || a.g.nb[2] == 1 || a.g.nb[3] == 1;
-    auto kernel = wrap ? k_sap_sweep_eo<S, A, WAVES, true> : k_sap_sweep_eo<S, A, WAVES, false>;
+    // the form with wrap tests spills at two workgroups per CU: where there is
+    // at most one, its wavefronts have all registers (4x8x16x16, FP16, one
+    // right-hand side: 1089 -> 1043 us a call of twelve cycles)
+    const bool lone = (long)a.nblk * ((a.nrhs + a.rpg - 1) / a.rpg) <= ctx->ncu;
+    auto kernel = !wrap ? (a.sig ? k_sap_sweep_eo<S, A, WAVES, false, true> : k_sap_sweep_eo<S, A, WAVES, false, false>)
+                  : lone ? (a.sig ? k_sap_sweep_eo<S, A, 1, true, true> : k_sap_sweep_eo<S, A, 1, true, false>)
+                         : (a.sig ? k_sap_sweep_eo<S, A, WAVES, true, true> : k_sap_sweep_eo<S, A, WAVES, true, false>);
     kernel<<<dim3(a.nblk, (a.nrhs + a.rpg - 1) / a.rpg), BS, 0, ctx->stream>>>(
         static_cast<const vec2_t<S> *>(eta), static_cast<vec2_t<S> *>(psi),
         static_cast<const vec2_t<S> *>(ctx->links[prec].p), static_cast<const vec2_t<S> *>(ctx->clover[prec].p),
-        static_cast<vec2_t<S> *>(faces), static_cast<vec2_t<S> *>(resid), a);
+        static_cast<vec2_t<S> *>(faces), a);
     DD_HIP_TRY(hipGetLastError());
     return Status::ok();
 }
@@ -492,9 +489,9 @@ Status run_sap(dd_ctx *ctx, const double *m0, int nrhs, const void *eta, void *p
             a.publish = !(cy == ncy - 1 && col == 1);
             a.write_r = cy < ncy - 1;
             if (eo) {
-                DD_TRY((prec == DD_F64   ? sweep_eo<double, double, 1>(ctx, a, prec, eta, psi, faces, resid, quiet)
-                        : prec == DD_F32 ? sweep_eo<float, float, 2>(ctx, a, prec, eta, psi, faces, resid, quiet)
-                                         : sweep_eo<__half, float, 2>(ctx, a, prec, eta, psi, faces, resid, quiet)));
+                DD_TRY((prec == DD_F64   ? sweep_eo<double, double, 1>(ctx, a, prec, eta, psi, faces, quiet)
+                        : prec == DD_F32 ? sweep_eo<float, float, 2>(ctx, a, prec, eta, psi, faces, quiet)
+                                         : sweep_eo<__half, float, 2>(ctx, a, prec, eta, psi, faces, quiet)));
             } else {
                 DD_TRY((prec == DD_F64   ? sweep<double, double, double, 1>(ctx, a, prec, eta, psi, faces, resid, quiet)
                         : prec == DD_F16 ? sweep<__half, float, __half, 2>(ctx, a, prec, eta, psi, faces, resid, quiet)
