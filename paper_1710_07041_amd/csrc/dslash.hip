@@ -286,6 +286,12 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(DslashWaves<
 // right-hand side's faces, which two workgroups per CU cover for each other.
 // WRAP: some direction has a single block.  FAST: SU(3) links and a mirrored
 // clover term, the usual fields; the general form reads what it may need.
+// LAST: the clover term, the largest of the nine, is added after the hops, as in
+// the gather form and in the sums of FP64 and of FP32 with up to three
+// right-hand sides since ever: started from, every hop rounds at its size (FP32
+// 1.09e-7 against 9.7e-8, FP64 2.41e-16 against 2.20e-16).  FP32 with four and
+// more has always started from it, and the setup's interpolation, twelve
+// vectors at a time, magnifies a last bit.
 template <typename A, typename SF, bool FAST> struct DLds {
     cx<A> tf[6][BS]; // projected half spinors for the +t hops
     cx<A> tb[6][BS]; // U^+ times projected half spinors for the -t hops
@@ -293,7 +299,7 @@ template <typename A, typename SF, bool FAST> struct DLds {
     vec2_t<SF> fl[FAST ? 2 : 1][6][FAST ? BS : 1]; // two rows of the links of this thread's face hops
 };
 
-template <typename SI, typename SO, typename SF, typename A, int WAVES, bool WRAP, bool FAST, bool RESID>
+template <typename SI, typename SO, typename SF, typename A, int WAVES, bool WRAP, bool FAST, bool LAST, bool RESID>
 __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(WAVES))) void k_dslash_block(
     const vec2_t<SI> *__restrict__ in, vec2_t<SO> *__restrict__ out, const vec2_t<SF> *__restrict__ links,
     const vec2_t<SF> *__restrict__ clov, const vec2_t<SO> *__restrict__ resid, DArgs a)
@@ -360,25 +366,34 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(WAVES))) voi
         }
         blk_t_post_spin<0>(L, U[3], s, x, x + 6);
         blk_t_post_spin<1>(L, U[3], s, x, x + 6);
-        clover_half_mac<A, FAST>(cl, diag, x, q);
-        if constexpr (HOLD) {
-            clover_half_mac<A, FAST>(cl + 18, diag, x + 6, q + 6);
-        } else {
-            // the same for every right-hand side: hide that, or it is held in registers
-            int zero = 0;
-            asm volatile("" : "+s"(zero));
-            cx<A> c2[18];
+        cx<A> c2[HOLD ? 1 : 18];
+        const auto load_half1 = [&]() {
+            if constexpr (!HOLD) {
+                // the same for every right-hand side: hide that, or it is held in registers
+                int zero = 0;
+                asm volatile("" : "+s"(zero));
 #pragma unroll
-            for (int e = 0; e < 18; ++e)
-                if (clover_reads(FAST, e)) c2[e] = ldc<A>(cp + zero + (18 + e) * BS);
-            clover_half_mac<A, FAST>(c2, diag, x + 6, q + 6);
+                for (int e = 0; e < 18; ++e)
+                    if (clover_reads(FAST, e)) c2[e] = ldc<A>(cp + zero + (18 + e) * BS);
+            }
+        };
+        const auto site_term = [&]() {
+            clover_half_mac<A, FAST>(cl, diag, x, q);
+            if constexpr (HOLD) clover_half_mac<A, FAST>(cl + 18, diag, x + 6, q + 6);
+            else clover_half_mac<A, FAST>(c2, diag, x + 6, q + 6);
+        };
+        if constexpr (!LAST) {
+            load_half1();
+            site_term();
         }
         blk_hop<0, WRAP>(a.g, b, bc, s, U[0], x, x + 6, q, q + 6);
         blk_hop<1, WRAP>(a.g, b, bc, s, U[1], x, x + 6, q, q + 6);
         blk_hop<2, WRAP>(a.g, b, bc, s, U[2], x, x + 6, q, q + 6);
         __syncthreads();
+        if constexpr (LAST) load_half1();
         blk_t_take<WRAP>(L, a.g, b, bc, s, U[3], q, q + 6);
         face_gather(a.g, s, &L.fb[0][0][0], &L.fb[1][0][0], q);
+        if constexpr (LAST) site_term();
         if (RESID) {
 #pragma unroll
             for (int c = 0; c < 12; ++c) stc_stream(out + sp + c * BS, ldc_stream<A>(resid + sp + c * BS) - q[c]);
@@ -431,14 +446,14 @@ void launch_gather(dd_ctx *ctx, const DArgs &a, const void *in, void *out, int f
         static_cast<const vec2_t<SO> *>(resid), a);
 }
 
-template <typename SI, typename SO, typename SF, typename A, int WAVES, bool RESID>
+template <typename SI, typename SO, typename SF, typename A, int WAVES, bool LAST, bool RESID>
 void launch_block(dd_ctx *ctx, DArgs a, const void *in, void *out, int field_prec, const void *resid)
 {
     a.rpg = rhs_per_group(ctx->g.nblocks, a.nrhs, ctx->ncu * WAVES);
     const bool wrap = a.g.nb[0] == 1 || a.g.nb[1] == 1 || a.g.nb[2] == 1 || a.g.nb[3] == 1;
     const bool fast = a.r12 && a.sig;
-    auto kernel = wrap ? (fast ? k_dslash_block<SI, SO, SF, A, WAVES, true, true, RESID> : k_dslash_block<SI, SO, SF, A, WAVES, true, false, RESID>)
-                       : (fast ? k_dslash_block<SI, SO, SF, A, WAVES, false, true, RESID> : k_dslash_block<SI, SO, SF, A, WAVES, false, false, RESID>);
+    auto kernel = wrap ? (fast ? k_dslash_block<SI, SO, SF, A, WAVES, true, true, LAST, RESID> : k_dslash_block<SI, SO, SF, A, WAVES, true, false, LAST, RESID>)
+                       : (fast ? k_dslash_block<SI, SO, SF, A, WAVES, false, true, LAST, RESID> : k_dslash_block<SI, SO, SF, A, WAVES, false, false, LAST, RESID>);
     kernel<<<dim3(ctx->g.nblocks, (a.nrhs + a.rpg - 1) / a.rpg), BS, 0, ctx->stream>>>(
         static_cast<const vec2_t<SI> *>(in), static_cast<vec2_t<SO> *>(out),
         static_cast<const vec2_t<SF> *>(ctx->links[field_prec].p), static_cast<const vec2_t<SF> *>(ctx->clover[field_prec].p),
@@ -459,7 +474,8 @@ Status launch(dd_ctx *ctx, const DArgs &a, const void *in, void *out, int field_
     // workgroups per CU that the LDS buffers leave room for
     constexpr int WAVES = sizeof(A) == 8 ? 1 : 2;
     if (block_wise<SF>(ctx, a.nrhs)) {
-        launch_block<SI, SO, SF, A, WAVES, RESID>(ctx, a, in, out, field_prec, resid);
+        if (sizeof(SF) == 8 || (sizeof(SF) == 4 && a.nrhs < 4)) launch_block<SI, SO, SF, A, WAVES, sizeof(SF) != 2, RESID>(ctx, a, in, out, field_prec, resid);
+        else launch_block<SI, SO, SF, A, WAVES, sizeof(SF) == 8, RESID>(ctx, a, in, out, field_prec, resid);
     } else if constexpr (sizeof(SF) != 4) {
         if (a.nrhs == 1) launch_gather<SI, SO, SF, A, RESID, true>(ctx, a, in, out, field_prec, resid);
         else launch_gather<SI, SO, SF, A, RESID, false>(ctx, a, in, out, field_prec, resid);
