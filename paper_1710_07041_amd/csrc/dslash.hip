@@ -19,6 +19,8 @@
 #include "dd_device.h"
 #include "dd_internal.h"
 
+#include <type_traits>
+
 namespace dd {
 
 namespace {
@@ -213,12 +215,13 @@ template <typename SI, typename A> struct DslashWaves {
 // Gather form: one 256-thread workgroup per (block, right-hand side); those of
 // one block follow each other in the launch order, so the block's links and
 // clover terms are re-read from L2.  Streaming clover loads (NTC) only with a
-// single right-hand side.  (FP64 fields with several right-hand sides: lanes of
-// a wavefront that shared each link among two or four right-hand sides took
-// 573 us where this form takes 515, 24^3x48 and four, and 5240 where it takes
-// 4787, 32^3x64 and twelve: a wavefront then covers 16 or 32 sites, short of
-// whole 128-byte lines, and its in-block neighbours come from memory.)
-template <typename SI, typename SO, typename SF, typename A, bool BLOCKONLY, bool RESID, bool NTC>
+// single right-hand side.  SIG: 1 a mirrored clover term, 0 a full one, -1 as
+// a.sig says.  (FP64 fields with several right-hand sides: lanes of a wavefront
+// that shared each link among two or four right-hand sides took 573 us where
+// this form takes 519, 24^3x48 and four, and 5240 where it takes 4800, 32^3x64
+// and twelve: a wavefront then covers 16 or 32 sites, short of whole 128-byte
+// lines, and its in-block neighbours come from memory.)
+template <typename SI, typename SO, typename SF, typename A, bool BLOCKONLY, bool RESID, bool NTC, int SIG>
 __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(DslashWaves<SI, A>::value))) void k_dslash(
     const vec2_t<SI> *__restrict__ in, vec2_t<SO> *__restrict__ out, const vec2_t<SF> *__restrict__ links,
     const vec2_t<SF> *__restrict__ clov, const vec2_t<SO> *__restrict__ resid, DArgs a)
@@ -253,7 +256,7 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(DslashWaves<
     for (int k = 0; k < 2; ++k) {
         cx<A> cl[18];
         const vec2_t<SF> *cp = clov + ((long)b * 36 + 18 * k) * BS + s;
-        load_clover_half<A, NTC>(cp, a.sig, cl);
+        load_clover_half<A, NTC>(cp, SIG < 0 ? a.sig != 0 : SIG != 0, cl);
         cx<A> psi[6];
 #pragma unroll
         for (int c = 0; c < 6; ++c) psi[c] = ldc<A>(&stg[(6 * k + c) * BS + s]);
@@ -270,41 +273,53 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(DslashWaves<
     }
 }
 
-// Block-wise form: one workgroup
-// per Schwarz block (and group of a.rpg right-hand sides) holds the site's links
-// and clover term in registers for all of them and takes them one after the
-// other; the in-block hops go across lanes (t through LDS), the hops that leave
-// the block are computed two per thread (face_hop) and handed over through LDS.
-// A right-hand side then reads each spinor of the block once, a half more for
-// the neighbours' faces, and no link or clover term; the links of the face hops
-// wait in LDS.  Bound by the L2 before: with every right-hand side (or three)
-// fetching the links and clover terms of its hops anew, the 61 KB of face links
-// a workgroup needs kept falling out of the L2 -- 11.0 GB fetched for the 3.3 GB
-// that 32^3x64 with twelve right-hand sides needs in FP32, at a hit rate of 48%.
-// 32^3x64 FP32: 2378 -> 1785 us with twelve, 313 -> 279 with one; 24^3x48 FP16
-// with five: 281 -> 205.  Now bound by HBM and the memory latency of a
-// right-hand side's faces, which two workgroups per CU cover for each other.
-// WRAP: some direction has a single block.  FAST: SU(3) links and a mirrored
-// clover term, the usual fields; the general form reads what it may need.
+// Block-wise form: one workgroup per Schwarz block (and group of a.rpg
+// right-hand sides) holds the site's links and clover term in registers for all
+// of them and takes them one after the other; the in-block hops go across lanes
+// (t through LDS), the hops that leave the block are computed two per thread
+// (face_hop) and handed over through LDS.  A right-hand side then reads each
+// spinor of the block once, a half more for the neighbours' faces, and no link
+// or clover term; the links of the face hops wait in LDS.  Bound by the L2
+// before: with every right-hand side (or three) fetching the links and clover
+// terms of its hops anew, the 61 KB of face links a workgroup needs kept falling
+// out of the L2 -- 11.0 GB fetched for the 3.3 GB that 32^3x64 with twelve
+// right-hand sides needs in FP32, at a hit rate of 48%.  32^3x64 FP32: 2380 ->
+// 1790 us with twelve, 327 -> 279 with one; 24^3x48 FP16 with five: 281 -> 205.
+// Now bound by HBM and the memory latency of a right-hand side's faces, which
+// two workgroups per CU cover for each other.
+// WRAP: some direction has a single block.  R12: two rows a link; else a.r12
+// says.  SIG: a mirrored clover term; else all of it is read, half 1 anew for
+// each right-hand side (FP16 as stored, in registers).  RESID: out = resid - D in.
 // LAST: the clover term, the largest of the nine, is added after the hops, as in
 // the gather form and in the sums of FP64 and of FP32 with up to three
 // right-hand sides since ever: started from, every hop rounds at its size (FP32
 // 1.09e-7 against 9.7e-8, FP64 2.41e-16 against 2.20e-16).  FP32 with four and
 // more has always started from it, and the setup's interpolation, twelve
 // vectors at a time, magnifies a last bit.
-template <typename A, typename SF, bool FAST> struct DLds {
+// The links of a thread's two face hops: their first two rows and, with nine
+// entries, the third of as many as there is room for (ROWS3; the other's is read
+// again from the L2).  Nine entries, all read again for each right-hand side:
+// 32^3x64 FP32 with twelve 2840 us, 4x24^2x48 122; in LDS 1932 and 85.
+template <typename A, typename SF> struct DLds {
     cx<A> tf[6][BS]; // projected half spinors for the +t hops
     cx<A> tb[6][BS]; // U^+ times projected half spinors for the -t hops
     cx<A> fb[2][6][BS]; // transported half spinors of the face hops
-    vec2_t<SF> fl[FAST ? 2 : 1][6][FAST ? BS : 1]; // two rows of the links of this thread's face hops
+    vec2_t<SF> fl[2][6][BS];
+};
+template <typename SF, bool R12> constexpr int ROWS3 = R12 ? 0 : sizeof(SF) == 2 ? 2 : sizeof(SF) == 4 ? 1 : 0;
+template <typename A, typename SF, int N3> struct DLds3 : DLds<A, SF> {
+    vec2_t<SF> f3[N3][3][BS];
 };
 
-template <typename SI, typename SO, typename SF, typename A, int WAVES, bool WRAP, bool FAST, bool LAST, bool RESID>
+template <typename SI, typename SO, typename SF, typename A, int WAVES, bool WRAP, bool R12, bool SIG, bool LAST, bool RESID>
 __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(WAVES))) void k_dslash_block(
     const vec2_t<SI> *__restrict__ in, vec2_t<SO> *__restrict__ out, const vec2_t<SF> *__restrict__ links,
     const vec2_t<SF> *__restrict__ clov, const vec2_t<SO> *__restrict__ resid, DArgs a)
 {
-    __shared__ DLds<A, SF, FAST> L;
+    constexpr int N3 = ROWS3<SF, R12>;
+    __shared__ std::conditional_t<(N3 > 0), DLds3<A, SF, N3>, DLds<A, SF>> L;
+    const bool r12 = R12 || a.r12;
+    const int rend = min((int)(blockIdx.y + 1) * a.rpg, a.nrhs);
     const int b = xcd_remap(blockIdx.x, gridDim.x);
     const int s = threadIdx.x;
     int bc[4];
@@ -312,24 +327,34 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(WAVES))) voi
     const FaceHop h0 = face_hop(a.g, b, bc, s, 0), h1 = face_hop(a.g, b, bc, s, 1);
     const vec2_t<SF> *l0 = links + ((long)h0.lb * 4 + h0.mu) * 9 * BS + h0.ls;
     const vec2_t<SF> *l1 = links + ((long)h1.lb * 4 + h1.mu) * 9 * BS + h1.ls;
-    if constexpr (FAST) {
 #pragma unroll
-        for (int e = 0; e < 6; ++e) {
-            L.fl[0][e][s] = l0[e * BS];
-            L.fl[1][e][s] = l1[e * BS];
+    for (int e = 0; e < 6; ++e) {
+        L.fl[0][e][s] = l0[e * BS];
+        L.fl[1][e][s] = l1[e * BS];
+    }
+    if (!r12) {
+#pragma unroll
+        for (int e = 0; e < 3; ++e) {
+            if constexpr (N3 > 0) L.f3[0][e][s] = l0[(6 + e) * BS];
+            if constexpr (N3 > 1) L.f3[1][e][s] = l1[(6 + e) * BS];
         }
     }
     // register-resident links carry the hop factor -1/2
     cx<A> U[4][9];
-    load_links4<A>(links + (long)b * 4 * 9 * BS + s, a.r12, (A)(-0.5), U);
-    constexpr bool HOLD = FAST && sizeof(A) == 4; // both clover halves in registers
+    load_links4<A>(links + (long)b * 4 * 9 * BS + s, r12, (A)(-0.5), U);
+    constexpr bool HOLD = SIG && sizeof(A) == 4; // both clover halves in registers
+    constexpr bool RAW = !SIG && sizeof(SF) == 2; // half 1 as stored
     cx<A> cl[HOLD ? 36 : 18];
+    vec2_t<SF> c2[HOLD ? 1 : 18];
     const vec2_t<SF> *cp = clov + (long)b * 36 * BS + s;
 #pragma unroll
     for (int e = 0; e < (HOLD ? 36 : 18); ++e)
-        if (clover_reads(FAST, e % 18)) cl[e] = ldc<A>(cp + e * BS);
+        if (clover_reads(SIG, e % 18)) cl[e] = ldc<A>(cp + e * BS);
+    if constexpr (RAW) {
+#pragma unroll
+        for (int e = 0; e < 18; ++e) c2[e] = cp[(18 + e) * BS];
+    }
 
-    const int rend = min((int)(blockIdx.y + 1) * a.rpg, a.nrhs);
     for (int r = blockIdx.y * a.rpg; r < rend; ++r) {
         if (a.active && !a.active[r]) continue; // uniform over the workgroup
         const A diag = (A)(4.0 + (a.m0_dev ? a.m0_dev[r] : a.m0[r]));
@@ -349,12 +374,17 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(WAVES))) voi
             cx<A> W[9], w[12];
 #pragma unroll
             for (int c = 0; c < 12; ++c) w[c] = ldc<A>(pp + c * BS);
-            if constexpr (FAST) {
 #pragma unroll
-                for (int e = 0; e < 6; ++e) W[e] = ldc<A>(&L.fl[j][e][s]);
+            for (int e = 0; e < 6; ++e) W[e] = ldc<A>(&L.fl[j][e][s]);
+            if (r12) {
                 face_third_row(W);
             } else {
-                load_link<A>(j == 0 ? l0 : l1, a.r12, W);
+                const vec2_t<SF> *lj = (j == 0 ? l0 : l1) + 6 * BS;
+#pragma unroll
+                for (int e = 0; e < 3; ++e) {
+                    if constexpr (N3 > 0) W[6 + e] = j < N3 ? ldc<A>(&L.f3[j % N3][e][s]) : ldc<A>(lj + e * BS);
+                    else W[6 + e] = ldc<A>(lj + e * BS);
+                }
             }
             face_hop_post(h, w, W, s, L.fb[j]);
         }
@@ -366,21 +396,28 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(WAVES))) voi
         }
         blk_t_post_spin<0>(L, U[3], s, x, x + 6);
         blk_t_post_spin<1>(L, U[3], s, x, x + 6);
-        cx<A> c2[HOLD ? 1 : 18];
         const auto load_half1 = [&]() {
-            if constexpr (!HOLD) {
-                // the same for every right-hand side: hide that, or it is held in registers
+            if constexpr (!HOLD && !RAW) {
+                // the same for every right-hand side: hide that, or it is held
+                // in registers
                 int zero = 0;
                 asm volatile("" : "+s"(zero));
 #pragma unroll
                 for (int e = 0; e < 18; ++e)
-                    if (clover_reads(FAST, e)) c2[e] = ldc<A>(cp + zero + (18 + e) * BS);
+                    if (clover_reads(SIG, e)) c2[e] = cp[zero + (18 + e) * BS];
             }
         };
         const auto site_term = [&]() {
-            clover_half_mac<A, FAST>(cl, diag, x, q);
-            if constexpr (HOLD) clover_half_mac<A, FAST>(cl + 18, diag, x + 6, q + 6);
-            else clover_half_mac<A, FAST>(c2, diag, x + 6, q + 6);
+            clover_half_mac<A, SIG>(cl, diag, x, q);
+            if constexpr (HOLD) {
+                clover_half_mac<A, SIG>(cl + 18, diag, x + 6, q + 6);
+            } else {
+                cx<A> ch[18];
+#pragma unroll
+                for (int e = 0; e < 18; ++e)
+                    if (clover_reads(SIG, e)) ch[e] = ldc<A>(&c2[e]);
+                clover_half_mac<A, SIG>(ch, diag, x + 6, q + 6);
+            }
         };
         if constexpr (!LAST) {
             load_half1();
@@ -420,27 +457,37 @@ DArgs make_args(const dd_ctx *ctx, const double *m0, int nrhs)
     return a;
 }
 
-// Which form runs.  FP32 fields: block-wise at every size (one right-hand side
-// 8^4 12.1 -> 9.6 us, 24^3x48 90.8 -> 89.9; the gather form is not built).  FP16:
-// block-wise for two right-hand sides and more (24^3x48: two 95 -> 91 us, five
-// 281 -> 205); with one there is nothing to share and the gather form's four
-// waves per SIMD stream better on a large lattice (32^3x64: 173 us against 193).
-// FP64: the exchange buffers leave one workgroup per CU, which streams worse
-// than the gather form (24^3x48 with five: 707 us against 637).  On a lattice
-// whose workgroups all run within two rounds of the CUs latency is what counts,
-// and the gather form's eight serial round trips lose: FP64 8^4 12.5 against
-// 11.1 us, 16^4 20.7 against 18.0, 16^3x32 35.9 against 33.9 (two workgroups
-// per CU; at four, 16^2x32^2, 65.0 against 67.6), FP16 16^4 13.0 against 8.7.
-template <typename SF> bool block_wise(const dd_ctx *ctx, int nrhs)
+// Which form runs.  Block-wise where all its workgroups run at once (waves per
+// CU; FP64, one workgroup per CU, in two rounds), since latency is what counts
+// there and the gather form's eight serial round trips lose: FP64 8^4 12.9
+// against 11.2 us, 16^4 22.4 against 18.8, FP16 16^4 12.8 against 8.9, 4x24^2x48
+// 14.4 against 11.3.  Beyond that, several right-hand sides share the fields:
+// FP32 at every count, FP16 (24^3x48: two 94 -> 92 us, five 281 -> 205), not FP64,
+// where the exchange buffers leave one workgroup per CU, which streams worse
+// than the gather form (24^3x48 with five: 707 us against 637).  One alone:
+// block-wise in FP32 with a mirrored clover term (24^3x48 91.9 -> 90.4 us); with
+// an explicit one, re-read late, the gather form stays ahead (95.3 against 92.0),
+// as in FP16, where its four waves per SIMD stream better (32^3x64: 173 us
+// against 193).
+bool wraps(const Geom &g) { return g.nb[0] == 1 || g.nb[1] == 1 || g.nb[2] == 1 || g.nb[3] == 1; }
+template <typename SF> bool block_wise(const dd_ctx *ctx, const DArgs &a, int waves)
 {
-    if (sizeof(SF) == 4 || (sizeof(SF) == 2 && nrhs > 1)) return true;
-    return (long)ctx->g.nblocks * nrhs <= 2L * ctx->ncu;
+    if ((long)ctx->g.nblocks * a.nrhs <= 2L * ctx->ncu) return true;
+    return a.nrhs > 1 ? sizeof(SF) < 8 : sizeof(SF) == 4 && a.sig;
 }
 
 template <typename SI, typename SO, typename SF, typename A, bool RESID, bool NTC>
 void launch_gather(dd_ctx *ctx, const DArgs &a, const void *in, void *out, int field_prec, const void *resid)
 {
-    k_dslash<SI, SO, SF, A, false, RESID, NTC><<<ctx->g.nblocks * a.nrhs, BS, 0, ctx->stream>>>(
+    // FP64 fields test the clover term's form at run time; FP16 fields gain by
+    // not waiting for that (24^3x48: 59.1 -> 56.1 us, explicit 64.7 -> 57.4);
+    // FP32 fields come here with an explicit one only
+    constexpr int OTHER = sizeof(SF) == 8 ? -1 : 0;
+    auto kernel = k_dslash<SI, SO, SF, A, false, RESID, NTC, OTHER>;
+    if constexpr (sizeof(SF) == 2) {
+        if (a.sig) kernel = k_dslash<SI, SO, SF, A, false, RESID, NTC, 1>;
+    }
+    kernel<<<ctx->g.nblocks * a.nrhs, BS, 0, ctx->stream>>>(
         static_cast<const vec2_t<SI> *>(in), static_cast<vec2_t<SO> *>(out),
         static_cast<const vec2_t<SF> *>(ctx->links[field_prec].p), static_cast<const vec2_t<SF> *>(ctx->clover[field_prec].p),
         static_cast<const vec2_t<SO> *>(resid), a);
@@ -450,10 +497,14 @@ template <typename SI, typename SO, typename SF, typename A, int WAVES, bool LAS
 void launch_block(dd_ctx *ctx, DArgs a, const void *in, void *out, int field_prec, const void *resid)
 {
     a.rpg = rhs_per_group(ctx->g.nblocks, a.nrhs, ctx->ncu * WAVES);
-    const bool wrap = a.g.nb[0] == 1 || a.g.nb[1] == 1 || a.g.nb[2] == 1 || a.g.nb[3] == 1;
-    const bool fast = a.r12 && a.sig;
-    auto kernel = wrap ? (fast ? k_dslash_block<SI, SO, SF, A, WAVES, true, true, LAST, RESID> : k_dslash_block<SI, SO, SF, A, WAVES, true, false, LAST, RESID>)
-                       : (fast ? k_dslash_block<SI, SO, SF, A, WAVES, false, true, LAST, RESID> : k_dslash_block<SI, SO, SF, A, WAVES, false, false, LAST, RESID>);
+    // two rows a link and a mirrored clover term, nine entries, or any
+    auto pick = [&](auto wrap) {
+        constexpr bool WRAP = decltype(wrap)::value;
+        return !a.sig ? k_dslash_block<SI, SO, SF, A, WAVES, WRAP, false, false, LAST, RESID>
+               : a.r12 ? k_dslash_block<SI, SO, SF, A, WAVES, WRAP, true, true, LAST, RESID>
+                       : k_dslash_block<SI, SO, SF, A, WAVES, WRAP, false, true, LAST, RESID>;
+    };
+    auto kernel = wraps(a.g) ? pick(std::true_type{}) : pick(std::false_type{});
     kernel<<<dim3(ctx->g.nblocks, (a.nrhs + a.rpg - 1) / a.rpg), BS, 0, ctx->stream>>>(
         static_cast<const vec2_t<SI> *>(in), static_cast<vec2_t<SO> *>(out),
         static_cast<const vec2_t<SF> *>(ctx->links[field_prec].p), static_cast<const vec2_t<SF> *>(ctx->clover[field_prec].p),
@@ -473,12 +524,12 @@ Status launch(dd_ctx *ctx, const DArgs &a, const void *in, void *out, int field_
     ProfScope ps(ctx->prof, ctx->stream, cls, by, 1848.0 * V * n);
     // workgroups per CU that the LDS buffers leave room for
     constexpr int WAVES = sizeof(A) == 8 ? 1 : 2;
-    if (block_wise<SF>(ctx, a.nrhs)) {
+    if (block_wise<SF>(ctx, a, WAVES)) {
         if (sizeof(SF) == 8 || (sizeof(SF) == 4 && a.nrhs < 4)) launch_block<SI, SO, SF, A, WAVES, sizeof(SF) != 2, RESID>(ctx, a, in, out, field_prec, resid);
         else launch_block<SI, SO, SF, A, WAVES, sizeof(SF) == 8, RESID>(ctx, a, in, out, field_prec, resid);
-    } else if constexpr (sizeof(SF) != 4) {
-        if (a.nrhs == 1) launch_gather<SI, SO, SF, A, RESID, true>(ctx, a, in, out, field_prec, resid);
-        else launch_gather<SI, SO, SF, A, RESID, false>(ctx, a, in, out, field_prec, resid);
+    } else {
+        if (sizeof(SF) < 8 || a.nrhs == 1) launch_gather<SI, SO, SF, A, RESID, true>(ctx, a, in, out, field_prec, resid);
+        else launch_gather<SI, SO, SF, A, RESID, sizeof(SF) < 8>(ctx, a, in, out, field_prec, resid);
     }
     DD_HIP_TRY(hipGetLastError());
     return Status::ok();
@@ -515,15 +566,15 @@ Status launch_dslash_block(dd_ctx *ctx, double m0, int block_id, const void *in,
     a.block_id = block_id;
     ProfScope ps(ctx->prof, ctx->stream, K_DSLASH_BLOCK, 256.0 * (144.0 + 48.0) * real_bytes(prec), 1848.0 * 256);
     if (prec == DD_F64)
-        k_dslash<double, double, double, double, true, false, true><<<1, BS, 0, ctx->stream>>>(
+        k_dslash<double, double, double, double, true, false, true, -1><<<1, BS, 0, ctx->stream>>>(
             static_cast<const double2 *>(in), static_cast<double2 *>(out), ctx->links[DD_F64].as<double2>(),
             ctx->clover[DD_F64].as<double2>(), nullptr, a);
     else if (prec == DD_F32)
-        k_dslash<float, float, float, float, true, false, true><<<1, BS, 0, ctx->stream>>>(
+        k_dslash<float, float, float, float, true, false, true, -1><<<1, BS, 0, ctx->stream>>>(
             static_cast<const float2 *>(in), static_cast<float2 *>(out), ctx->links[DD_F32].as<float2>(),
             ctx->clover[DD_F32].as<float2>(), nullptr, a);
     else
-        k_dslash<__half, __half, __half, float, true, false, true><<<1, BS, 0, ctx->stream>>>(
+        k_dslash<__half, __half, __half, float, true, false, true, -1><<<1, BS, 0, ctx->stream>>>(
             static_cast<const __half2 *>(in), static_cast<__half2 *>(out), ctx->links[DD_F16].as<__half2>(),
             ctx->clover[DD_F16].as<__half2>(), nullptr, a);
     DD_HIP_TRY(hipGetLastError());
