@@ -458,9 +458,10 @@ DArgs make_args(const dd_ctx *ctx, const double *m0, int nrhs)
 }
 
 // Which form runs.  Block-wise where all its workgroups run at once (waves per
-// CU; FP64, one workgroup per CU, in two rounds), since latency is what counts
-// there and the gather form's eight serial round trips lose: FP64 8^4 12.9
-// against 11.2 us, 16^4 22.4 against 18.8, FP16 16^4 12.8 against 8.9, 4x24^2x48
+// CU), since latency is what counts there and the gather form's eight serial
+// round trips lose: FP64 8^4 12.9 against 11.2 us, 16^4 22.4 against 18.8 (one
+// workgroup per CU: a second round costs more than it gains, 4x16^3 with seven
+// right-hand sides 20.7 against 23.6), FP16 16^4 12.8 against 8.9, 4x24^2x48
 // 14.4 against 11.3.  Beyond that, several right-hand sides share the fields:
 // FP32 at every count, FP16 (24^3x48: two 94 -> 92 us, five 281 -> 205), not FP64,
 // where the exchange buffers leave one workgroup per CU, which streams worse
@@ -472,7 +473,7 @@ DArgs make_args(const dd_ctx *ctx, const double *m0, int nrhs)
 bool wraps(const Geom &g) { return g.nb[0] == 1 || g.nb[1] == 1 || g.nb[2] == 1 || g.nb[3] == 1; }
 template <typename SF> bool block_wise(const dd_ctx *ctx, const DArgs &a, int waves)
 {
-    if ((long)ctx->g.nblocks * a.nrhs <= 2L * ctx->ncu) return true;
+    if ((long)ctx->g.nblocks * a.nrhs <= (long)ctx->ncu * waves) return true;
     return a.nrhs > 1 ? sizeof(SF) < 8 : sizeof(SF) == 4 && a.sig;
 }
 
