@@ -320,6 +320,11 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(WAVES))) voi
     __shared__ std::conditional_t<(N3 > 0), DLds3<A, SF, N3>, DLds<A, SF>> L;
     const bool r12 = R12 || a.r12;
     const int rend = min((int)(blockIdx.y + 1) * a.rpg, a.nrhs);
+    if (a.active) {
+        bool any = false;
+        for (int r = blockIdx.y * a.rpg; r < rend; ++r) any |= a.active[r] != 0;
+        if (!any) return; // uniform: nothing to do
+    }
     const int b = xcd_remap(blockIdx.x, gridDim.x);
     const int s = threadIdx.x;
     int bc[4];
