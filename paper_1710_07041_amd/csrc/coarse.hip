@@ -492,7 +492,10 @@ struct GState {
     double cs[CK];
     double bnorm;
     int ncol;   // columns built so far
-    int closed; // the Krylov space closed (no further columns)
+    // the first step not to take: one past the step at which the Krylov space
+    // closed.  Step j tests it against j, so what that step sets while others
+    // are still to read it changes no test of the step itself.
+    int stop;
 };
 
 // The totals of values 0..count-1 over the CG group partials
@@ -600,7 +603,7 @@ __global__ __launch_bounds__(CTPB) void k_cg_init(const double2 *__restrict__ bv
         if (s == 0) {
             S.bnorm = nb;
             S.ncol = 0;
-            S.closed = nb > 0 ? 0 : 1;
+            S.stop = nb > 0 ? CK : 0;
             S.g[0] = make_double2(nb, 0);
         }
     }
@@ -645,7 +648,7 @@ __global__ __launch_bounds__(CTPB) void k_cg_dots(const double2 *__restrict__ V,
 {
     __shared__ Red R;
     const int r = blockIdx.y;
-    if ((a.active && !a.active[r]) || st[r].closed) return;
+    if ((a.active && !a.active[r]) || st[r].stop <= j) return;
     const long nrow = (long)a.nblocks * 2 * a.N;
     group_dots(R, V + (long)r * (kmax + 1) * nrow, w + (long)r * nrow, nrow, j, part, r, kmax + 1);
 }
@@ -660,7 +663,7 @@ __global__ __launch_bounds__(CTPB) void k_cg_orth(const double2 *__restrict__ V,
     __shared__ Red R, Rn;
     __shared__ double2 h[CK + 1];
     const int r = blockIdx.y, s = threadIdx.x;
-    if ((a.active && !a.active[r]) || st[r].closed) return;
+    if ((a.active && !a.active[r]) || st[r].stop <= j) return;
     const long nrow = (long)a.nblocks * 2 * a.N;
     group_totals(part, r, kmax + 1, j + 1, h);
     const double2 *Vr = V + (long)r * (kmax + 1) * nrow;
@@ -689,9 +692,7 @@ __global__ __launch_bounds__(CTPB) void k_cg_next(double2 *__restrict__ V, const
 {
     __shared__ double2 h[CK + 1], h1[CK + 1], tot[1];
     const int r = blockIdx.y, s = threadIdx.x;
-    // group 0 may set closed while others are still to start: they then have
-    // nothing to write, since this step's vector is not used
-    if ((a.active && !a.active[r]) || st[r].closed) return;
+    if ((a.active && !a.active[r]) || st[r].stop <= j) return;
     const long nrow = (long)a.nblocks * 2 * a.N;
     group_totals(partN, r, 1, 1, tot);
     group_totals(partB, r, kmax + 1, j + 1, h);
@@ -742,7 +743,7 @@ __global__ __launch_bounds__(CTPB) void k_cg_next(double2 *__restrict__ V, const
             stc(&S.g[j], c * gj);
             stc(&S.g[j + 1], mk<double>(0, 0) - conjx(sn) * gj);
             S.ncol = j + 1;
-            if (closes) S.closed = 1;
+            if (closes) S.stop = j + 1;
         }
     }
 }
@@ -765,11 +766,11 @@ template <int N2> constexpr int CT = (9 * N2 * CS<N2> + 63) / 64 * 64;        //
 template <int N2>
 __global__ __launch_bounds__(CT<N2>) void k_coarse_apply(const __half2 *__restrict__ Ah, const double2 *__restrict__ x,
                                                          long xs, double2 *__restrict__ y, long ys,
-                                                         const GState *__restrict__ st, CArgs a)
+                                                         const GState *__restrict__ st, CArgs a, int j)
 {
     __shared__ double2 X[CS<N2> * 9][N2]; // source vectors, then the partial sums
     const int r = blockIdx.y, t = threadIdx.x;
-    if ((a.active && !a.active[r]) || (st && st[r].closed)) return;
+    if ((a.active && !a.active[r]) || (st && st[r].stop <= j)) return;
     const int sd = t / N2, k = t - sd * N2; // block (site, direction) of the workgroup, row
     const int site = sd / 9, d = sd - 9 * site;
     const int b = blockIdx.x * CS<N2> + site;
@@ -803,10 +804,10 @@ __global__ __launch_bounds__(CT<N2>) void k_coarse_apply(const __half2 *__restri
 }
 
 void coarse_apply(const dd_ctx *ctx, int W, const __half2 *Ah, const double2 *x, long xs, double2 *y, long ys,
-                  const GState *S, const CArgs &a)
+                  const GState *S, const CArgs &a, int j)
 {
     switch (a.N) {
-#define DD_CA(n) case n: k_coarse_apply<2 * n><<<dim3((a.nblocks + CS<2 * n> - 1) / CS<2 * n>, W), CT<2 * n>, 0, ctx->stream>>>(Ah, x, xs, y, ys, S, a); break;
+#define DD_CA(n) case n: k_coarse_apply<2 * n><<<dim3((a.nblocks + CS<2 * n> - 1) / CS<2 * n>, W), CT<2 * n>, 0, ctx->stream>>>(Ah, x, xs, y, ys, S, a, j); break;
         DD_CA(1) DD_CA(2) DD_CA(3) DD_CA(4) DD_CA(5) DD_CA(6) DD_CA(7) DD_CA(8)
         DD_CA(9) DD_CA(10) DD_CA(11) DD_CA(12) DD_CA(13) DD_CA(14) DD_CA(15) DD_CA(16)
 #undef DD_CA
@@ -1019,7 +1020,7 @@ Status coarse_gmres(dd_ctx *ctx, AmgWork &wk, int W, int k, const double *m0_dev
     k_cg_init<<<grid, CTPB, 0, st>>>(wk.xb.as<double2>(), V, wk.partN.as<double2>(), S, a, kmax);
     for (int j = 0; j < k; ++j) {
         // w = (D_c + m0) v_j
-        coarse_apply(ctx, W, A.Ah.as<__half2>(), V + (long)j * nrow, (long)(kmax + 1) * nrow, w, nrow, S, a);
+        coarse_apply(ctx, W, A.Ah.as<__half2>(), V + (long)j * nrow, (long)(kmax + 1) * nrow, w, nrow, S, a, j);
         k_cg_dots<<<grid, CTPB, 0, st>>>(V, w, wk.partA.as<double2>(), S, a, kmax, j);
         k_cg_orth<<<grid, CTPB, 0, st>>>(V, w, wk.partA.as<double2>(), wk.partB.as<double2>(), wk.partN.as<double2>(), S, a, kmax, j);
         k_cg_next<<<grid, CTPB, 0, st>>>(V, w, wk.partA.as<double2>(), wk.partB.as<double2>(), wk.partN.as<double2>(), S, a, kmax, j);
@@ -1220,7 +1221,7 @@ Status amg_standalone(dd_ctx *ctx, int op, const double *m0, int nrhs, const voi
         break;
     case 2: // coarse apply
         coarse_apply(ctx, nrhs, A.Ah.as<__half2>(), static_cast<const double2 *>(in), (long)ncoarse(ctx),
-                     static_cast<double2 *>(out), (long)ncoarse(ctx), nullptr, a);
+                     static_cast<double2 *>(out), (long)ncoarse(ctx), nullptr, a, 0);
         break;
     case 3: // coarse solve with k steps
         DD_HIP_TRY(hipMemcpyAsync(wk.xb.p, in, cv, hipMemcpyDeviceToDevice, ctx->stream));
