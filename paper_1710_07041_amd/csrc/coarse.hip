@@ -490,7 +490,6 @@ struct GState {
     double2 g[CK + 1];
     double2 sn[CK];
     double cs[CK];
-    double bnorm;
     int ncol;   // columns built so far
     // the first step not to take: one past the step at which the Krylov space
     // closed.  Step j tests it against j, so what that step sets while others
@@ -601,7 +600,6 @@ __global__ __launch_bounds__(CTPB) void k_cg_init(const double2 *__restrict__ bv
         for (int e = s; e <= CK; e += CTPB) S.g[e] = make_double2(0, 0);
         __syncthreads();
         if (s == 0) {
-            S.bnorm = nb;
             S.ncol = 0;
             S.stop = nb > 0 ? CK : 0;
             S.g[0] = make_double2(nb, 0);
@@ -635,13 +633,17 @@ __device__ __forceinline__ void givens(cx<double> f, cx<double> g, double &c, cx
 // basis; a first Gram-Schmidt pass, with the dots and the norm of what it
 // leaves; a second pass, which also normalises.  The norm after the second
 // pass is |w|^2 - sum |h|^2 with the norm after the first and the second pass's
-// h (the basis is orthonormal, and those h are of rounding size, so nothing
-// cancels; where w is all rounding, the space has closed either way): the
-// vector needs no kernel of its own to be normalised.  Bound by the launches
-// (4.5 us each) and a chain of a few memory round trips.  Four kernels, partial
-// sums read across lines and one vector's dot after another took 32.5 us a step
-// at 24^3x48 (N = 12, sixteen steps) where this takes 23, and 28 us at 16^4 where
-// this takes 19; the preconditioner 2.83 -> 2.68 and 0.99 -> 0.87 ms.
+// h, so the vector needs no kernel of its own to be normalised: the basis is
+// orthonormal, and those h are the rounding of the first pass, a few eps
+// |D v_j|.  Where w itself is no longer than that (1e-14 |D v_j|) the space has
+// closed and the vector is not used; else they take little off |w|^2.  (Against
+// |b| the test depended on the right-hand side's scale: a tiny one went on with
+// vectors that were all rounding and not of length one, a huge one stopped at
+// once.)  Bound by the launches (4.5 us each) and a chain of a few memory round
+// trips.  Four kernels, partial sums read across lines and one vector's dot
+// after another took 32.5 us a step at 24^3x48 (N = 12, sixteen steps) where
+// this takes 23, and 28 us at 16^4 where this takes 19; the preconditioner
+// 2.83 -> 2.68 and 0.99 -> 0.87 ms.
 __global__ __launch_bounds__(CTPB) void k_cg_dots(const double2 *__restrict__ V, const double2 *__restrict__ w,
                                                   double2 *__restrict__ part, const GState *__restrict__ st, CArgs a,
                                                   int kmax, int j)
@@ -654,7 +656,8 @@ __global__ __launch_bounds__(CTPB) void k_cg_dots(const double2 *__restrict__ V,
 }
 
 // First pass: w -= sum_i h_i v_i (i <= j), h_i the totals of part; the partial
-// dots of the new w (partB) and of |w|^2 (partN).
+// dots of the new w (partB) and of |w|^2 (partN; group 0's imaginary part, else
+// zero, is sum |h_i|^2, so that the total is |w|^2 + i (|D v_j|^2 - |w|^2)).
 __global__ __launch_bounds__(CTPB) void k_cg_orth(const double2 *__restrict__ V, double2 *__restrict__ w,
                                                   const double2 *__restrict__ part, double2 *__restrict__ partB,
                                                   double2 *__restrict__ partN, const GState *__restrict__ st, CArgs a,
@@ -676,7 +679,10 @@ __global__ __launch_bounds__(CTPB) void k_cg_orth(const double2 *__restrict__ V,
         stc(wr + t, x);
         n2 += x.re * x.re + x.im * x.im;
     }
-    wave_put(Rn, s & 63, s >> 6, 0, n2, 0.0);
+    double hh = 0;
+    if (blockIdx.x == 0 && s == 0)
+        for (int i = 0; i <= j; ++i) hh += h[i].x * h[i].x + h[i].y * h[i].y;
+    wave_put(Rn, s & 63, s >> 6, 0, n2, hh);
     // the rows of this thread were written by this thread: no barrier needed
     group_dots(R, Vr, wr, nrow, j, partB, r, kmax + 1);
     if (s == 0) stc(partN + ((long)r * CG + blockIdx.x), wave_get(Rn, 0));
@@ -684,7 +690,7 @@ __global__ __launch_bounds__(CTPB) void k_cg_orth(const double2 *__restrict__ V,
 
 // Second pass, h the totals of partB: v_{j+1} = (w - sum_i h_i v_i) / beta;
 // group 0 sets column j of H, the totals of both passes, and rotates it; a
-// space that closed (beta tiny against |b|) stops growing.
+// space that closed (beta tiny against |D v_j|) stops growing.
 __global__ __launch_bounds__(CTPB) void k_cg_next(double2 *__restrict__ V, const double2 *__restrict__ w,
                                                   const double2 *__restrict__ partA, const double2 *__restrict__ partB,
                                                   const double2 *__restrict__ partN, GState *__restrict__ st, CArgs a,
@@ -699,7 +705,7 @@ __global__ __launch_bounds__(CTPB) void k_cg_next(double2 *__restrict__ V, const
     double n2 = tot[0].x;
     for (int i = 0; i <= j; ++i) n2 -= h[i].x * h[i].x + h[i].y * h[i].y;
     const double beta = n2 > 0 ? sqrt(n2) : n2 == n2 ? 0.0 : n2; // (a NaN stays one)
-    const bool closes = !(beta > 1e-14 * st[r].bnorm);
+    const bool closes = !(beta > 1e-14 * sqrt(tot[0].x + tot[0].y));
     if (!closes && j + 1 <= kmax) {
         const double inv = 1.0 / beta;
         double2 *Vr = V + (long)r * (kmax + 1) * nrow;

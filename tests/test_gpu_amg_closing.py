@@ -49,3 +49,10 @@ def solve_all(lat, scale, k):
 @pytest.mark.parametrize("k", [13, 32])
 def test_exhausted_space(lat, k):
     solve_all(lat, 1.0, k)
+
+
+@pytest.mark.parametrize("scale", [1e-12, 1e-6, 1e6, 1e16])
+def test_any_scale(lat, scale):
+    """The solution is linear in b: the step at which the space counts as
+    exhausted must not depend on |b|."""
+    solve_all(lat, scale, 16)
