@@ -269,31 +269,58 @@ __global__ __launch_bounds__(BS) void k_amg_build(const double2 *__restrict__ Pd
 // FP64 arithmetic, FP32 data with the FP32 copy in FP32 arithmetic.
 //
 // Bound by reading P (N spinors a block, 764 MB in FP32 at 24^3x48 and N = 12).
-// A thread takes two neighbouring sites of one chiral half, so P comes in
-// 16-byte loads (FP32; two of them in FP64), and RR right-hand sides, which
-// share them; the vectors go two at a time, the next two in flight meanwhile.
-// (P read once per right-hand side before: 16^3x32 FP32 with eight, restriction
-// 192 -> 85 us and prolongation 173 -> 63 us, the whole preconditioner 3.81 ->
-// 3.60 ms; 16^4 FP64 with four 2.29 -> 2.28.  One right-hand side, 24^3x48
-// FP32: 168 and 160 us either way.)
+// A thread takes two sites of one chiral half, neighbours in FP32 so that P comes
+// in 16-byte loads, and RR right-hand sides, which share them; FP32 takes two
+// vectors at a time and FP64, short of registers, one (two workgroups per CU with
+// RR = 2 instead of one), the next in flight meanwhile.  The groups of a block's
+// right-hand sides follow each other on one XCD and share its L2 (transfer_part).
+// Restriction / prolongation in us, P read for each right-hand side anew, then in
+// groups at a grid's length from each other, now: 24^3x48 FP32 with three
+// 416 / 511, 160 / 175, 161 / 175, with five 703 / 852, 300 / 370, 287 / 257;
+// FP64 with three 849 / 1018, 591 / 697, 340 / 378, with five 1396 / 1679,
+// 886 / 1048, 434 / 446; 16^4 FP64 with three 49 / 42, 62 / 65, 41 / 40; 8^4 FP32
+// with twelve 22 / 19, 26 / 22, 19 / 18.  One right-hand side: 24^3x48 FP32 159 /
+// 182, now 140 / 160; 16^3x32 37 / 36, now 39 / 37.
 template <typename S> using PT = vec2_t<S>;
-template <typename S> struct alignas(2 * sizeof(vec2_t<S>) > 16 ? 16 : 2 * sizeof(vec2_t<S>)) Pair {
+template <typename S> struct alignas(16) Pair {
     vec2_t<S> e[2];
 };
-// right-hand sides that share a read of P, as many as registers hold
+// the two sites of thread h (0..127) of a chiral half
+template <typename S> __device__ __forceinline__ int pair_site(int h, int k) { return sizeof(S) == 4 ? 2 * h + k : h + (BS / 2) * k; }
+// right-hand sides that share a read of P, as many as registers hold (a group
+// past the last repeats the last one's reads: 24^3x48 FP32, three 161 us, four 168)
 template <typename S> constexpr int rr_max() { return sizeof(S) == 4 ? 4 : 2; }
+// vectors taken at a time
+template <typename S> constexpr int PU = sizeof(S) == 4 ? 2 : 1;
 
-template <typename S, bool NT> __device__ __forceinline__ void load_p(const Pair<S> *__restrict__ p, Pair<S> q[6])
+// six components of a vector at the thread's two sites
+template <typename S, bool NT> __device__ __forceinline__ void load_p(const PT<S> *__restrict__ p, int h, Pair<S> q[6])
 {
 #pragma unroll
     for (int x = 0; x < 6; ++x) {
-        if (NT) {
-            q[x].e[0] = ld_stream(&p[x * (BS / 2)].e[0]);
-            q[x].e[1] = ld_stream(&p[x * (BS / 2)].e[1]);
+        if constexpr (sizeof(S) == 4 && !NT) {
+            q[x] = *reinterpret_cast<const Pair<S> *>(p + x * BS + 2 * h);
         } else {
-            q[x] = p[x * (BS / 2)];
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                const PT<S> *e = p + x * BS + pair_site<S>(h, k);
+                q[x].e[k] = NT ? ld_stream(e) : *e;
+            }
         }
     }
+}
+
+// The block and the group of right-hand sides of this workgroup.  The groups of
+// a block follow each other on one XCD (workgroups go to the XCDs in turn), so
+// the block's P comes from its L2 for all but the first.  False past the last
+// block (the launch rounds them up to whole turns).
+constexpr int NXCD = 8;
+__device__ __forceinline__ bool transfer_part(int nblocks, int ngroups, int &b, int &grp)
+{
+    const int t = blockIdx.x / NXCD;
+    grp = t % ngroups;
+    b = t / ngroups * NXCD + blockIdx.x % NXCD;
+    return b < nblocks;
 }
 
 template <typename S, int RR, bool NT>
@@ -302,32 +329,37 @@ __global__ __launch_bounds__(BS) void k_amg_restrict(const vec2_t<S> *__restrict
                                                      int nblocks, int W)
 {
     __shared__ double part[4][RR][NMAX][2];
-    const int b = blockIdx.x, r0 = blockIdx.y * RR, s = threadIdx.x, lane = s & 63;
+    int b, grp;
+    if (!transfer_part(nblocks, (W + RR - 1) / RR, b, grp)) return;
+    const int r0 = grp * RR, s = threadIdx.x, lane = s & 63;
     const int wave = __builtin_amdgcn_readfirstlane(s >> 6), c = wave >> 1, h = s & 127;
     bool on = false;
 #pragma unroll
     for (int rr = 0; rr < RR; ++rr) on |= r0 + rr < W && (!active || active[r0 + rr]);
     if (!on) return; // uniform
-    const Pair<S> *p = reinterpret_cast<const Pair<S> *>(P + pidx(b, c, 0, N, 0, 0)) + h;
-    Pair<S> q[2][6], qn[2][6];
-    load_p<S, NT>(p, q[0]);
-    if (N > 1) load_p<S, NT>(p + 6 * (BS / 2), q[1]);
+    const PT<S> *p = P + pidx(b, c, 0, N, 0, 0);
+    constexpr int U = PU<S>;
+    Pair<S> q[U][6], qn[U][6];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+        if (u < N) load_p<S, NT>(p + u * 6 * BS, h, q[u]);
     cx<S> v[RR][6][2];
 #pragma unroll
     for (int rr = 0; rr < RR; ++rr) {
         // a slot past the last repeats the last; its sums are not stored
-        const vec2_t<S> *e = in + ((long)b * W + min(r0 + rr, W - 1)) * 12 * BS + 6 * c * BS + 2 * h;
+        const vec2_t<S> *e = in + ((long)b * W + min(r0 + rr, W - 1)) * 12 * BS + 6 * c * BS;
 #pragma unroll
         for (int x = 0; x < 6; ++x)
 #pragma unroll
-            for (int k = 0; k < 2; ++k) v[rr][x][k] = ldc<S>(e + x * BS + k);
+            for (int k = 0; k < 2; ++k) v[rr][x][k] = ldc<S>(e + x * BS + pair_site<S>(h, k));
     }
 #pragma unroll 1
-    for (int i = 0; i < N; i += 2) {
-        if (i + 2 < N) load_p<S, NT>(p + (long)(i + 2) * 6 * (BS / 2), qn[0]);
-        if (i + 3 < N) load_p<S, NT>(p + (long)(i + 3) * 6 * (BS / 2), qn[1]);
+    for (int i = 0; i < N; i += U) {
 #pragma unroll
-        for (int u = 0; u < 2; ++u) {
+        for (int u = 0; u < U; ++u)
+            if (i + U + u < N) load_p<S, NT>(p + (long)(i + U + u) * 6 * BS, h, qn[u]);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
             if (i + u < N) {
 #pragma unroll
                 for (int rr = 0; rr < RR; ++rr) {
@@ -349,7 +381,7 @@ __global__ __launch_bounds__(BS) void k_amg_restrict(const vec2_t<S> *__restrict
             }
         }
 #pragma unroll
-        for (int u = 0; u < 2; ++u)
+        for (int u = 0; u < U; ++u)
 #pragma unroll
             for (int x = 0; x < 6; ++x) q[u][x] = qn[u][x];
     }
@@ -369,16 +401,20 @@ __global__ __launch_bounds__(BS) void k_amg_prolong(const double2 *__restrict__ 
                                                     const int *__restrict__ active, int N, int nblocks, int W)
 {
     __shared__ cx<S> xs[RR][2 * NMAX];
-    const int b = blockIdx.x, r0 = blockIdx.y * RR, s = threadIdx.x;
+    int b, grp;
+    if (!transfer_part(nblocks, (W + RR - 1) / RR, b, grp)) return;
+    const int r0 = grp * RR, s = threadIdx.x;
     const int c = __builtin_amdgcn_readfirstlane(s >> 7), h = s & 127;
     bool on = false;
 #pragma unroll
     for (int rr = 0; rr < RR; ++rr) on |= r0 + rr < W && (!active || active[r0 + rr]);
     if (!on) return; // uniform
-    const Pair<S> *p = reinterpret_cast<const Pair<S> *>(P + pidx(b, c, 0, N, 0, 0)) + h;
-    Pair<S> q[2][6], qn[2][6];
-    load_p<S, NT>(p, q[0]);
-    if (N > 1) load_p<S, NT>(p + 6 * (BS / 2), q[1]);
+    const PT<S> *p = P + pidx(b, c, 0, N, 0, 0);
+    constexpr int U = PU<S>;
+    Pair<S> q[U][6], qn[U][6];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+        if (u < N) load_p<S, NT>(p + u * 6 * BS, h, q[u]);
     if (s < 2 * N * RR) {
         const int rr = s / (2 * N), k = s - rr * 2 * N;
         xs[rr][k] = ldc<S>(xc + ((long)min(r0 + rr, W - 1) * nblocks + b) * 2 * N + k);
@@ -390,11 +426,12 @@ __global__ __launch_bounds__(BS) void k_amg_prolong(const double2 *__restrict__ 
 #pragma unroll
         for (int x = 0; x < 6; ++x) acc[rr][x][0] = acc[rr][x][1] = mk<S>(0, 0);
 #pragma unroll 1
-    for (int i = 0; i < N; i += 2) {
-        if (i + 2 < N) load_p<S, NT>(p + (long)(i + 2) * 6 * (BS / 2), qn[0]);
-        if (i + 3 < N) load_p<S, NT>(p + (long)(i + 3) * 6 * (BS / 2), qn[1]);
+    for (int i = 0; i < N; i += U) {
 #pragma unroll
-        for (int u = 0; u < 2; ++u) {
+        for (int u = 0; u < U; ++u)
+            if (i + U + u < N) load_p<S, NT>(p + (long)(i + U + u) * 6 * BS, h, qn[u]);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
             if (i + u < N) {
 #pragma unroll
                 for (int rr = 0; rr < RR; ++rr) {
@@ -407,7 +444,7 @@ __global__ __launch_bounds__(BS) void k_amg_prolong(const double2 *__restrict__ 
             }
         }
 #pragma unroll
-        for (int u = 0; u < 2; ++u)
+        for (int u = 0; u < U; ++u)
 #pragma unroll
             for (int x = 0; x < 6; ++x) q[u][x] = qn[u][x];
     }
@@ -415,11 +452,11 @@ __global__ __launch_bounds__(BS) void k_amg_prolong(const double2 *__restrict__ 
     for (int rr = 0; rr < RR; ++rr) {
         const int r = r0 + rr;
         if (r >= W || (active && !active[r])) continue; // uniform
-        vec2_t<S> *o = out + (off ? off[r] : 0) + ((long)b * W + r) * 12 * BS + 6 * c * BS + 2 * h;
+        vec2_t<S> *o = out + (off ? off[r] : 0) + ((long)b * W + r) * 12 * BS + 6 * c * BS;
 #pragma unroll
         for (int x = 0; x < 6; ++x)
 #pragma unroll
-            for (int k = 0; k < 2; ++k) stc(o + x * BS + k, acc[rr][x][k]);
+            for (int k = 0; k < 2; ++k) stc(o + x * BS + pair_site<S>(h, k), acc[rr][x][k]);
     }
 }
 
@@ -435,31 +472,46 @@ template <typename S> bool p_streams(int nb, int N)
 template <typename S, int RR>
 void restrict_rr(int nb, int W, hipStream_t st, const void *in, const DevBuf &P, void *xc, const int *active, int N)
 {
-    (p_streams<S>(nb, N) ? k_amg_restrict<S, RR, sizeof(S) == 4> : k_amg_restrict<S, RR, false>)<<<dim3(nb, (W + RR - 1) / RR), BS, 0, st>>>(
+    (p_streams<S>(nb, N) ? k_amg_restrict<S, RR, sizeof(S) == 4> : k_amg_restrict<S, RR, false>)<<<(nb + NXCD - 1) / NXCD * NXCD * ((W + RR - 1) / RR), BS, 0, st>>>(
         static_cast<const vec2_t<S> *>(in), static_cast<const vec2_t<S> *>(P.p), static_cast<double2 *>(xc), active, N, nb, W);
 }
 template <typename S, int RR>
 void prolong_rr(int nb, int W, hipStream_t st, const void *xc, const DevBuf &P, void *out, const long *off, const int *active,
                 int N)
 {
-    (p_streams<S>(nb, N) ? k_amg_prolong<S, RR, sizeof(S) == 4> : k_amg_prolong<S, RR, false>)<<<dim3(nb, (W + RR - 1) / RR), BS, 0, st>>>(
+    (p_streams<S>(nb, N) ? k_amg_prolong<S, RR, sizeof(S) == 4> : k_amg_prolong<S, RR, false>)<<<(nb + NXCD - 1) / NXCD * NXCD * ((W + RR - 1) / RR), BS, 0, st>>>(
         static_cast<const double2 *>(xc), static_cast<const vec2_t<S> *>(P.p), static_cast<vec2_t<S> *>(out), off, active, N,
         nb, W);
 }
+// Right-hand sides per workgroup: as few as keep the workgroups to two per CU
+// (waiting for each other's sums costs a lone workgroup more than the reads that
+// it shares), else as many as registers hold.
+template <typename S> int rr_of(const dd_ctx *ctx, int W)
+{
+    for (int rr = 1; rr < rr_max<S>(); rr *= 2)
+        if (W <= rr || (long)ctx->g.nblocks * ((W + rr - 1) / rr) <= 2L * ctx->ncu) return rr;
+    return rr_max<S>();
+}
+
 // x_c = P^+ in and out = P x_c
 template <typename S>
-void amg_restrict(int nb, int W, hipStream_t st, const void *in, const DevBuf &P, void *xc, const int *active, int N)
+void amg_restrict(const dd_ctx *ctx, int W, const void *in, const DevBuf &P, void *xc, const int *active, int N)
 {
-    if (W == 1) restrict_rr<S, 1>(nb, W, st, in, P, xc, active, N);
-    else if (W == 2) restrict_rr<S, 2>(nb, W, st, in, P, xc, active, N);
+    const int nb = ctx->g.nblocks;
+    hipStream_t st = ctx->stream;
+    const int rr = rr_of<S>(ctx, W);
+    if (rr == 1) restrict_rr<S, 1>(nb, W, st, in, P, xc, active, N);
+    else if (rr == 2) restrict_rr<S, 2>(nb, W, st, in, P, xc, active, N);
     else restrict_rr<S, rr_max<S>()>(nb, W, st, in, P, xc, active, N);
 }
 template <typename S>
-void amg_prolong(int nb, int W, hipStream_t st, const void *xc, const DevBuf &P, void *out, const long *off, const int *active,
-                 int N)
+void amg_prolong(const dd_ctx *ctx, int W, const void *xc, const DevBuf &P, void *out, const long *off, const int *active, int N)
 {
-    if (W == 1) prolong_rr<S, 1>(nb, W, st, xc, P, out, off, active, N);
-    else if (W == 2) prolong_rr<S, 2>(nb, W, st, xc, P, out, off, active, N);
+    const int nb = ctx->g.nblocks;
+    hipStream_t st = ctx->stream;
+    const int rr = rr_of<S>(ctx, W);
+    if (rr == 1) prolong_rr<S, 1>(nb, W, st, xc, P, out, off, active, N);
+    else if (rr == 2) prolong_rr<S, 2>(nb, W, st, xc, P, out, off, active, N);
     else prolong_rr<S, rr_max<S>()>(nb, W, st, xc, P, out, off, active, N);
 }
 
@@ -1057,9 +1109,9 @@ Status run_two_grid(dd_ctx *ctx, AmgWork &wk, int W, const void *eta, const long
     {
         ProfScope ps(ctx->prof, st, K_AMG_RESTRICT, (double)spinor_bytes(ctx->g, prec, W) * (1 + N), 0.0);
         if (prec == DD_F64)
-            amg_restrict<double>(nb, W, st, e, A.Pd, wk.xb.p, active, N);
+            amg_restrict<double>(ctx, W, e, A.Pd, wk.xb.p, active, N);
         else
-            amg_restrict<float>(nb, W, st, e, A.Pf, wk.xb.p, active, N);
+            amg_restrict<float>(ctx, W, e, A.Pf, wk.xb.p, active, N);
     }
     {
         ProfScope ps(ctx->prof, st, K_AMG_COARSE, 0.0, 0.0);
@@ -1071,8 +1123,8 @@ Status run_two_grid(dd_ctx *ctx, AmgWork &wk, int W, const void *eta, const long
         ProfScope ps(ctx->prof, st, K_AMG_PROLONG, (double)spinor_bytes(ctx->g, prec, W) * (1 + N), 0.0);
         void *psi = post ? wk.ps.p : z;
         const long *off = post ? nullptr : z_off;
-        if (prec == DD_F64) amg_prolong<double>(nb, W, st, wk.xx.p, A.Pd, psi, off, active, N);
-        else amg_prolong<float>(nb, W, st, wk.xx.p, A.Pf, psi, off, active, N);
+        if (prec == DD_F64) amg_prolong<double>(ctx, W, wk.xx.p, A.Pd, psi, off, active, N);
+        else amg_prolong<float>(ctx, W, wk.xx.p, A.Pf, psi, off, active, N);
     }
     DD_HIP_TRY(hipGetLastError());
     if (!post) return Status::ok();
@@ -1209,21 +1261,21 @@ Status amg_standalone(dd_ctx *ctx, int op, const double *m0, int nrhs, const voi
     if (m0) masses.assign(m0, m0 + nrhs);
     DD_HIP_TRY(hipMemcpyAsync(wk.m0.p, masses.data(), nrhs * sizeof(double), hipMemcpyHostToDevice, ctx->stream));
     DD_HIP_TRY(hipStreamSynchronize(ctx->stream)); // masses is a host temporary
-    const int N = A.N, nb = ctx->g.nblocks;
+    const int N = A.N;
     const size_t cv = ncoarse(ctx) * 16 * nrhs;
     const CArgs a = cargs(ctx, nrhs, wk.m0.as<double>(), nullptr);
     switch (op) {
     case 0: // restrict: out (coarse) = P^+ in
         if (prec == DD_F64)
-            amg_restrict<double>(nb, nrhs, ctx->stream, in, A.Pd, out, nullptr, N);
+            amg_restrict<double>(ctx, nrhs, in, A.Pd, out, nullptr, N);
         else
-            amg_restrict<float>(nb, nrhs, ctx->stream, in, A.Pf, out, nullptr, N);
+            amg_restrict<float>(ctx, nrhs, in, A.Pf, out, nullptr, N);
         break;
     case 1: // prolong: out (fine) = P in
         if (prec == DD_F64)
-            amg_prolong<double>(nb, nrhs, ctx->stream, in, A.Pd, out, nullptr, nullptr, N);
+            amg_prolong<double>(ctx, nrhs, in, A.Pd, out, nullptr, nullptr, N);
         else
-            amg_prolong<float>(nb, nrhs, ctx->stream, in, A.Pf, out, nullptr, nullptr, N);
+            amg_prolong<float>(ctx, nrhs, in, A.Pf, out, nullptr, nullptr, N);
         break;
     case 2: // coarse apply
         coarse_apply(ctx, nrhs, A.Ah.as<__half2>(), static_cast<const double2 *>(in), (long)ncoarse(ctx),
