@@ -260,9 +260,11 @@ __global__ __launch_bounds__(TPB) void k_convert_from64(const double2 *__restric
 // through LDS: entry e of the block in canonical order is component e % 12 of
 // the run's site (e / 12) % 4, and thread t takes entries t, t + 256, ..., so
 // both sides move 16-byte (blocked: one complex number) contiguous accesses.
-// Without LDS each thread took its own site's 192 B, i.e. 16 B out of every
-// 192 per instruction: 24^3x48, twelve right-hand sides, FP32 in and out
-// 1076 us, now 778 us (5.9 TB/s; a plain streaming copy reaches 5.8).
+// Without LDS a wavefront takes 16 B out of every 192: pack and unpack of twelve
+// right-hand sides at 24^3x48, FP32, 425 + 641 us, now 383 + 418 (5.7 TB/s; a
+// plain streaming copy reaches 5.8).  pack reads past the caches (NT) where input
+// and output outgrow the 256 MB in front of HBM (12 x 24^3x48 FP32 424 -> 383 us);
+// below, the input may still lie there (one right-hand side 32.9 -> 28.5 us).
 // LROW: the component stride in LDS, padded so that the twelve components of
 // four neighbouring sites (consecutive lanes) fall on different banks.
 constexpr int LROW = BS + 4;
@@ -279,7 +281,7 @@ __device__ __forceinline__ long tile_entry(const CanonGeom &g, int b, int e, int
     return canon_site(g, b, s) * 12 + c;
 }
 
-template <typename S>
+template <typename S, bool NT>
 __global__ __launch_bounds__(TPB) void k_spinor_pack(const double2 *__restrict__ in, vec2_t<S> *__restrict__ out,
                                                      CanonGeom g, int nrhs, long V, int width, int slot0,
                                                      int *__restrict__ nonzero)
@@ -290,7 +292,10 @@ __global__ __launch_bounds__(TPB) void k_spinor_pack(const double2 *__restrict__
     double2 v[12];
     int s, c;
 #pragma unroll
-    for (int k = 0; k < 12; ++k) v[k] = ld_stream(src + tile_entry(g, b, k * TPB + t, s, c));
+    for (int k = 0; k < 12; ++k) {
+        const double2 *p = src + tile_entry(g, b, k * TPB + t, s, c);
+        v[k] = NT ? ld_stream(p) : *p;
+    }
     bool nz = false;
 #pragma unroll
     for (int k = 0; k < 12; ++k) {
@@ -303,7 +308,31 @@ __global__ __launch_bounds__(TPB) void k_spinor_pack(const double2 *__restrict__
     __syncthreads();
     vec2_t<S> *dst = out + ((long)b * width + slot0 + r) * 12 * BS + t;
 #pragma unroll
-    for (int k = 0; k < 12; ++k) dst[(long)k * BS] = T.v[k][t];
+    for (int k = 0; k < 12; ++k) {
+        if (NT) st_stream(dst + (long)k * BS, T.v[k][t]);
+        else dst[(long)k * BS] = T.v[k][t];
+    }
+}
+
+// The same, a thread taking its own site's 192 B, without LDS: shorter where a
+// CU has two workgroups at most and the trip through LDS is what takes the time
+// (8^4 with three right-hand sides in FP16 6.1 -> 4.3 us, 4x16x24x48 7.5 -> 5.9).
+template <typename S>
+__global__ __launch_bounds__(TPB) void k_spinor_pack_sites(const double2 *__restrict__ in, vec2_t<S> *__restrict__ out,
+                                                           CanonGeom g, int nrhs, long V, int width, int slot0,
+                                                           int *__restrict__ nonzero)
+{
+    const int b = blockIdx.x / nrhs, r = blockIdx.x % nrhs, t = threadIdx.x;
+    const double2 *src = in + ((long)r * V + canon_site(g, b, t)) * 12;
+    vec2_t<S> *dst = out + ((long)b * width + slot0 + r) * 12 * BS + t;
+    bool nz = false;
+#pragma unroll
+    for (int c = 0; c < 12; ++c) {
+        const double2 v = src[c];
+        nz |= v.x != 0.0 || v.y != 0.0;
+        stc(dst + (long)c * BS, mk<double>(v.x, v.y));
+    }
+    if (nonzero && __any(nz) && (t % 64) == 0) atomicOr(nonzero, 1);
 }
 
 template <typename S>
@@ -429,10 +458,15 @@ Status set_clover_canon(dd_ctx *ctx, const double *C_dev)
 namespace {
 
 template <typename S>
-void launch_pack(hipStream_t st, const GeomHost &g, const double *in, void *out, int nrhs, int width, int slot0, int *nonzero)
+void launch_pack(const dd_ctx *ctx, hipStream_t st, const double *in, void *out, int nrhs, int width, int slot0, int *nonzero)
 {
-    k_spinor_pack<S><<<g.nblocks * nrhs, TPB, 0, st>>>(reinterpret_cast<const double2 *>(in), static_cast<vec2_t<S> *>(out),
-                                                       canon_geom(g), nrhs, g.V, width, slot0, nonzero);
+    const GeomHost &g = ctx->g;
+    const int wgs = g.nblocks * nrhs;
+    // (reasons at the kernels)
+    const bool few = wgs <= 2 * ctx->ncu, streams = (size_t)wgs * 12 * BS * (16 + sizeof(vec2_t<S>)) > (256u << 20);
+    auto kernel = few ? k_spinor_pack_sites<S> : streams ? k_spinor_pack<S, true> : k_spinor_pack<S, false>;
+    kernel<<<wgs, TPB, 0, st>>>(reinterpret_cast<const double2 *>(in), static_cast<vec2_t<S> *>(out), canon_geom(g), nrhs, g.V,
+                                width, slot0, nonzero);
 }
 template <typename S>
 void launch_unpack(hipStream_t st, const GeomHost &g, const void *in, double *out, int nrhs, int width, int slot0)
@@ -447,9 +481,9 @@ Status pack_spinor(dd_ctx *ctx, const double *canon, void *blocked, int prec, in
 {
     const GeomHost &g = ctx->g;
     ProfScope ps(ctx->prof, ctx->stream, K_PACK, (double)g.V * nrhs * 24.0 * (8 + real_bytes(prec)), 0.0);
-    if (prec == DD_F64) launch_pack<double>(ctx->stream, g, canon, blocked, nrhs, nrhs, 0, nullptr);
-    else if (prec == DD_F32) launch_pack<float>(ctx->stream, g, canon, blocked, nrhs, nrhs, 0, nullptr);
-    else launch_pack<__half>(ctx->stream, g, canon, blocked, nrhs, nrhs, 0, nullptr);
+    if (prec == DD_F64) launch_pack<double>(ctx, ctx->stream, canon, blocked, nrhs, nrhs, 0, nullptr);
+    else if (prec == DD_F32) launch_pack<float>(ctx, ctx->stream, canon, blocked, nrhs, nrhs, 0, nullptr);
+    else launch_pack<__half>(ctx, ctx->stream, canon, blocked, nrhs, nrhs, 0, nullptr);
     DD_HIP_TRY(hipGetLastError());
     return Status::ok();
 }
@@ -468,7 +502,7 @@ Status unpack_spinor(dd_ctx *ctx, const void *blocked, double *canon, int prec, 
 Status pack_slot(dd_ctx *ctx, hipStream_t st, const double *canon, void *blocked, int width, int slot, int *nonzero)
 {
     ProfScope ps(ctx->prof, st, K_PACK, (double)ctx->g.V * 24.0 * 16, 0.0);
-    launch_pack<double>(st, ctx->g, canon, blocked, 1, width, slot, nonzero);
+    launch_pack<double>(ctx, st, canon, blocked, 1, width, slot, nonzero);
     DD_HIP_TRY(hipGetLastError());
     return Status::ok();
 }
