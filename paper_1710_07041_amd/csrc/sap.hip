@@ -380,7 +380,7 @@ Status sweep(dd_ctx *ctx, SArgs a, int prec, const void *eta, void *psi, void *f
     const int fprec = sizeof(SF) == 8 ? DD_F64 : (sizeof(SF) == 4 ? DD_F32 : DD_F16);
     const int cls = prec == DD_F64 ? K_SAP_F64 : prec == DD_F32 ? K_SAP_F32 : K_SAP_F16;
     ProfScope ps(ctx->prof, ctx->stream, cls, sweep_bytes(a, sizeof(SF), sizeof(S), true),
-                 256.0 * a.nblk * a.nrhs * a.nmr * 2184.0, !quiet);
+                 256.0 * a.nblk * a.nrhs * (a.nmr * 2184.0 + (a.fresh ? 1848.0 : 0.0)), !quiet);
     a.rpg = rhs_per_group(a.nblk, a.nrhs, ctx->ncu * WAVES);
     // a direction that one block spans wraps inside it
     const bool wrap = a.g.nb[0] == 1 || a.g.nb[1] == 1 || a.g.nb[2] == 1 || a.g.nb[3] == 1;
@@ -480,6 +480,8 @@ Status run_sap(dd_ctx *ctx, const double *m0, int nrhs, const void *eta, void *p
     void *resid = static_cast<char *>(scratch) + spinor_bytes(ctx->g, prec, nrhs);
     const bool quiet = slots && slots->quiet;
     TraceRange tr(eo ? "sap_eo" : "sap");
+    // the visits of cycle cy form their residual anew: the faces they read are psi's
+    const auto fresh = [&](int cy) { return prec == DD_F64 && !eo && cy > 0 && cy % FRESH_EVERY == 0; };
     for (int cy = 0; cy < ncy; ++cy)
         for (int col = 0; col < 2; ++col) {
             if (ctx->ncolour[col] == 0) continue;
@@ -487,7 +489,9 @@ Status run_sap(dd_ctx *ctx, const double *m0, int nrhs, const void *eta, void *p
             a.nblk = ctx->ncolour[col];
             a.mode = (cy == 0 && col == 0) ? 0 : (cy == 0 ? 1 : 2);
             a.publish = !(cy == ncy - 1 && col == 1);
-            a.write_r = cy < ncy - 1;
+            a.write_r = cy < ncy - 1 && !fresh(cy + 1);
+            a.fresh = fresh(cy);
+            a.psi_faces = fresh(col == 0 ? cy : cy + 1);
             if (eo) {
                 DD_TRY((prec == DD_F64   ? sweep_eo<double, double, 1>(ctx, a, prec, eta, psi, faces, quiet)
                         : prec == DD_F32 ? sweep_eo<float, float, 2>(ctx, a, prec, eta, psi, faces, quiet)

@@ -35,6 +35,14 @@ namespace dd {
 // against 6.75 ms; 32^3x64, FP32: 8.98 against 6.70 ms.
 template <typename S, bool WRAP, bool SIG> constexpr bool PSI_LDS = sizeof(S) < 8 || WRAP || !SIG;
 
+// The carried residual lets the rounding of psi add up from visit to visit.  FP64
+// arithmetic, which formed it anew at every visit before it was carried, does so
+// every FRESH_EVERY cycles: the error against exact sums is then at every count
+// of cycles what it was (8^4: 3.9e-16; carried throughout, 4.5e-16 after 32) for
+// 2% of the time of twelve cycles.  FP32 and FP16 have always carried it.
+template <typename S> constexpr bool FRESH = sizeof(S) == 8;
+constexpr int FRESH_EVERY = 8;
+
 template <typename S, typename A, bool PL> struct SweepLds {
     cx<A> tf[6][BS];   // projected half spinors for the +t hops
     cx<A> tb[6][BS];   // U^+ times projected half spinors for the -t hops
@@ -101,6 +109,8 @@ struct SArgs {
     int r12;              // links stored as SU(3): read two rows, rebuild the third
     int sig;              // the clover term is sigma . F: mirrored slots are not read
     int write_r;          // plain sweep: store the block residual for the next visit
+    int fresh;            // plain FP64 sweep: form the block residual from psi (the faces are psi's)
+    int psi_faces;        // plain FP64 sweep: publish the faces of psi, not of delta
 };
 
 // The block (grid x) and the right-hand sides [r0, r1) (grid y) of this
@@ -195,29 +205,41 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(WAVES))) voi
 #pragma unroll
             for (int c = 0; c < 12; ++c) L.psi[c][s] = psi[sp + c * BS];
         }
-        const vec2_t<S> *__restrict__ src = a.mode == 2 ? resid : eta;
+        // (FP64: where a.fresh is set, eta - (D psi)_B)
+        const bool fresh = FRESH<S> && a.fresh;
+        const vec2_t<S> *__restrict__ src = a.mode == 2 && !fresh ? resid : eta;
         vec2_t<S> er[12];
-#pragma unroll
-        for (int c = 0; c < 12; ++c) er[c] = src[sp + c * BS];
         cx<A> rr[12], q[12];
+        const auto take_rho = [&]() {
 #pragma unroll
-        for (int c = 0; c < 12; ++c) q[c] = mk<A>(0, 0);
-        if (!PL && a.mode != 0) {
-            vec2_t<S> f[6];
-            blk_face_load<0, S, A>(a.g, b, bc, s, r, a.nrhs, faces, f);
-            blk_face_add<0, S, A>(a.g, bc, s, f, U[0], q, q + 6);
-            blk_face_load<1, S, A>(a.g, b, bc, s, r, a.nrhs, faces, f);
-            blk_face_add<1, S, A>(a.g, bc, s, f, U[1], q, q + 6);
-            blk_face_load<2, S, A>(a.g, b, bc, s, r, a.nrhs, faces, f);
-            blk_face_add<2, S, A>(a.g, bc, s, f, U[2], q, q + 6);
-            blk_face_load<3, S, A>(a.g, b, bc, s, r, a.nrhs, faces, f);
-            blk_face_add<3, S, A>(a.g, bc, s, f, U[3], q, q + 6);
-        }
-        if (PL && a.mode != 0) face_consume<S, A>(a.g, b, bc, s, r, a.nrhs, faces, U, q);
+            for (int c = 0; c < 12; ++c) er[c] = src[sp + c * BS];
+            if (!PL && a.mode != 0) {
+                vec2_t<S> f[6];
+                blk_face_load<0, S, A>(a.g, b, bc, s, r, a.nrhs, faces, f);
+                blk_face_add<0, S, A>(a.g, bc, s, f, U[0], q, q + 6);
+                blk_face_load<1, S, A>(a.g, b, bc, s, r, a.nrhs, faces, f);
+                blk_face_add<1, S, A>(a.g, bc, s, f, U[1], q, q + 6);
+                blk_face_load<2, S, A>(a.g, b, bc, s, r, a.nrhs, faces, f);
+                blk_face_add<2, S, A>(a.g, bc, s, f, U[2], q, q + 6);
+                blk_face_load<3, S, A>(a.g, b, bc, s, r, a.nrhs, faces, f);
+                blk_face_add<3, S, A>(a.g, bc, s, f, U[3], q, q + 6);
+            }
+            if (PL && a.mode != 0) face_consume<S, A>(a.g, b, bc, s, r, a.nrhs, faces, U, q);
 #pragma unroll
-        for (int c = 0; c < 12; ++c) rr[c] = ldc<A>(&er[c]) - q[c];
-        // MR on D_BB: delta += alpha r, r -= alpha q
+            for (int c = 0; c < 12; ++c) rr[c] = ldc<A>(&er[c]) - q[c];
+        };
         int it = 0;
+        if (fresh) {
+            // step -1 of the loop applies D_BB to psi
+#pragma unroll
+            for (int c = 0; c < 12; ++c) rr[c] = ldc<A>(psi + sp + c * BS);
+            it = -1;
+        } else {
+#pragma unroll
+            for (int c = 0; c < 12; ++c) q[c] = mk<A>(0, 0);
+            take_rho();
+        }
+        // MR on D_BB: delta += alpha r, r -= alpha q
         for (; it < a.nmr; ++it) {
 #pragma unroll
             for (int c = 0; c < 12; ++c) q[c] = mk<A>(0, 0);
@@ -259,6 +281,11 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(WAVES))) voi
                     if (clover_reads(SIG, e)) c2[e] = ldc<A>(&c2late[e]);
                 clover_half_mac<A, SIG>(c2, diag, rr + 6, q + 6);
             }
+            if (FRESH<S> && it < 0) { // uniform
+                take_rho();
+                __syncthreads(); // this step's reads of the t buffers end here
+                continue;
+            }
             cx<A> alpha;
             if (!mr_alpha(L, lane, wave, q, rr, alpha)) break;
 #pragma unroll
@@ -282,15 +309,13 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(WAVES))) voi
         }
 #pragma unroll
         for (int c = 0; c < 12; ++c) rr[c] = it > 0 ? L.del[c][s] : mk<A>(0, 0);
-        if (a.publish) {
-            face_publish<S, A>(faces, b, a.nrhs, r, s, rr, U);
-        }
+        if (a.publish && !(FRESH<S> && a.psi_faces)) face_publish<S, A>(faces, b, a.nrhs, r, s, rr, U);
 #pragma unroll
         for (int c = 0; c < 12; ++c) {
-            cx<A> v = rr[c];
-            if (a.mode == 2) v = v + ldc<A>(PL ? &L.psi[PL ? c : 0][s] : &er[c]);
-            stc(psi + sp + c * BS, v);
+            if (a.mode == 2) rr[c] = rr[c] + ldc<A>(PL ? &L.psi[PL ? c : 0][s] : &er[c]);
+            stc(psi + sp + c * BS, rr[c]);
         }
+        if (FRESH<S> && a.publish && a.psi_faces) face_publish<S, A>(faces, b, a.nrhs, r, s, rr, U);
     }
 }
 
