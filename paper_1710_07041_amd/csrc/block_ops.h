@@ -286,7 +286,8 @@ __device__ __forceinline__ void blk_t_take(LT &L, const Geom &g, int b, const in
 // ---------------------------------------------------------------------------
 // Face buffers of the Schwarz sweep.  A block that has just been solved
 // publishes, for each of its boundary sites and a spinor p (its update delta
-// in the plain sweep, its psi in the even-odd sweep), the half spinor that
+// in the plain sweep, its psi in the even-odd sweep and where the next visits of
+// the plain one form their residual anew), the half spinor that
 // the neighbouring block (of the other colour) needs for the hop into it:
 //   face 2 mu     (sites with l_mu = 0): h = (1 - gamma_mu) p, projected,
 //                 for the +mu hop of the block below, which applies its own

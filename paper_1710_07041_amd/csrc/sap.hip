@@ -30,7 +30,8 @@
 // neighbouring blocks of the other colour made in between (on the first
 // visit R_B = eta_B).  The hops of delta arrive through face buffers that the
 // other colour published at the end of its solves (block_ops.h: six dense
-// components per boundary hop).
+// components per boundary hop).  FP64 forms the residual anew from psi every
+// eighth cycle, from faces of psi (FRESH, sap_sweep.h).
 // Blocks of one colour share no site and read only the other colour's data,
 // so a sweep needs no synchronisation between workgroups.
 //

@@ -15,9 +15,10 @@
 // registers (FP32 arithmetic), so no memory load sits inside the step.
 // Measured together, twelve FP32 cycles at 32^3x64: 7.07 -> 6.70 ms a call,
 // ten FP16 ones at 48^3x96: 23.4 -> 22.5 ms, twelve FP64 ones at 24^3x48, which
-// now carry the residual instead of recomputing it: 6.60 -> 6.05 ms.  The faces
-// are published by the even-odd sweep's routine, a whole half spinor at a time:
-// 6.70 -> 6.64 and 6.14 -> 6.01 ms against one that goes spin by spin.
+// now carry the residual: 6.60 -> 6.05 ms.  The faces are published by the
+// even-odd sweep's routine, a whole half spinor at a time: 6.70 -> 6.64 and 6.14
+// -> 6.01 ms against one that goes spin by spin; forming FP64's residual anew
+// every eighth cycle takes 0.06 ms of that back.
 // More wavefronts did not pay: three workgroups per CU (168 registers, link
 // rows rebuilt at each use) spill, 15.4 ms in FP32; two threads per site (512
 // threads a block at 128 registers) double the LDS traffic and the barriers,
@@ -29,11 +30,13 @@
 namespace dd {
 
 // FP64 data read psi again at the end of the visit and take the faces in an
-// unrolled loop; FP32 arithmetic, at half the registers a thread, and the FP64
-// kernels with wrap tests or a full clover term spill with either: they keep
-// psi in LDS meanwhile (PL) and one face trip in flight.  24^3x48, FP64: 6.05
-// against 6.75 ms; 32^3x64, FP32: 8.98 against 6.70 ms.
-template <typename S, bool WRAP, bool SIG> constexpr bool PSI_LDS = sizeof(S) < 8 || WRAP || !SIG;
+// unrolled loop; FP32 arithmetic, at half the registers a thread, spills with
+// either: it keeps psi in LDS meanwhile (PL) and one face trip in flight.
+// 24^3x48, FP64: 6.05 against 6.75 ms, with an explicit clover term (eight
+// registers spilled) 6.54 against 7.07; 4x24^2x48 with four right-hand sides 3.54
+// against 3.85, explicit (twenty spilled) 3.77 against 4.16; 32^3x64, FP32: 8.98
+// against 6.70 ms.
+template <typename S> constexpr bool PSI_LDS = sizeof(S) < 8;
 
 // The carried residual lets the rounding of psi add up from visit to visit.  FP64
 // arithmetic, which formed it anew at every visit before it was carried, does so
@@ -170,7 +173,7 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(WAVES))) voi
     const vec2_t<S> *__restrict__ eta0, vec2_t<S> *__restrict__ psi0, const vec2_t<SF> *__restrict__ links,
     const vec2_t<SF> *__restrict__ clov, vec2_t<S> *__restrict__ faces, vec2_t<S> *__restrict__ resid, SArgs a)
 {
-    constexpr bool PL = PSI_LDS<S, WRAP, SIG>;
+    constexpr bool PL = PSI_LDS<S>;
     __shared__ SweepLds<S, A, PL> L;
     int b, rhs0, rhs1;
     if (!sweep_part(a, b, rhs0, rhs1)) return;
