@@ -20,7 +20,8 @@ from collections import defaultdict
 from pathlib import Path
 
 PKG = Path(__file__).resolve().parent
-KERNEL_SOURCES = ["csrc/sap.hip", "csrc/dslash.hip", "csrc/dd_device.h", "csrc/block_ops.h", "csrc/engine.hip"]
+KERNEL_SOURCES = ["csrc/sap.hip", "csrc/sap_sweep.h", "csrc/dslash.hip", "csrc/dd_device.h", "csrc/block_ops.h",
+                  "csrc/engine.hip"]
 COPY_BYTES = 1 << 30
 
 CLASS_PATTERNS = [
