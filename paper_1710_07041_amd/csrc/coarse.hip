@@ -1055,13 +1055,6 @@ Status amg_reserve(dd_ctx *ctx, AmgWork &wk, int W, int prec, int kmax)
 AmgWork *amg_work_new() { return new AmgWork(); }
 void AmgWorkDeleter::operator()(AmgWork *w) const { delete w; }
 
-size_t amg_work_bytes(const dd_ctx *ctx, int W, int prec, int kmax, int N)
-{
-    const size_t nc = (size_t)ctx->g.nblocks * 2 * N, cv = nc * 16 * W;
-    return cv * (kmax + 4) + (size_t)W * CG * (2 * kmax + 3) * 16 + W * sizeof(GState) +
-           4 * spinor_bytes(ctx->g, prec, W) + sap_scratch_bytes(ctx->g, prec, W);
-}
-
 // k-step GMRES from zero on (D_c + m0_r) x_r = b_r for the W slots (b in
 // wk.xb, x to wk.xx); device only.
 Status coarse_gmres(dd_ctx *ctx, AmgWork &wk, int W, int k, const double *m0_dev, const int *active)

@@ -377,32 +377,6 @@ __device__ __forceinline__ void clover_half_mac(const cx<A> c[18], A diag, const
         }
 }
 
-// acc += (diag + C) p, C = two packed Hermitian 6x6 halves (36 slots)
-template <typename A>
-__device__ __forceinline__ void clover_mac(const cx<A> cl[36], A diag, const cx<A> p[12], cx<A> acc[12])
-{
-#pragma unroll
-    for (int k = 0; k < 2; ++k) {
-        const cx<A> *c = cl + 18 * k;
-        const cx<A> *x = p + 6 * k;
-        A d[6] = {c[0].re, c[0].im, c[1].re, c[1].im, c[2].re, c[2].im};
-        cx<A> y[6];
-#pragma unroll
-        for (int i = 0; i < 6; ++i) y[i] = (d[i] + diag) * x[i];
-        int e = 3;
-#pragma unroll
-        for (int i = 0; i < 6; ++i)
-#pragma unroll
-            for (int j = i + 1; j < 6; ++j) {
-                cmac(y[i], c[e], x[j]);
-                cmacc(y[j], c[e], x[i]);
-                ++e;
-            }
-#pragma unroll
-        for (int i = 0; i < 6; ++i) acc[6 * k + i] = acc[6 * k + i] + y[i];
-    }
-}
-
 // ---------------------------------------------------------------------------
 // geometry of the blocked lattice
 // ---------------------------------------------------------------------------
