@@ -360,8 +360,25 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(WAVES))) voi
         for (int e = 0; e < 18; ++e) c2[e] = cp[(18 + e) * BS];
     }
 
+    // FP16 data leave room for one face hop's spinor of the next right-hand side,
+    // in flight during the present one (32^3x64 with two 310 -> 297 us, with twelve
+    // 1456 -> 1393; with wrap tests it is slower, 4x24^2x48 with two 17.7 -> 18.8,
+    // and next to a full clover term it spills)
+    constexpr bool AHEAD = sizeof(SI) == 2 && SIG && !WRAP;
+    vec2_t<SI> wn[AHEAD ? 12 : 1];
+    const auto face0 = [&](int r) {
+        const vec2_t<SI> *pp = in + (a.in_off ? a.in_off[r] : 0) + ((long)h0.bn * a.nrhs + r) * 12 * BS + h0.sn;
+#pragma unroll
+        for (int c = 0; c < 12; ++c) wn[c] = pp[c * BS];
+    };
+    if constexpr (AHEAD) face0(blockIdx.y * a.rpg);
     for (int r = blockIdx.y * a.rpg; r < rend; ++r) {
-        if (a.active && !a.active[r]) continue; // uniform over the workgroup
+        if (a.active && !a.active[r]) { // uniform over the workgroup
+            if constexpr (AHEAD) {
+                if (r + 1 < rend) face0(r + 1);
+            }
+            continue;
+        }
         const A diag = (A)(4.0 + (a.m0_dev ? a.m0_dev[r] : a.m0[r]));
         const vec2_t<SI> *__restrict__ inr = in + (a.in_off ? a.in_off[r] : 0);
         const long sp = ((long)b * a.nrhs + r) * 12 * BS + s;
@@ -378,7 +395,7 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(WAVES))) voi
             const vec2_t<SI> *pp = inr + ((long)h.bn * a.nrhs + r) * 12 * BS + h.sn;
             cx<A> W[9], w[12];
 #pragma unroll
-            for (int c = 0; c < 12; ++c) w[c] = ldc<A>(pp + c * BS);
+            for (int c = 0; c < 12; ++c) w[c] = AHEAD && j == 0 ? ldc<A>(&wn[AHEAD ? c : 0]) : ldc<A>(pp + c * BS);
 #pragma unroll
             for (int e = 0; e < 6; ++e) W[e] = ldc<A>(&L.fl[j][e][s]);
             if (r12) {
@@ -392,6 +409,9 @@ __global__ __launch_bounds__(BS) __attribute__((amdgpu_waves_per_eu(WAVES))) voi
                 }
             }
             face_hop_post(h, w, W, s, L.fb[j]);
+        }
+        if constexpr (AHEAD) {
+            if (r + 1 < rend) face0(r + 1);
         }
         cx<A> x[12], q[12];
 #pragma unroll
