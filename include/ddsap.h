@@ -193,7 +193,10 @@ dd_status dd_unpack_spinor(dd_ctx *ctx, const void *blocked, double *canon, int 
 
 /* y = D x for nrhs right-hand sides, right-hand side r with mass m0[r]
  * (host array of nrhs doubles).  x, y: blocked device buffers of precision
- * prec; they must not overlap. */
+ * prec; they must not overlap.  Which kernel runs depends on nrhs, the lattice,
+ * the fields' form and the device's number of compute units, so a right-hand
+ * side's result alone and in a batch may differ in its last bits (repeated
+ * calls do not). */
 dd_status dd_apply_D(dd_ctx *ctx, const double *m0, const void *x, void *y, int prec, int nrhs);
 
 /* y_B = D_BB x_B on one Schwarz block (canonical block id): D restricted to

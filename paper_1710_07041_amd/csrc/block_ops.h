@@ -357,8 +357,10 @@ __device__ __forceinline__ FaceHop face_hop(const Geom &g, int b, const int bc[4
 // multiply-adds.  Which of two products a sum fuses is otherwise the compiler's
 // choice and changes with the code around it, and the adaptive rounds of the
 // two-level setup magnify a last bit of the FP32 residual (8^4, twelve vectors,
-// two rounds: 1e-8 in the residual moves the interpolation by 6e-6).  In this
-// order an interpolation stays what it was, bit for bit; it costs no time.
+// two rounds: 1e-8 in the residual moves the interpolation by 6e-6).  Either
+// choice is as good; the ones here, which differ by spin and by direction, are
+// those that interpolations have been made with so far, and keep them what they
+// were, bit for bit.  It costs no time.
 template <typename A> __device__ __forceinline__ void face_mul(const cx<A> U[9], const cx<A> h[6], cx<A> out[6])
 {
 #pragma unroll
